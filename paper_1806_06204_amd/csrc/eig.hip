@@ -11,8 +11,8 @@
 //  2. Divide and conquer on T (Cuppen's method): T splits into 1 x 1 blocks
 //     by removing every off-diagonal coupling (a rank-one term each); blocks
 //     are merged pairwise, bottom up, each merge solving the eigenproblem of
-//     D + rho z z^T: deflation, the secular equation by bisection (one
-//     thread per root), Gu-Eisenstat eigenvectors, and the product of the
+//     D + rho z z^T: deflation, the secular equation by a bracketed rational
+//     iteration (one wave per root), Gu-Eisenstat eigenvectors, and the product of the
 //     merged block's eigenvectors with that solution (matrix cores).
 //  3. Back-transformation V = Q V_T with the reflectors of stage 1 in
 //     blocks of kBT, on the matrix cores.
@@ -369,53 +369,78 @@ __global__ void dc_rotate(DcArgs a) {
     }
 }
 
-// One thread per root: bisection of the secular equation.
-__global__ void dc_secular(DcArgs a) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
+// One wave per root: the sums over the K poles are spread over its lanes, so
+// a root costs about a dozen evaluations of K / 64 terms per lane.  Bound: FP64
+// division (one per term).  One thread per root with plain bisection (some 60
+// evaluations of K terms, one wave per 64 roots) left most of the chip idle:
+// 111 ms of the 401 ms of Zolo-SVD at n = 4096, 19 of 55 ms at 900 x 600;
+// with this kernel (and dc_lowner and dc_rank spread the same way) the two
+// calls take 288 and 36 ms.
+__global__ __launch_bounds__(kET) void dc_secular(DcArgs a) {
+    const int p = blockIdx.x * (kET / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (p >= a.n) return;
     const int g = p / (2 * a.s), A0 = 2 * a.s * g, t = p - A0, K = a.K[g];
     if (K < 0 || t >= K) return;
+    const double* pole = a.pole + A0;
+    const double* zp = a.zp + A0;
+    const double rho = a.rho[g];
+    auto sums = [&](double origin, double x, int split) {
+        double f = 0.0, dpsi = 0.0, dphi = 0.0;
+#pragma unroll 4
+        for (int j = lane; j < K; j += 64) {
+            const double z = zp[j], q = z / ((pole[j] - origin) - x);
+            f += z * q;
+            if (j <= split) dpsi += q * q;
+            else dphi += q * q;
+        }
+        return dc::SecularSums{1.0 / rho + wave_sum(f), wave_sum(dpsi), wave_sum(dphi)};
+    };
     int o;
     double tau;
-    dc::secular_root(K, a.pole + A0, a.zp + A0, a.rho[g], t, &o, &tau);
-    a.org[A0 + t] = o;
-    a.tau[A0 + t] = tau;
+    dc::secular_root(K, pole, rho, t, &o, &tau, sums);
+    if (lane == 0) {
+        a.org[p] = o;
+        a.tau[p] = tau;
+    }
 }
 
-// Gu-Eisenstat z and the new eigenvalues (roots, then deflated values).
-__global__ void dc_lowner(DcArgs a) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
+// Gu-Eisenstat z and the new eigenvalues (roots, then deflated values), one
+// wave per entry.
+__global__ __launch_bounds__(kET) void dc_lowner(DcArgs a) {
+    const int p = blockIdx.x * (kET / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (p >= a.n) return;
     const int g = p / (2 * a.s), A0 = 2 * a.s * g, t = p - A0, K = a.K[g];
-    if (K < 0) {
-        a.vals[p] = a.D[p];
+    if (K < 0 || t >= K) {
+        if (lane == 0) a.vals[p] = K < 0 ? a.D[p] : a.dval[p];
         return;
     }
-    if (t < K) {
-        a.zh[p] = dc::lowner_z(K, a.pole + A0, a.zp + A0, a.rho[g], a.org + A0, a.tau + A0, t);
+    double prod = dc::lowner_product(K, a.pole + A0, a.org + A0, a.tau + A0, t, lane, 64);
+    for (int off = 32; off > 0; off >>= 1) prod *= __shfl_xor(prod, off, 64);
+    if (lane == 0) {
+        a.zh[p] = dc::lowner_z(K, a.pole + A0, a.zp[p], a.rho[g], a.org + A0, a.tau + A0, t, prod);
         a.vals[p] = a.pole[A0 + a.org[p]] + a.tau[p];
-    } else {
-        a.vals[p] = a.dval[p];
     }
 }
 
-// Ascending order of the new eigenvalues of each group: inv[A0 + rank] = t.
-__global__ void dc_rank(DcArgs a) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
+// Ascending order of the new eigenvalues of each group: inv[A0 + rank] = t
+// (one wave per value).
+__global__ __launch_bounds__(kET) void dc_rank(DcArgs a) {
+    const int p = blockIdx.x * (kET / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (p >= a.n) return;
     const int g = p / (2 * a.s), A0 = 2 * a.s * g, t = p - A0, K = a.K[g];
     if (K < 0) {
-        a.inv[p] = t;
+        if (lane == 0) a.inv[p] = t;
         return;
     }
     const int k = min(2 * a.s, a.n - A0);
     const double x = a.vals[p];
     int rank = 0;
-    for (int u = 0; u < k; ++u) {
+    for (int u = lane; u < k; u += 64) {
         const double y = a.vals[A0 + u];
         rank += (y < x || (y == x && u < t)) ? 1 : 0;
     }
-    a.inv[A0 + rank] = t;
+    for (int off = 32; off > 0; off >>= 1) rank += __shfl_xor(rank, off, 64);
+    if (lane == 0) a.inv[A0 + rank] = t;
 }
 
 // One workgroup per output column p of the group's k x k block of U, and the
@@ -580,9 +605,10 @@ hipError_t syevd(int n, double* A, long long lda, double* w_host, double* Z, lon
             const int k = std::min(2 * s, n);
             dc_rotate<<<dim3(std::max(1, std::min(64, (k + kET - 1) / kET)), ngroups), kET, 0, st>>>(da);
         }
-        dc_secular<<<(n + 63) / 64, 64, 0, st>>>(da);
-        dc_lowner<<<(n + 63) / 64, 64, 0, st>>>(da);
-        dc_rank<<<(n + 63) / 64, 64, 0, st>>>(da);
+        const int gwave = (n + kET / 64 - 1) / (kET / 64);   // one wave per root
+        dc_secular<<<gwave, kET, 0, st>>>(da);
+        dc_lowner<<<gwave, kET, 0, st>>>(da);
+        dc_rank<<<gwave, kET, 0, st>>>(da);
         dc_vectors<<<n, kET, 0, st>>>(da);
         if ((err = fill_matrix<double>(n, n, Qb, ld, 0, 1, 0.0, 0.0, st)) != hipSuccess) return err;
         if (2 * s <= 64) {

@@ -97,42 +97,106 @@ struct DeflateScan {
     }
 };
 
+// Sums over the poles at a point x of the secular equation, x measured from
+// an origin pole: f = 1/rho + sum_j z_j^2 / (delta_j - x), and the derivative
+// split at pole t: dpsi over j <= t, dphi over j > t (both positive).
+struct SecularSums {
+    double f, dpsi, dphi;
+};
+
+// Bracketed rational iteration for one root.  The bracket [lo, hi] always
+// holds the sign change of f and ends when its ends are neighbouring numbers,
+// as plain bisection does.  Between evaluations the next point is the zero of
+//   c + p / (delta_t - y) + q / (delta_{t+1} - y),
+// fitted to the value and to the two parts of the derivative at x (the
+// "middle way" of Li 1993; the last root has no pole to its right, q = 0).
+// Once a step is a few units in the last place, points a few units further
+// on the other side of the root close the bracket.  A point outside the
+// bracket, or slow progress, falls back to the midpoint.
+struct SecularIter {
+    double lo, hi, x, probe;
+    int steps;
+
+    ZOLO_HD void begin(double lo_, double hi_) {
+        lo = lo_;
+        hi = hi_;
+        x = probe = 0.0;
+        steps = 0;
+    }
+    // False when the bracket is closed; otherwise x is the next point.
+    ZOLO_HD bool next() {
+        const double m = 0.5 * (lo + hi);
+        if (!(m > lo && m < hi)) return false;
+        if (!(x > lo && x < hi)) x = m;
+        return true;
+    }
+    // The next point from the sums at x; dl = delta_t - x < 0 and
+    // dr = delta_{t+1} - x > 0 (ignored for the last root).
+    ZOLO_HD void propose(const SecularSums& s, double dl, double dr, bool last) {
+        double eta;
+        if (last) {
+            eta = dl + s.dpsi * dl * dl / (s.f - dl * s.dpsi);
+        } else {
+            const double dd = dl * dr;
+            const double a = (dl + dr) * s.f - dd * (s.dpsi + s.dphi), b = dd * s.f;
+            const double c = s.f - dl * s.dpsi - dr * s.dphi;
+            const double disc = sqrt(fmax(a * a - 4.0 * b * c, 0.0));
+            eta = a <= 0.0 ? (a - disc) / (2.0 * c) : 2.0 * b / (a + disc);
+        }
+        const double ulp = 2.0 * kEps * fabs(x);
+        ++steps;
+        if (!(fabs(eta) > 2.0 * ulp)) {          // converged (or NaN): close the bracket
+            if (probe == 0.0) probe = 2.0 * ulp;
+            x = s.f > 0.0 ? x - probe : x + probe;
+            probe *= 4.0;
+        } else if (steps > 12 && (steps & 1)) {
+            x = 0.5 * (lo + hi);
+        } else {
+            x += eta;
+        }
+    }
+    ZOLO_HD void cut(double f) {
+        if (f > 0.0) hi = x;
+        else lo = x;
+    }
+};
+
 // Root t (0 <= t < K) of the secular equation 1 + rho sum_j zp_j^2 / (pole_j - lambda) = 0
 // with poles strictly increasing and rho > 0: lambda_t lies in (pole_t, pole_{t+1})
 // (the last in (pole_{K-1}, pole_{K-1} + rho)).  lambda is returned as
 // pole[*org] + *tau with the origin the nearer pole, so that the distances
 // pole_j - lambda = (pole_j - pole_org) - tau keep their relative accuracy.
-// Bisection on tau to the last bit.
-ZOLO_HD inline void secular_root(int K, const double* pole, const double* zp, double rho, int t, int* org,
-                                 double* tau) {
+// sums(origin, x, t) gives the SecularSums at origin + x.
+template <class Sums>
+ZOLO_HD inline void secular_root(int K, const double* pole, double rho, int t, int* org, double* tau, Sums sums) {
+    const bool last = t + 1 == K;
     const double left = pole[t];
-    const double right = t + 1 < K ? pole[t + 1] : pole[t] + rho;
+    const double right = last ? pole[t] + rho : pole[t + 1];
     int o = t;
-    double lo = 0.0, hi = right - left;
-    if (t + 1 < K) {
-        // g at the midpoint, relative to the left pole, picks the origin.
-        const double mid = 0.5 * (right - left);
-        double g = 1.0 / rho;
-        for (int j = 0; j < K; ++j) g += zp[j] * zp[j] / ((pole[j] - left) - mid);
-        if (g < 0.0) {          // root in the right half: measure from pole_{t+1}
+    SecularIter it;
+    it.begin(0.0, right - left);
+    if (!last) {
+        // f at the midpoint, relative to the left pole, picks the origin.
+        const double half = 0.5 * (right - left);
+        const SecularSums s = sums(left, half, t);
+        if (s.f < 0.0) {        // root in the right half: measure from pole_{t+1}
             o = t + 1;
-            lo = -mid;
-            hi = 0.0;
+            it.begin(-half, 0.0);
+            it.x = -half;
         } else {
-            hi = mid;
+            it.begin(0.0, half);
+            it.x = half;
         }
+        it.propose(s, -half, half, false);
     }
     const double po = pole[o];
-    for (int it = 0; it < 400; ++it) {
-        const double m = 0.5 * (lo + hi);
-        if (!(m > lo && m < hi)) break;
-        double g = 1.0 / rho;
-        for (int j = 0; j < K; ++j) g += zp[j] * zp[j] / ((pole[j] - po) - m);
-        if (g > 0.0) hi = m;
-        else lo = m;
+    for (int n = 0; n < 400 && it.next(); ++n) {
+        const SecularSums s = sums(po, it.x, t);
+        it.cut(s.f);
+        it.propose(s, (left - po) - it.x, (right - po) - it.x, last);
     }
     *org = o;
-    *tau = 0.5 * (lo + hi);
+    *tau = 0.5 * (it.lo + it.hi);
 }
 
 // pole_i - lambda_j for the root stored as (org_j, tau_j).
@@ -144,14 +208,25 @@ ZOLO_HD inline double pole_minus_root(const double* pole, int i, int org_j, doub
 // of diag(pole) + rho zh zh^T,
 //   zh_i^2 = (lambda_{K-1} - pole_i) / rho * prod_{j<i} (lambda_j - pole_i)/(pole_j - pole_i)
 //                                       * prod_{i<j<K} (lambda_{j-1} - pole_i)/(pole_j - pole_i),
-// every factor positive by interlacing; the sign of zp_i.
-ZOLO_HD inline double lowner_z(int K, const double* pole, const double* zp, double rho, const int* org,
-                               const double* tau, int i) {
-    double p = -pole_minus_root(pole, i, org[K - 1], tau[K - 1]) / rho;
-    for (int j = 0; j < i; ++j) p *= pole_minus_root(pole, i, org[j], tau[j]) / (pole[i] - pole[j]);
-    for (int j = i + 1; j < K; ++j) p *= pole_minus_root(pole, i, org[j - 1], tau[j - 1]) / (pole[i] - pole[j]);
+// every factor positive by interlacing and the products' at most 1.  This is
+// the product over j = first, first + step, ... of the factors of j != i.
+ZOLO_HD inline double lowner_product(int K, const double* pole, const int* org, const double* tau, int i, int first,
+                                     int step) {
+    double p = 1.0;
+    for (int j = first; j < K; j += step) {
+        if (j == i) continue;
+        const int r = j < i ? j : j - 1;
+        p *= pole_minus_root(pole, i, org[r], tau[r]) / (pole[i] - pole[j]);
+    }
+    return p;
+}
+
+// zh_i from the whole product; the sign of zp_i.
+ZOLO_HD inline double lowner_z(int K, const double* pole, double zp_i, double rho, const int* org, const double* tau,
+                               int i, double product) {
+    const double p = product * (-pole_minus_root(pole, i, org[K - 1], tau[K - 1]) / rho);
     const double v = sqrt(fmax(p, 0.0));
-    return zp[i] >= 0.0 ? v : -v;
+    return zp_i >= 0.0 ? v : -v;
 }
 
 }  // namespace dc

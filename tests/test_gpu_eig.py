@@ -53,6 +53,16 @@ def test_random_symmetric(z, n):
     check(z, (B + B.T) / 2)
 
 
+@pytest.mark.parametrize("n", [129, 513, 1025])
+def test_merges_past_a_wave(z, n):
+    # Merges whose pole count leaves a remainder over the 64 lanes that share
+    # a root, on a spectrum that deflates little and on one that deflates a lot.
+    rng = np.random.default_rng(950 + n)
+    V = W.haar(n, n, 80 + n)
+    for s in (rng.standard_normal(n), np.repeat(rng.standard_normal(n // 3 + 1), 3)[:n]):
+        check(z, (V * s) @ V.T)
+
+
 def test_graded_and_clustered_spectra(z):
     # The spectra H has in Zolo-SVD: log-spaced over 16 decades, and clusters
     # of nearly equal eigenvalues (many deflations in the merges).
