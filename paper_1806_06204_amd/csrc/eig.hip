@@ -29,7 +29,8 @@ namespace zolo {
 namespace {
 
 constexpr int kTB = 32;       // tridiagonalisation panel width
-constexpr int kBT = 128;      // reflectors per block of the back-transformation
+constexpr int kBT = 256;      // reflectors per block of the back-transformation
+constexpr int kFT = 128;      // reflectors whose T factor one workgroup forms in LDS
 constexpr int kET = 256;      // threads per workgroup
 constexpr int kMaxG = 512;    // workgroups of the row-parallel kernels (partial sums)
 
@@ -222,21 +223,99 @@ __global__ void trd_cleanup(int n, double* A, long long lda, double* d) {
     }
 }
 
-// T factor of the reflector block starting at column j0 (nb columns):
-// T[c][c] = tau_c, T[0:c, c] = -tau_c T[0:c, 0:c] S[0:c, c], S = V^T V.
-__global__ void form_t(int nb, const double* S, long long lds, const double* tau, double* T, long long ldt) {
-    for (int e = threadIdx.x; e < nb * nb; e += blockDim.x) T[(e % nb) + (long long)(e / nb) * ldt] = 0.0;
+// T factors (compact WY) of kFT reflectors each from S = V^T V, one workgroup
+// of 8 waves per factor: workgroup x forms the diagonal block of columns
+// kFT x ... of the reflectors, half x % 2 of back-transformation block x / 2.
+// Each wave first forms the T of its own 16 reflectors (lane = row, in
+// registers), then neighbouring factors are merged in LDS,
+//   T12 = -T1 (S12 T2),
+// on the matrix cores for 16, 32 and 64 reflectors a side.  Reflectors past
+// nref get tau = 0, so their rows and columns of T are zero.  Bound: latency of
+// the 16-column recurrence and of the three merges.  One thread per row with
+// T in global memory and a barrier per column took 0.73-0.87 ms for 128
+// reflectors (28 ms of Zolo-SVD at n = 4096; 900 x 600: 3.6 of 36 ms).  With
+// this kernel, one launch for all blocks, S and V aligned for the pipelined
+// GEMM and 256 reflectors a block, the two calls went from 288 to 248 and from
+// 36.0 to 32.1 ms.
+constexpr int kFTld = kFT + 2;
+constexpr size_t kFormTLds = (size_t)kFTld * kFT * sizeof(double);
+__global__ __launch_bounds__(512) void form_t(int nref, const double* S, const double* tau, double* T) {
+    extern __shared__ double Tl[];               // T[i][j] at i + j kFTld
+    __shared__ double Sl[kFT / 16][16][17];      // S's 16 x 16 diagonal blocks
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int c0 = blockIdx.x * kFT, half = (blockIdx.x & 1) * kFT;
+    const long long blk = (long long)(blockIdx.x >> 1) * kBT * kBT;
+    const double* Sb = S + blk + half + (long long)half * kBT;
+    for (int e = tid; e < kFTld * kFT; e += 512) Tl[e] = 0.0;
+    for (int e = tid; e < kFT * 16; e += 512) {
+        const int q = e / 256, r = e % 16, c = (e / 16) % 16;
+        Sl[q][r][c] = r < c ? Sb[16 * q + r + (long long)(16 * q + c) * kBT] : 0.0;
+    }
     __syncthreads();
-    for (int c = 0; c < nb; ++c) {
-        const double t = tau[c];
-        const int i = threadIdx.x;
-        double s = 0.0;
-        if (i < c)
-            for (int k = i; k < c; ++k) s += T[i + (long long)k * ldt] * S[k + (long long)c * lds];
-        __syncthreads();
-        if (i < c) T[i + (long long)c * ldt] = -t * s;
-        if (i == c) T[c + (long long)c * ldt] = t;
-        __syncthreads();
+    {
+        // T[i][c] = -tau_c sum_{i <= k < c} T[i][k] S[k][c], T[c][c] = tau_c.
+        const int i = lane & 15;
+        double row[16];
+#pragma unroll
+        for (int c = 0; c < 16; ++c) {
+            const int gc = c0 + 16 * w + c;
+            const double t = gc < nref ? tau[gc] : 0.0;
+            double s = 0.0;
+#pragma unroll
+            for (int k = 0; k < c; ++k) s += row[k] * Sl[w][k][c];
+            row[c] = i == c ? t : (i < c ? -t * s : 0.0);
+        }
+        if (lane < 16) {
+#pragma unroll
+            for (int c = 0; c < 16; ++c) Tl[16 * w + i + (16 * w + c) * kFTld] = row[c];
+        }
+    }
+    __syncthreads();
+    const int li = lane & 15, lk = lane >> 4;
+    for (int s = 16; s < kFT; s *= 2) {
+        const int ts = s / 16, per = ts * ts;    // 16 x 16 tiles of one merge
+        const int total = kFT / (2 * s) * per;   // 4, 8, 16
+        d4 acc[2];
+        // Y = S12 T2 into the place of T12, then T12 = -T1 Y.
+        for (int phase = 0; phase < 2; ++phase) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int tile = w + 8 * u;
+                acc[u] = d4{0, 0, 0, 0};
+                if (tile >= total) continue;
+                const int o = tile / per * 2 * s, ti = tile % per % ts * 16, tj = tile % per / ts * 16;
+                for (int k = 0; k < s; k += 4) {
+                    double x, y;
+                    if (phase == 0) {
+                        x = Sb[o + ti + li + (long long)(o + s + k + lk) * kBT];
+                        y = Tl[o + s + k + lk + (o + s + tj + li) * kFTld];
+                    } else {
+                        x = Tl[o + ti + li + (o + k + lk) * kFTld];
+                        y = Tl[o + k + lk + (o + s + tj + li) * kFTld];
+                    }
+                    acc[u] = mfma_f64_16x16x4(x, y, acc[u]);
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int tile = w + 8 * u;
+                if (tile >= total) continue;
+                const int o = tile / per * 2 * s, ti = tile % per % ts * 16, tj = tile % per / ts * 16;
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    Tl[o + ti + Mfma<double>::row(lane, e) + (o + s + tj + li) * kFTld] =
+                        phase == 0 ? acc[u][e] : -acc[u][e];
+            }
+            __syncthreads();
+        }
+    }
+    // The diagonal block of T, and zeros below it.
+    double* Tb = T + blk + (long long)half * kBT;
+    for (int e = tid; e < kFT * kFT; e += 512) {
+        const int i = e % kFT, j = e / kFT;
+        Tb[half + i + (long long)j * kBT] = Tl[i + j * kFTld];
+        if (half == 0) Tb[kFT + i + (long long)j * kBT] = 0.0;
     }
 }
 
@@ -511,7 +590,8 @@ T* carve(char*& p, size_t count) {
 
 size_t syevd_work_bytes(int n) {
     const size_t nn = (size_t)n * n, N = (size_t)n + 64;
-    return 3 * (nn * 8 + 256) + (size_t)n * kTB * 8 + 256 + (size_t)kBT * kBT * 8 * 2 + 512 +
+    const size_t nblk = ((size_t)n + kBT - 1) / kBT;
+    return 3 * (nn * 8 + 256) + (size_t)n * kTB * 8 + 256 + nblk * (2 * kBT * kBT + kFT * kFT) * 8 + 768 +
            20 * (N * 8 + 256) + 10 * (N * 4 + 256) + 4 * (kMaxG * 8 + 256) + 4096;
 }
 
@@ -528,8 +608,10 @@ hipError_t syevd(int n, double* A, long long lda, double* w_host, double* Z, lon
     double* Qb = carve<double>(p, (size_t)n * n);
     double* U = carve<double>(p, (size_t)n * n);
     double* W = carve<double>(p, (size_t)n * kTB);
-    double* S = carve<double>(p, (size_t)kBT * kBT);
-    double* Tf = carve<double>(p, (size_t)kBT * kBT);
+    const int nref = n - 1, nblk = (nref + kBT - 1) / kBT;
+    double* S = carve<double>(p, (size_t)nblk * kBT * kBT);
+    double* Tf = carve<double>(p, (size_t)nblk * kBT * kBT);
+    double* Y = carve<double>(p, (size_t)nblk * kFT * kFT);
     const size_t N = (size_t)n + 64;
     double *d = carve<double>(p, N), *e = carve<double>(p, N), *tau = carve<double>(p, N), *sc = carve<double>(p, N);
     double *y = carve<double>(p, N), *pq = carve<double>(p, N), *alpha = carve<double>(p, N);
@@ -651,33 +733,67 @@ hipError_t syevd(int n, double* A, long long lda, double* w_host, double* Z, lon
     gather_columns<<<dim3(std::max(1, std::min(64, (n + kET - 1) / kET)), n), kET, 0, st>>>(n, Qa, ld, perm, Z, ldz);
 
     // --- Stage 3: Z <- Q Z with the reflectors of stage 1 --------------------
-    const int nref = n - 1;
+    // Blocks of kBT reflectors.  A block's V is taken from row b0 on, one row
+    // above its first unit entry: that row is zero in V, and the operands keep
+    // the alignment of A's columns.
+    if (nref > 0) {
+        // S = V^T V of every block at once (upper tiles; the rows above a
+        // block are zero), then the T factors.
+        if ((err = fill_matrix<double>(kBT, kBT * nblk, S, kBT, 0, 1, 0.0, 0.0, st)) != hipSuccess) return err;
+        const int fullb = nref / kBT;
+        for (int part = 0; part < 2; ++part) {
+            const long long b0 = part == 0 ? 0 : (long long)fullb * kBT;
+            GemmDesc g;
+            g.m = g.n = part == 0 ? kBT : nref - (int)b0;
+            g.k = n - (int)b0; g.transa = 1;
+            g.batch = part == 0 ? fullb : 1;
+            if (g.m <= 0 || g.batch <= 0) continue;
+            g.A = g.B = A + b0 + b0 * lda; g.lda = g.ldb = lda;
+            g.strideA = g.strideB = (long long)kBT * lda;
+            g.C = S + (b0 / kBT) * kBT * kBT; g.ldc = kBT; g.strideC = (long long)kBT * kBT;
+            g.flags = kCUpperTiles | kCStoreUpper;
+            if ((err = gemm(g, st)) != hipSuccess) return err;
+        }
+        if ((err = hipFuncSetAttribute((const void*)form_t, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)kFormTLds)) != hipSuccess)
+            return err;
+        form_t<<<2 * nblk, 512, kFormTLds, st>>>(nref, S, tau, Tf);
+        if ((err = hipGetLastError()) != hipSuccess) return err;
+        GemmDesc y;  // Y = S12 T2
+        y.m = y.n = y.k = kFT; y.batch = nblk;
+        y.A = S + (long long)kFT * kBT; y.lda = kBT; y.strideA = (long long)kBT * kBT;
+        y.B = Tf + kFT + (long long)kFT * kBT; y.ldb = kBT; y.strideB = (long long)kBT * kBT;
+        y.C = Y; y.ldc = kFT; y.strideC = (long long)kFT * kFT;
+        y.flags = kBUpper;
+        if ((err = gemm(y, st)) != hipSuccess) return err;
+        GemmDesc t;  // T12 = -T1 Y
+        t.m = t.n = t.k = kFT; t.batch = nblk;
+        t.A = Tf; t.lda = kBT; t.strideA = (long long)kBT * kBT;
+        t.B = Y; t.ldb = kFT; t.strideB = (long long)kFT * kFT;
+        t.C = Tf + (long long)kFT * kBT; t.ldc = kBT; t.strideC = (long long)kBT * kBT;
+        t.alpha = -1.0; t.flags = kAUpper;
+        if ((err = gemm(t, st)) != hipSuccess) return err;
+    }
     const long long ldt = std::min(kBT, n);   // scratch U, Qb hold nb x n with nb <= ldt
-    for (int b0 = ((nref - 1) / kBT) * kBT; nref > 0 && b0 >= 0; b0 -= kBT) {
-        const int nb = std::min(kBT, nref - b0);
-        const int rows = n - b0 - 1;
-        const double* V = A + (b0 + 1) + (long long)b0 * lda;
-        GemmDesc s;  // S = V^T V
-        s.m = nb; s.n = nb; s.k = rows; s.transa = 1;
-        s.A = V; s.lda = lda; s.B = V; s.ldb = lda; s.C = S; s.ldc = kBT;
-        s.flags = kAUpper | kBLower;
-        if ((err = gemm(s, st)) != hipSuccess) return err;
-        form_t<<<1, kBT, 0, st>>>(nb, S, kBT, tau + b0, Tf, kBT);
-        GemmDesc w1;  // U = V^T Z[b0+1:, :]   (nb x n, in U)
+    for (int q = nblk - 1; q >= 0; --q) {
+        const int b0 = q * kBT, nb = std::min(kBT, nref - b0);
+        const int rows = n - b0;
+        const double* V = A + b0 + (long long)b0 * lda;
+        GemmDesc w1;  // U = V^T Z[b0:, :]   (nb x n, in U)
         w1.m = nb; w1.n = n; w1.k = rows; w1.transa = 1;
-        w1.A = V; w1.lda = lda; w1.B = Z + (b0 + 1); w1.ldb = ldz; w1.C = U; w1.ldc = ldt;
+        w1.A = V; w1.lda = lda; w1.B = Z + b0; w1.ldb = ldz; w1.C = U; w1.ldc = ldt;
         w1.flags = kAUpper;
         if ((err = gemm(w1, st)) != hipSuccess) return err;
         GemmDesc w2;  // Qb = T U
         w2.m = nb; w2.n = n; w2.k = nb;
-        w2.A = Tf; w2.lda = kBT; w2.B = U; w2.ldb = ldt; w2.C = Qb; w2.ldc = ldt;
+        w2.A = Tf + (long long)q * kBT * kBT; w2.lda = kBT; w2.B = U; w2.ldb = ldt; w2.C = Qb; w2.ldc = ldt;
         w2.flags = kAUpper;
         if ((err = gemm(w2, st)) != hipSuccess) return err;
-        GemmDesc w3;  // Z[b0+1:, :] -= V Qb
+        GemmDesc w3;  // Z[b0:, :] -= V Qb
         w3.m = rows; w3.n = n; w3.k = nb;
         w3.A = V; w3.lda = lda; w3.B = Qb; w3.ldb = ldt;
-        w3.Cin = Z + (b0 + 1); w3.ldcin = ldz; w3.beta = 1.0; w3.alpha = -1.0;
-        w3.C = Z + (b0 + 1); w3.ldc = ldz;
+        w3.Cin = Z + b0; w3.ldcin = ldz; w3.beta = 1.0; w3.alpha = -1.0;
+        w3.C = Z + b0; w3.ldc = ldz;
         w3.flags = kALower;
         if ((err = gemm(w3, st)) != hipSuccess) return err;
     }

@@ -63,6 +63,20 @@ def test_merges_past_a_wave(z, n):
         check(z, (V * s) @ V.T)
 
 
+@pytest.mark.parametrize("n", [128, 130, 256, 257, 258, 386])
+def test_back_transformation_block_edges(z, n):
+    # Reflector counts just below, at and past 128 (one factor in LDS) and 256
+    # (one block), even and odd leading dimensions.  The eigenvalues are
+    # settled before the back-transformation: residual and orthogonality judge it.
+    rng = np.random.default_rng(970 + n)
+    B = rng.standard_normal((n, n))
+    A = (B + B.T) / 2
+    w, Z = z.syevd(dev(A))
+    Z = Z.cpu().numpy()
+    assert np.linalg.norm(A @ Z - Z * w) <= 1e-14 * np.linalg.norm(A, 2) * np.sqrt(n)
+    assert np.linalg.norm(Z.T @ Z - np.eye(n)) <= 1e-15 * n
+
+
 def test_graded_and_clustered_spectra(z):
     # The spectra H has in Zolo-SVD: log-spaced over 16 decades, and clusters
     # of nearly equal eigenvalues (many deflations in the merges).
