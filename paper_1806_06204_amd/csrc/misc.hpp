@@ -37,9 +37,10 @@ hipError_t frob2(int m, int n, const double* X, long long ldx, const double* Y, 
                  double* out, hipStream_t st);
 // out[0] = ||G - I||_F^2 from the upper triangle of symmetric G.  part: >= 2048 doubles.
 hipError_t orth2(int n, const double* G, long long ldg, double* part, double* out, hipStream_t st);
-// v <- A^T A v / ||A^T A v||, *lam = v^T A^T A v (u: m, w: n scratch).
-hipError_t power_step(int m, int n, const double* A, long long lda, double* v, double* u, double* w, double* lam,
-                      hipStream_t st);
+// `steps` times v <- A^T A v / ||A^T A v||, lam[t] = v^T A^T A v of the unit v
+// before step t (u: m, w: n scratch).
+hipError_t power_steps(int m, int n, const double* A, long long lda, int steps, double* v, double* u, double* w,
+                       double* lam, hipStream_t st);
 hipError_t fill_vector(int n, double* v, double val, hipStream_t st);
 // p[0..count) = 0 by a kernel (not a memset node, so that it may be captured).
 hipError_t zero_ints(int* p, int count, hipStream_t st);

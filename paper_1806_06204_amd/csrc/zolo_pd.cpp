@@ -483,8 +483,7 @@ int pd_core(zolo_handle h, char* base, int m, int n, const double* A, int lda, d
         double lam_prev = 0.0;
         bool done = false;
         for (int chunk = 0; chunk < 10 && !done; ++chunk) {
-            for (int it = 0; it < 10; ++it)
-                HIPFIN(power_step(m, n, A, lda, w.vec_v, w.vec_u, w.vec_w, w.lam + it, st));
+            HIPFIN(power_steps(m, n, A, lda, 10, w.vec_v, w.vec_u, w.vec_w, w.lam, st));
             if ((rc = readback(h, w.lam, sizeof(double) * 10))) return finish(rc);
             for (int it = 0; it < 10; ++it) {
                 lam = h->host[it];
@@ -516,8 +515,7 @@ int pd_core(zolo_handle h, char* base, int m, int n, const double* A, int lda, d
             b = std::sqrt(lam) / alpha;
         } else {
             HIPFIN(fill_vector(n, w.vec_v, 1.0 / std::sqrt((double)n), st));
-            for (int it = 0; it < 4; ++it)
-                HIPFIN(power_step(m, n, w.X, m, w.vec_v, w.vec_u, w.vec_w, w.lam + it, st));
+            HIPFIN(power_steps(m, n, w.X, m, 4, w.vec_v, w.vec_u, w.vec_w, w.lam, st));
             if ((rc = readback(h, w.lam + 3, sizeof(double)))) return finish(rc);
             b = std::sqrt(std::max(h->host[0], 0.0));
             inf.flops_exec += 4.0 * m * (double)n * 4;
