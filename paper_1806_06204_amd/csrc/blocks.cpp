@@ -159,7 +159,8 @@ int zolo_structured_qr_batched(zolo_handle h, int m, int n, const double* pivots
     const size_t need = 14 * 256 + sizeof(double) * (2 * qr_w_elems(n, batch) + qr_tb_elems(n, batch) +
                                                      qr_ts_elems(n, batch) + 2 * blk + qr_split_elems(n, batch) +
                                                      qr_s_elems(batch) + part) +
-                        sizeof(unsigned) * qr_flag_elems(m, e, batch, h->panel_coresident) + 64;
+                        sizeof(unsigned) * qr_flag_elems(m, e, batch, h->panel_coresident) + 64 + 256 +
+                        sizeof(unsigned long long) * qr_colslot_elems(m, e, batch, h->panel_coresident);
     if (int rc = grow(h, need)) return rc;
     QrWork w;
     w.W = (double*)bump(h->arena, off, sizeof(double) * qr_w_elems(n, batch));
@@ -175,6 +176,8 @@ int zolo_structured_qr_batched(zolo_handle h, int m, int n, const double* pivots
     w.flag_elems = qr_flag_elems(m, e, batch, h->panel_coresident);
     w.flags = (unsigned*)bump(h->arena, off, sizeof(unsigned) * w.flag_elems);
     w.error_flag = (int*)bump(h->arena, off, 64);
+    w.colslot_elems = qr_colslot_elems(m, e, batch, h->panel_coresident);
+    w.colslots = (unsigned long long*)bump(h->arena, off, sizeof(unsigned long long) * w.colslot_elems);
     w.max_coresident = h->panel_coresident;
     hipStream_t st = h->stream;
     hipError_t err = hipMemsetAsync(w.error_flag, 0, sizeof(int), st);

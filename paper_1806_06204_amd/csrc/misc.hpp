@@ -91,6 +91,8 @@ struct QrWork {
     double* partials = nullptr;   // qr_partials_elems: per-workgroup exchange slots (kPanelSlot doubles, two parities)
     unsigned* flags = nullptr;    // qr_flag_elems: per-workgroup panel sequence flags
     size_t flag_elems = 0;
+    unsigned long long* colslots = nullptr;  // qr_colslot_elems: the panels' tagged column slots
+    size_t colslot_elems = 0;
     int* error_flag = nullptr;    // 1 int
     int max_coresident = 0;       // workgroups of the panel kernel that fit at once
 };
@@ -126,6 +128,12 @@ inline size_t qr_partials_elems(int m, int e, int batch, int max_coresident) {
 }
 inline size_t qr_flag_elems(int m, int e, int batch, int max_coresident) {
     return (size_t)batch * (qr_panel_groups(m, e, batch, max_coresident) + 1);
+}
+// 8-byte words of the column exchange per workgroup: two parities of 32
+// tagged 16-byte slots.
+constexpr int kPanelColWords = 2 * 32 * 2;
+inline size_t qr_colslot_elems(int m, int e, int batch, int max_coresident) {
+    return qr_flag_elems(m, e, batch, max_coresident) * kPanelColWords;
 }
 
 // M_b[0:m] = X (ld ldx; X null: leave the dense block), M_b[m:m+n] = pivots[b] * I, b < batch <= 16.

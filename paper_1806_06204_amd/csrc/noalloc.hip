@@ -18,9 +18,12 @@ namespace zolo {
 namespace {
 
 constexpr size_t kScratchBytes = (size_t)256 << 20;
+// Room after them for the workspace's tail (the panels' column slots, at most
+// about 1 KiB per co-resident workgroup), which the limit does not count.
+constexpr size_t kScratchTail = (size_t)1 << 20;
 constexpr int kMaxDevices = 64;
 
-static __device__ __align__(256) char scratch[kScratchBytes];
+static __device__ __align__(256) char scratch[kScratchBytes + kScratchTail];
 
 std::mutex g_scratch_mu;
 char* g_scratch_ptr[kMaxDevices] = {};
@@ -42,8 +45,6 @@ hipError_t scratch_address(int device, char** out) {
     return hipSuccess;
 }
 
-size_t scratch_bytes() { return kScratchBytes; }
-
 }  // namespace zolo
 
 extern "C" int zolo_pd_noalloc(zolo_handle h, int m, int n, const double* A, int lda, double alpha, double l,
@@ -52,7 +53,10 @@ extern "C" int zolo_pd_noalloc(zolo_handle h, int m, int n, const double* A, int
     zolo_opts opts;
     int rc = zolo::check_pd_args(h, m, n, A, lda, alpha, l, r, Qp, ldq, H, ldh, opts_in, &opts);
     if (rc) return zolo::report(info, rc);
-    if (zolo::workspace_bytes(h, m, n, r, opts) > zolo::scratch_bytes()) return zolo::report(info, ZOLO_SCRATCH);
+    size_t counted = 0;
+    const size_t bytes = zolo::workspace_bytes(h, m, n, r, opts, &counted);
+    if (counted > zolo::kScratchBytes || bytes > zolo::kScratchBytes + zolo::kScratchTail)
+        return zolo::report(info, ZOLO_SCRATCH);
     char* base = nullptr;
     if (zolo::scratch_address(h->device, &base) != hipSuccess) return zolo::report(info, ZOLO_HIP);
     return zolo::pd_core(h, base, m, n, A, lda, alpha, l, r, Qp, ldq, H, ldh, opts, info);

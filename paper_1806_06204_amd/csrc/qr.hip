@@ -15,16 +15,13 @@
 // Panel: one launch per panel factors all b together (a cooperative launch
 // when a matrix takes more than one workgroup).  Each matrix gets G
 // workgroups, each owning a slab of the panel's live rows.  The panel's 64
-// columns are factored in leaves of 16.  For column k a workgroup applies
-// reflector k-1 to the leaf's columns on its rows and, in the same pass,
-// accumulates the dot products of column k (below the pivot) with the
-// leaf's columns and picks up the pivot row; one cross-workgroup reduction
-// of these 32 numbers gives the norm, the update coefficients of the leaf's
-// remaining columns and the next column of the leaf's T (compact WY,
-// Q = I - V T V^T).  At the end of a leaf one MFMA reduction and one
-// exchange give V_leaf^T times the other panel columns, from which the
-// panel's T is extended and the rest of the panel takes the leaf's block
-// reflector.  Every reduction sums partials in a fixed order; its barrier
+// columns are factored in leaves of 16, held in registers.  Per column one
+// reduction over the rows gives the norm, the update coefficients of the
+// leaf's remaining columns and the products with the leaf's earlier
+// reflectors (compact WY, Q = I - V T V^T).  At the end of a leaf one MFMA
+// reduction and one exchange give V_leaf^T times the other panel columns,
+// from which the panel's T is formed and the rest of the panel takes the
+// leaf's block reflector.  Every reduction sums partials in a fixed order; its barrier
 // waits a bounded time.  On exit the panel's top block holds V explicitly
 // (unit diagonal, zeros above) and the R diagonal block is saved apart.
 //
@@ -41,9 +38,7 @@
 #include "misc.hpp"
 #include "stats.hpp"
 
-#include <cstdlib>
 #include <algorithm>
-#include <map>
 #include <mutex>
 
 namespace zolo {
@@ -58,20 +53,10 @@ constexpr int kRG = kPT / 64;            // row groups: every wave owns the leaf
 // Exchanges of one panel: one per column and one at the end of each leaf.
 constexpr int kPanelExchanges = kNB + kNL;
 static_assert(kLW * kOther == kPanelSlot, "exchange slot sized for the leaf-end sums");
-// Slab rows per lane loaded together in the column sweep: two when the
-// slab stays in global memory (latency of L2), one from LDS.
-template <bool InLds>
-constexpr int kRowUnroll = InLds ? 1 : 2;
-// Resident-leaf variant (one workgroup per matrix, slab in global memory):
-// while a leaf's columns are factored the leaf stays on chip, a thread's
-// rows first + 512 j in registers for j < kResJ and in LDS beyond, so that
-// a column's sweep touches no global memory.  It takes panels of at most
-// kResRows live rows (the LDS part then holds 1024 rows x 16 columns).
-constexpr int kResJ = 3;
-constexpr int kResRows = 2560;
-// Rows per lane step of the leaf-end MFMA reduction (loads issued together).
-template <bool InLds>
-constexpr int kQuadUnroll = InLds ? 2 : 16;
+// panel_kernel: slab rows per lane loaded together in the column sweep
+// (latency of L2), and rows per lane step of its leaf-end MFMA reduction.
+constexpr int kRowUnroll = 2;
+constexpr int kQuadUnroll = 16;
 // Cache-policy operand of a buffer load that makes it coherent at agent
 // scope (sc1 on gfx950), and the fourth word of a raw buffer resource.
 constexpr int kCoherentLoad = 16;
@@ -85,20 +70,14 @@ struct PanelArgs {
     double* P; long long ld, sp;         // panel top-left (row p0, column p0) of matrix 0
     double* T; long long st;             // T_b, kNB x kNB column-major
     double* Rd; long long srd;           // R diagonal block out, kNB x kNB
-    double* partials;                    // [batch][2][G][kPanelSlot]
+    double* partials;                    // [batch][2][G][kPanelSlot]: leaf-end sums
     unsigned* flags;                     // [batch][G]: last exchange each workgroup published
-    unsigned seq;                        // exchange x of this panel is published as seq + x + 1
+    unsigned long long* colslots;        // [batch][2][G][4 kLW]: tagged column sums (register-leaf kernel)
+    unsigned seq;                        // exchange x of this panel is published as seq + x + 1 (columns 0..63, then leaf ends)
     int* error_flag;
     unsigned spin_limit;
-    int lds_stride;                      // leading dimension of the slab (InLds) or of the leaf's rows (Res) in LDS
 };
 
-// The workgroup's slab (rows [r0, r1) of the panel) lives either in LDS
-// (InLds: loaded once, written back at the end) or stays in global memory.
-// Row r of the slab, column j, is X[(r - r0) + j * xld] with X = LDS or P + r0.
-// One level of the transposing butterfly: lanes with bit OFF set keep the
-// upper HALF of their values, the others the lower, each adding its
-// partner's copy of the kept half (compile-time indices keep h in registers).
 // A wave-uniform double moved to scalar registers.
 __device__ inline double uniform(double x) {
     const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
@@ -107,6 +86,9 @@ __device__ inline double uniform(double x) {
     return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
 
+// One level of the transposing butterfly: lanes with bit OFF set keep the
+// upper HALF of their values, the others the lower, each adding its
+// partner's copy of the kept half (compile-time indices keep h in registers).
 template <int HALF, int OFF>
 __device__ inline void butterfly_step(double (&h)[16], int lane) {
     const bool upper = (lane & OFF) != 0;
@@ -118,8 +100,9 @@ __device__ inline void butterfly_step(double (&h)[16], int lane) {
     }
 }
 
-// Blocked panel.  The panel's columns are factored in leaves of kLW = 16.
-// Inside a leaf, column k takes one sweep over the slab's rows that applies
+// Blocked panel for matrices too tall for the register-leaf kernel below: any
+// number of rows per workgroup, the slab in global memory.  The panel's columns
+// are factored in leaves of kLW = 16.  Inside a leaf, column k takes one sweep over the slab's rows that applies
 // reflector k-1 to the leaf's later columns and accumulates the dot products
 // of column k below its pivot with the leaf's 16 columns, then one exchange
 // of those 16 sums and of the pivot row's 16 entries, which give the norm,
@@ -132,10 +115,7 @@ __device__ inline void butterfly_step(double (&h)[16], int lane) {
 // applies the leaf's block reflector to C:  C -= V_s (T_s^T (V_s^T C)).
 // Against one sweep of all 64 columns per column, this sweeps 16 columns per
 // column and the whole panel twice per leaf.
-template <bool InLds, bool Res = false>
 __global__ __launch_bounds__(kPT) void panel_kernel(PanelArgs a) {
-    static_assert(!(InLds && Res), "the resident leaf is for slabs in global memory");
-    extern __shared__ double smem[];
     __shared__ double s_T[kNB * (kNB + 1) / 2];  // upper T packed by columns: T[i][l] at l (l + 1) / 2 + i
     // Leaf-end sums W[i][q] at i * kOther + q (i: leaf column, q: other
     // column, the earlier leaves' columns first).  While a leaf's columns
@@ -143,7 +123,6 @@ __global__ __launch_bounds__(kPT) void panel_kernel(PanelArgs a) {
     __shared__ double s_W[kLW * kOther];
     __shared__ double s_coef[kLW], s_z[kLW];
     __shared__ double s_rfl[4];          // beta, tau, scale of the latest reflector
-    __shared__ double s_prow[kLW];       // Res: the pivot row of the leaf after the sweep
     double* const s_wp = s_W;
     const int g = blockIdx.x % a.G, b = blockIdx.x / a.G;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -153,19 +132,10 @@ __global__ __launch_bounds__(kPT) void panel_kernel(PanelArgs a) {
     const int r0 = g * a.rows_per_wg;
     const int r1 = min(a.L, r0 + a.rows_per_wg);
     const int nb = a.nb;
-    const long long xld = InLds ? a.lds_stride : ld;
-    double* __restrict__ X = InLds ? smem : P + r0;
+    const long long xld = ld;
+    double* __restrict__ X = P + r0;
     constexpr int S = 64 * kRG;          // row stride of a lane
     const int first = r0 + 64 * wv + lane;  // this thread's rows: first + S j
-    const int ldl = a.lds_stride;        // Res: LDS rows of the leaf, row first + S (kResJ + j) at 64 w + lane + S j
-    double xr[Res ? kResJ : 1][kLW];     // Res: the leaf on this thread's first kResJ rows
-    if (InLds) {
-        for (int e = tid; e < (r1 - r0) * nb; e += kPT) {
-            const int rl = e % (r1 - r0), j = e / (r1 - r0);
-            X[rl + j * xld] = P[(r0 + rl) + j * ld];
-        }
-    }
-    __syncthreads();
     unsigned* flg = a.flags + (long long)b * a.G;
     unsigned ex = 0;  // exchanges done in this panel
 
@@ -284,21 +254,6 @@ __global__ __launch_bounds__(kPT) void panel_kernel(PanelArgs a) {
 
     for (int c0 = 0; c0 < nb; c0 += kLW) {
         const int lw = min(kLW, nb - c0);
-        if constexpr (Res) {
-            // The leaf onto the chip (each thread its own rows).
-#pragma unroll
-            for (int j = 0; j < kResJ; ++j) {
-                const int row = first + S * j;
-#pragma unroll
-                for (int q = 0; q < kLW; ++q)
-                    xr[j][q] = row < r1 ? X[row - r0 + (c0 + min(q, lw - 1)) * xld] : 0.0;
-            }
-            for (int row = first + S * kResJ; row < r1; row += S) {
-                const int rr = row - r0 - S * kResJ;
-#pragma unroll
-                for (int q = 0; q < kLW; ++q) smem[rr + q * ldl] = X[row - r0 + (c0 + min(q, lw - 1)) * xld];
-            }
-        }
         for (int kk = 0; kk < lw; ++kk) {
             const int k = c0 + kk;
             // Sweep: reflector k-1 (inside this leaf) on the leaf's columns
@@ -312,14 +267,11 @@ __global__ __launch_bounds__(kPT) void panel_kernel(PanelArgs a) {
             for (int q = 0; q < kLW; ++q) {
                 const double c = s_coef[q];
                 acc[q] = 0.0;
-                // Res: column kk too (its coefficient is ck), so that the
-                // sweep leaves reflector k-1 applied to column kk in place.
-                cq[q] = (kk > 0 && (Res ? q >= kk : q > kk) && q < lw) ? c : 0.0;
-                if constexpr (Res) cq[q] = uniform(cq[q]);  // wave-uniform: scalar registers
+                cq[q] = (kk > 0 && q > kk && q < lw) ? c : 0.0;
             }
             const double ck = kk > 0 ? s_coef[kk] : 0.0;
             const int lo = max(r0, kk > 0 ? k - 1 : k);
-            constexpr int U = kRowUnroll<InLds>;
+            constexpr int U = kRowUnroll;
             // Rows are taken U at a time, all their loads first, then the
             // arithmetic and the stores row by row in increasing order, so
             // each lane accumulates its rows in the same order as one at a time.
@@ -351,59 +303,12 @@ __global__ __launch_bounds__(kPT) void panel_kernel(PanelArgs a) {
                         if (q > kk && q < lw) X[rl + (c0 + q) * xld] = val[q];
                 }
             };
-            if constexpr (Res) {
-                // The same arithmetic on the resident leaf, with column kk
-                // updated in place; the thread that owns the pivot row
-                // (always a register row) publishes it.
+            for (int row = first; row < r1; row += S * U) {
+                double val[U][kLW], vraw[U], xraw[U];
 #pragma unroll
-                for (int j = 0; j < kResJ; ++j) {
-                    const int row = first + S * j;
-                    if (row >= lo && row < r1) {
-                        double vprev = 0.0;
-                        if (kk > 0) {
-                            double vr = 0.0;
+                for (int u = 0; u < U; ++u) load_row(row + S * u, val[u], vraw[u], xraw[u]);
 #pragma unroll
-                            for (int q = 0; q < kLW; ++q)
-                                if (q + 1 == kk) vr = xr[j][q];
-                            vprev = row == k - 1 ? 1.0 : vr;
-                        }
-#pragma unroll
-                        for (int q = 0; q < kLW; ++q) xr[j][q] = xr[j][q] - cq[q] * vprev;
-                        double xk = 0.0;
-#pragma unroll
-                        for (int q = 0; q < kLW; ++q)
-                            if (q == kk) xk = xr[j][q];
-                        const double xa = row > k ? xk : 0.0;  // column k below the pivot
-#pragma unroll
-                        for (int q = 0; q < kLW; ++q) acc[q] += xa * xr[j][q];
-                        if (row == k) {
-#pragma unroll
-                            for (int q = 0; q < kLW; ++q) s_prow[q] = xr[j][q];
-                        }
-                    }
-                }
-                for (int row = first + S * kResJ; row < r1; row += S) {
-                    if (row < lo) continue;
-                    // LDS rows column by column (no row copy in registers).
-                    const int rr = row - r0 - S * kResJ;
-                    const double vprev = kk > 0 ? (row == k - 1 ? 1.0 : smem[rr + (kk - 1) * ldl]) : 0.0;
-                    const double xk = smem[rr + kk * ldl] - ck * vprev;
-                    const double xa = row > k ? xk : 0.0;
-#pragma unroll
-                    for (int q = 0; q < kLW; ++q) {
-                        const double v = smem[rr + q * ldl] - cq[q] * vprev;
-                        acc[q] += xa * v;
-                        if (kk > 0 && q >= kk && q < lw) smem[rr + q * ldl] = v;
-                    }
-                }
-            } else {
-                for (int row = first; row < r1; row += S * U) {
-                    double val[U][kLW], vraw[U], xraw[U];
-#pragma unroll
-                    for (int u = 0; u < U; ++u) load_row(row + S * u, val[u], vraw[u], xraw[u]);
-#pragma unroll
-                    for (int u = 0; u < U; ++u) finish_row(row + S * u, val[u], vraw[u], xraw[u]);
-                }
+                for (int u = 0; u < U; ++u) finish_row(row + S * u, val[u], vraw[u], xraw[u]);
             }
             {
                 // The 16 column sums of the wave in one transposing butterfly:
@@ -439,12 +344,8 @@ __global__ __launch_bounds__(kPT) void panel_kernel(PanelArgs a) {
                 } else if (lane < 2 * kLW && k >= r0 && k < r1) {
                     const int q = lane - kLW, rl = k - r0;
                     double v;
-                    if constexpr (Res) {
-                        v = s_prow[q];
-                    } else {
-                        v = X[rl + (c0 + min(q, lw - 1)) * xld];
-                        if (q == kk) v -= ck * (kk > 0 ? X[rl + (k - 1) * xld] : 0.0);
-                    }
+                    v = X[rl + (c0 + min(q, lw - 1)) * xld];
+                    if (q == kk) v -= ck * (kk > 0 ? X[rl + (k - 1) * xld] : 0.0);
                     val = q < lw ? v : 0.0;
                 }
                 double sum = val;
@@ -479,36 +380,12 @@ __global__ __launch_bounds__(kPT) void panel_kernel(PanelArgs a) {
             // Column k on this thread's rows: R entry on row k-1, beta on the
             // pivot, v below (column k was not stored by the sweep; column
             // k-1 on these rows was written by this thread).
-            if constexpr (Res) {
-                // Column kk already holds reflector k-1's result (the sweep).
-#pragma unroll
-                for (int j = 0; j < kResJ; ++j) {
-                    const int row = first + S * j;
-                    if (row >= lo && row < r1) {
-                        double x = 0.0;
-#pragma unroll
-                        for (int q = 0; q < kLW; ++q)
-                            if (q == kk) x = xr[j][q];
-                        const double nv = row == k ? beta : (row > k ? scale * x : x);
-#pragma unroll
-                        for (int q = 0; q < kLW; ++q)
-                            if (q == kk) xr[j][q] = nv;
-                    }
-                }
-                for (int row = first + S * kResJ; row < r1; row += S) {
-                    if (row < lo) continue;
-                    const int rr = row - r0 - S * kResJ;
-                    const double x = smem[rr + kk * ldl];
-                    smem[rr + kk * ldl] = row == k ? beta : (row > k ? scale * x : x);
-                }
-            } else {
-                for (int row = first; row < r1; row += S) {
-                    if (row < lo) continue;
-                    const int rl = row - r0;
-                    const double vprev = kk > 0 ? (row == k - 1 ? 1.0 : X[rl + (k - 1) * xld]) : 0.0;
-                    const double x = X[rl + k * xld] - ck * vprev;
-                    X[rl + k * xld] = row == k ? beta : (row > k ? scale * x : x);
-                }
+            for (int row = first; row < r1; row += S) {
+                if (row < lo) continue;
+                const int rl = row - r0;
+                const double vprev = kk > 0 ? (row == k - 1 ? 1.0 : X[rl + (k - 1) * xld]) : 0.0;
+                const double x = X[rl + k * xld] - ck * vprev;
+                X[rl + k * xld] = row == k ? beta : (row > k ? scale * x : x);
             }
             // Column kk of the leaf's T_s (every workgroup keeps T_s):
             // T[c0+j][k] = -tau sum_l T[c0+j][c0+l] z_l, T[k][k] = tau.
@@ -529,24 +406,6 @@ __global__ __launch_bounds__(kPT) void panel_kernel(PanelArgs a) {
                 } else {
                     s_T[base + kk] = tau;
                 }
-            }
-        }
-        if constexpr (Res) {
-            // The leaf back to global memory (each thread its own rows).
-#pragma unroll
-            for (int j = 0; j < kResJ; ++j) {
-                const int row = first + S * j;
-                if (row < r1) {
-#pragma unroll
-                    for (int q = 0; q < kLW; ++q)
-                        if (q < lw) X[row - r0 + (c0 + q) * xld] = xr[j][q];
-                }
-            }
-            for (int row = first + S * kResJ; row < r1; row += S) {
-                const int rr = row - r0 - S * kResJ;
-#pragma unroll
-                for (int q = 0; q < kLW; ++q)
-                    if (q < lw) X[row - r0 + (c0 + q) * xld] = smem[rr + q * ldl];
             }
         }
         __syncthreads();  // the leaf's columns and T_s are complete
@@ -570,7 +429,7 @@ __global__ __launch_bounds__(kPT) void panel_kernel(PanelArgs a) {
             const int cb = q0 < c0 ? q0 : q0 + lw;  // first column of the block (blocks do not straddle the leaf)
             const int ci = c0 + i, cj = cb + i;
             const bool iok = i < lw, jok = cj < nb && (q0 + i) < nother;
-            constexpr int UQ = kQuadUnroll<InLds>;
+            constexpr int UQ = kQuadUnroll;
             for (int base = rs + 4 * UQ * part; base < r1; base += 4 * UQ * nparts) {
                 double av[UQ], bv[UQ];
 #pragma unroll
@@ -693,16 +552,594 @@ __global__ __launch_bounds__(kPT) void panel_kernel(PanelArgs a) {
             if (in && i <= j) X[(i - r0) + j * xld] = (i == j) ? 1.0 : 0.0;
         }
     }
-    if (InLds) {
-        __syncthreads();
-        for (int e = tid; e < (r1 - r0) * nb; e += kPT) {
-            const int rl = e % (r1 - r0), j = e / (r1 - r0);
-            P[(r0 + rl) + j * ld] = X[rl + j * xld];
-        }
-    }
     if (g == 0 && tid < kNB) {
         double* Tb = a.T + b * a.st;
         for (int l = 0; l < kNB; ++l) Tb[tid + l * kNB] = (tid <= l && l < nb) ? s_T[l * (l + 1) / 2 + tid] : 0.0;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Register-leaf panel.  A workgroup of NT threads owns up to NT * J rows of the
+// panel, thread t the rows t, t + NT, ...; while a leaf of 16 columns is
+// factored it stays in registers (J x 16 per thread), so a column touches no
+// memory but the few LDS words of its reduction.
+//
+// The leaf's registers are a ring: the current column is entry 0, the later
+// ones follow, the finished reflectors of the leaf come last.  Column k takes
+//   1. the products of its entries below the pivot with all 16 entries
+//      (norm, update dots and the products with the finished reflectors);
+//   2. their sums over the wave by a transposing butterfly of lane swaps and
+//      DPP moves (no LDS), over the waves through LDS, and for MULTI over the
+//      matrix's workgroups (below);
+//   3. the reflector, which every wave forms for itself from those sums (the
+//      double-buffered LDS words make one barrier a column enough; MULTI takes
+//      a second one after wave 0's exchange);
+//   4. its application to the later columns, which also turns the ring by one:
+//      new[q - 1] = old[q] - c_q v.  Coefficient q sits in lane q of each row
+//      of 16 lanes and reaches the others by a DPP row broadcast.
+// After 16 columns the ring is in column order again.
+//
+// End of a leaf: each wave stages V (its own rows, 64 x 16 at a time) in LDS
+// and forms its part of W = V_s^T [V_prev, C] with 16 x 16 x 4 MFMAs, reading
+// 128 contiguous bytes per lane of the other columns; the parts are summed
+// over the waves (MULTI: and workgroups).  W2 = T_s^T (V_s^T C) comes out of
+// the MFMA in the layout that the update C -= V_s W2 takes as its operand.
+// V_prev^T V_s goes to the packed V^T V from which the first workgroup merges
+// T once, after the last leaf.
+//
+// The workgroups' exchange of a column (MULTI): wave 0 stores the workgroup's
+// 16 sums, the first workgroup also the pivot row, as 16-byte slots
+// {low word, tag, high word, tag}; each 8-byte half carries the exchange's
+// sequence number, so a reader polls the data itself: one trip through memory
+// where a flag took three (partials acknowledged, flag, partials read).  Slots
+// alternate between two parities: a workgroup rewrites a slot only after every
+// other one has published the exchange after the one that read it.  Tags grow
+// through a factorisation and start from zeroed slots.  Every wait is bounded.
+//
+// Bound: latency of the 64 dependent columns, 0.75-0.9 us each in one workgroup of
+// 256 rows and 1.2 us more with the exchange, and of the four leaf ends.  64-column
+// panels, us, against the kernel before (the slab in LDS, a sweep of 16 columns
+// per column through LDS, two or more workgroups from 128 rows on, flag exchange):
+//   live rows      128   256   512  1024  2048  4160  8256  8 x 8256
+//   before         372   400   408   426   433   471   502       542
+//   this kernel    100   108   141   206   220   254   290       309
+// and one workgroup per matrix (many-matrix call) 2048 rows 420 against about 660.
+// ---------------------------------------------------------------------------
+typedef unsigned u4v __attribute__((ext_vector_type(4)));
+typedef double dpair_u __attribute__((ext_vector_type(2), aligned(8)));
+
+template <int CTRL>
+__device__ inline double dpp(double x) {
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
+    const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)u, CTRL, 0xf, 0xf, true);
+    const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), CTRL, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E;             // quad_perm [1,0,3,2], [2,3,0,1]
+constexpr int kDppRor8 = 0x128, kDppHalfMirror = 0x141;     // lane ^ 8; lane ^ 7
+constexpr int kDppRowBcast = 0x150;                         // row_newbcast:0 (+ n: lane n of each row of 16)
+
+// a' = [a.low half, b.low half] and b' = [a.high half, b.high half] over the
+// 32-lane halves; the sum adds each value's two halves, a in lanes 0-31, b above.
+__device__ inline double swap32_add(double a, double b) {
+    const unsigned long long x = __builtin_bit_cast(unsigned long long, a), y = __builtin_bit_cast(unsigned long long, b);
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+    return __builtin_bit_cast(double, ((unsigned long long)hi[0] << 32) | lo[0]) +
+           __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
+}
+// The same over neighbouring rows of 16 lanes: a in rows 0 and 2, b in rows 1 and 3.
+__device__ inline double swap16_add(double a, double b) {
+    const unsigned long long x = __builtin_bit_cast(unsigned long long, a), y = __builtin_bit_cast(unsigned long long, b);
+    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+    return __builtin_bit_cast(double, ((unsigned long long)hi[0] << 32) | lo[0]) +
+           __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
+}
+// Sums of 16 values over the wave: lane l returns the sum of value (l >> 2) & 15.
+__device__ inline double wave_sums16(double (&h)[16], int lane) {
+#pragma unroll
+    for (int p = 0; p < 8; ++p) h[p] = swap32_add(h[p], h[p + 8]);
+#pragma unroll
+    for (int p = 0; p < 4; ++p) h[p] = swap16_add(h[p], h[p + 4]);
+    const bool b3 = lane & 8, b2 = lane & 4;
+#pragma unroll
+    for (int p = 0; p < 2; ++p) h[p] = (b3 ? h[p + 2] : h[p]) + dpp<kDppRor8>(b3 ? h[p] : h[p + 2]);
+    double t = (b2 ? h[1] : h[0]) + dpp<kDppHalfMirror>(b2 ? h[0] : h[1]);
+    t += dpp<kDppXor1>(t);
+    t += dpp<kDppXor2>(t);
+    return t;
+}
+
+// xr[q - 1] = xr[q] - c_q v for q = 1..15 (c: lane q of each row of 16 holds c_q), xr[15] = last.
+template <int N>
+__device__ inline double row_bcast(double x) {
+    return __builtin_bit_cast(double, (long long)__builtin_amdgcn_update_dpp(
+                                          0ll, __builtin_bit_cast(long long, x), kDppRowBcast + N, 0xf, 0xf, true));
+}
+template <int Q>
+__device__ inline void ring_turn(double (&xr)[kLW], double c, double v) {
+    if constexpr (Q < kLW) {
+        xr[Q - 1] = fma(-row_bcast<Q>(c), v, xr[Q]);
+        ring_turn<Q + 1>(xr, c, v);
+    }
+}
+
+// x where mask is -1, +0 where it is 0.
+__device__ inline double keep_if(double x, int mask) {
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
+    const unsigned lo = (unsigned)u & (unsigned)mask, hi = (unsigned)(u >> 32) & (unsigned)mask;
+    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+
+// Packed strict upper triangle: (i, j), i < j.
+__device__ inline int upper_at(int i, int j) { return j * (j - 1) / 2 + i; }
+
+template <int NT, int J, bool MULTI>
+__global__ __launch_bounds__(NT) void panel_leaf_kernel(PanelArgs a) {
+    constexpr int NW = NT / 64;
+    constexpr int VS = 65;                        // row stride of a staged V column
+    constexpr int TS = kNB + 1;
+    __shared__ double s_v[NW][kLW * VS];          // staged V, then the waves' parts of W, at the end T
+    __shared__ double s_W[kLW * kOther];          // W[i][q] at i * kOther + q
+    __shared__ double s_G[kNB * (kNB - 1) / 2];   // V^T V, strict upper
+    __shared__ double s_Ts[kNL][kLW][kLW + 1];    // T_s of each leaf
+    __shared__ double s_part[2][NW][kLW], s_prow[2][kLW], s_tot[2][2 * kLW];
+    __shared__ double s_tau[kNB];
+    static_assert(4 * kLW * VS >= kNB * TS && kLW * kOther <= kLW * VS, "s_v holds T and a part of W");
+    static_assert(NW >= 4, "T in s_v");
+    const int g = MULTI ? blockIdx.x % a.G : 0, b = MULTI ? blockIdx.x / a.G : blockIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, lg = lane >> 4;
+    const long long ld = a.ld;
+    const int nb = a.nb;
+    const int r0 = g * a.rows_per_wg;
+    const int nr = min(a.L - r0, a.rows_per_wg);  // rows of this workgroup
+    double* __restrict__ X = a.P + b * a.sp + r0;
+    bool dead = false;                            // a bounded wait gave up: wait no more
+
+    // Sums s_W over the matrix's workgroups (s_W on every one that wants them).
+    auto leaf_exchange = [&](int leaf, bool want) __attribute__((always_inline)) {
+        double* slots = a.partials + ((long long)b * 2 + (leaf & 1)) * a.G * kPanelSlot;
+        for (int t = tid; t < kPanelSlot; t += NT)
+            __hip_atomic_store(&slots[(long long)g * kPanelSlot + t], s_W[t], __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+        __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+        __syncthreads();
+        unsigned* flg = a.flags + (long long)b * a.G;
+        const unsigned target = a.seq + kNB + leaf + 1u;
+        if (tid == 0) __hip_atomic_store(&flg[g], target, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (!want) return;
+        for (int t = tid; t < a.G; t += NT) {
+            unsigned spins = 0;
+            while (!dead && __hip_atomic_load(&flg[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
+                if (++spins > a.spin_limit) {
+                    atomicOr(a.error_flag, 1);
+                    dead = true;
+                }
+                __builtin_amdgcn_s_sleep(1);
+            }
+        }
+        __syncthreads();
+        // Plain buffer loads with the agent-coherence policy: all of a round
+        // are in flight together (atomic loads would be taken one by one).
+        const __amdgpu_buffer_rsrc_t rs =
+            __builtin_amdgcn_make_buffer_rsrc((void*)slots, (short)0, 0x7fffffff, kBufferRsrcWord3);
+        for (int t = tid; t < kPanelSlot; t += NT) {
+            double sum = 0.0;
+            for (int gg = 0; gg < a.G; gg += 16) {
+                double v[16];
+#pragma unroll
+                for (int u = 0; u < 16; ++u)
+                    v[u] = __builtin_bit_cast(
+                        double, __builtin_amdgcn_raw_buffer_load_b64(
+                                    rs, (min(gg + u, a.G - 1) * kPanelSlot + t) * 8, 0, kCoherentLoad));
+#pragma unroll
+                for (int u = 0; u < 16; ++u) sum += gg + u < a.G ? v[u] : 0.0;
+            }
+            s_W[t] = sum;
+        }
+        __syncthreads();
+    };
+    // Wave 0: val = the workgroup's sum (value lane & 15 in every row of 16
+    // lanes); returns the sums over the workgroups, and in prow the pivot row.
+    auto column_exchange = [&](int k, double val, double& prow) __attribute__((always_inline)) -> double {
+        const unsigned tag = a.seq + k + 1u;
+        unsigned long long* slots = a.colslots + ((long long)b * 2 + (k & 1)) * a.G * (4 * kLW);
+        if (lane < (g == 0 ? 2 * kLW : kLW)) {
+            const unsigned long long u = __builtin_bit_cast(unsigned long long, lane < kLW ? val : prow);
+            unsigned long long* p = slots + (long long)g * (4 * kLW) + 2 * lane;
+            __hip_atomic_store(p, ((unsigned long long)tag << 32) | (unsigned)u, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(p + 1, ((unsigned long long)tag << 32) | (unsigned)(u >> 32), __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+        }
+        const __amdgpu_buffer_rsrc_t rs =
+            __builtin_amdgcn_make_buffer_rsrc((void*)slots, (short)0, 0x7fffffff, kBufferRsrcWord3);
+        auto value = [](u4v x) { return __builtin_bit_cast(double, ((unsigned long long)x[2] << 32) | x[0]); };
+        double sum = 0.0;
+        constexpr int U = 4;                      // loads in flight: 4 U workgroups
+        for (int w0 = 0; w0 < a.G; w0 += 4 * U) {
+            u4v v[U + 1];
+            unsigned spins = 0;
+            for (;;) {
+                bool ok = true;
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int wg = min(w0 + 4 * u + lg, a.G - 1);
+                    v[u] = __builtin_amdgcn_raw_buffer_load_b128(rs, wg * (32 * kLW) + l16 * 16, 0, kCoherentLoad);
+                }
+                // The pivot row, from the first workgroup's second half.
+                v[U] = __builtin_amdgcn_raw_buffer_load_b128(rs, (kLW + l16) * 16, 0, kCoherentLoad);
+#pragma unroll
+                for (int u = 0; u <= U; ++u) ok = ok && v[u][1] == tag && v[u][3] == tag;
+                if (__all(ok) || dead) break;
+                if (++spins > (a.spin_limit >> 4)) {   // a memory round trip each: about a second
+                    if (lane == 0) atomicOr(a.error_flag, 1);
+                    dead = true;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) sum += w0 + 4 * u + lg < a.G ? value(v[u]) : 0.0;
+            prow = value(v[U]);
+        }
+        sum += __shfl_xor(sum, 16, 64);
+        sum += __shfl_xor(sum, 32, 64);
+        return sum;
+    };
+
+    for (int c0 = 0; c0 < nb; c0 += kLW) {
+        const int lw = min(kLW, nb - c0), leaf = c0 / kLW;
+        double xr[J][kLW];
+        // Loads from valid addresses, then zeros for rows past the slab and
+        // columns past a short leaf, by a mask the compiler cannot turn back
+        // into a branch around each load (which would wait for them one by one).
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const unsigned at = min(tid + NT * j, nr - 1);
+#pragma unroll
+            for (int q = 0; q < kLW; ++q) xr[j][q] = (X + (long long)(c0 + min(q, lw - 1)) * ld)[at];
+        }
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            int in = tid + NT * j < nr ? -1 : 0;
+            asm("" : "+v"(in));
+#pragma unroll
+            for (int q = 0; q < kLW; ++q) xr[j][q] = keep_if(xr[j][q], q < lw ? in : 0);
+        }
+        for (int kk = 0; kk < lw; ++kk) {
+            const int k = c0 + kk, kr = k - r0;   // kr: pivot row within the slab
+            const int buf = kk & 1;
+            double acc[kLW];
+#pragma unroll
+            for (int j = 0; j < J; ++j) {
+                const int row = tid + NT * j;
+                const double xa = row > kr ? xr[j][0] : 0.0;
+#pragma unroll
+                for (int q = 0; q < kLW; ++q) acc[q] = j == 0 ? xa * xr[j][q] : fma(xa, xr[j][q], acc[q]);
+            }
+            if (tid == kr) {                      // pivot rows are rows 0..63: j = 0
+#pragma unroll
+                for (int q = 0; q < kLW; ++q) s_prow[buf][q] = xr[0][q];
+            }
+            const double ws = wave_sums16(acc, lane);
+            if ((lane & 3) == 0) s_part[buf][wv][lane >> 2] = ws;
+            __syncthreads();
+            double sum, prow;
+            auto sum_waves = [&]() __attribute__((always_inline)) {
+                double h[NW];
+#pragma unroll
+                for (int w = 0; w < NW; ++w) h[w] = s_part[buf][w][l16];
+#pragma unroll
+                for (int s = 1; s < NW; s *= 2)
+#pragma unroll
+                    for (int w = 0; w + s < NW; w += 2 * s) h[w] += h[w + s];
+                return h[0];
+            };
+            if constexpr (MULTI) {
+                if (wv == 0) {
+                    prow = s_prow[buf][l16];
+                    sum = column_exchange(k, sum_waves(), prow);
+                    if (lane < 2 * kLW) s_tot[buf][lane] = lane < kLW ? sum : prow;
+                }
+                __syncthreads();
+                sum = s_tot[buf][l16];
+                prow = s_tot[buf][kLW + l16];
+            } else {
+                sum = sum_waves();
+                prow = s_prow[buf][l16];
+            }
+            // Reflector k on x = [alpha; below], beta = -sign(alpha) |x|,
+            // v = [1; below / (alpha - beta)]  (no cancellation in alpha - beta).
+            const double s2 = uniform(sum), alpha = uniform(prow);
+            double beta = alpha, tau = 0.0, scale = 0.0;
+            if (s2 != 0.0) {
+                const double nrm = sqrt(alpha * alpha + s2);
+                beta = alpha >= 0.0 ? -nrm : nrm;
+                tau = (beta - alpha) / beta;
+                scale = 1.0 / (alpha - beta);
+            }
+            const double w = prow + scale * sum;  // v_k^T column (later) or v_l^T v_k (finished)
+            const double c = l16 < kLW - kk ? tau * w : 0.0;
+            if (wv == 0 && lane < kLW) {
+                if (lane >= kLW - kk) s_G[upper_at(c0 + lane - (kLW - kk), k)] = w;
+                if (lane == 0) s_tau[k] = tau;
+            }
+#pragma unroll
+            for (int j = 0; j < J; ++j) {
+                const int row = tid + NT * j;
+                const double x = xr[j][0];
+                const double v = row > kr ? scale * x : (row == kr ? 1.0 : 0.0);
+                ring_turn<1>(xr[j], c, v);
+                xr[j][kLW - 1] = row > kr ? v : (row == kr ? beta : x);
+            }
+        }
+        for (int kk = lw; kk < kLW; ++kk) {       // a short leaf: turn the ring back into column order
+#pragma unroll
+            for (int j = 0; j < J; ++j) {
+                const double x = xr[j][0];
+#pragma unroll
+                for (int q = 1; q < kLW; ++q) xr[j][q - 1] = xr[j][q];
+                xr[j][kLW - 1] = x;
+            }
+        }
+        // The leaf to memory.
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const int row = tid + NT * j;
+            if (row >= nr) continue;
+            if (lw == kLW) {
+#pragma unroll
+                for (int q = 0; q < kLW; ++q) (X + (long long)(c0 + q) * ld)[(unsigned)row] = xr[j][q];
+            } else {
+#pragma unroll
+                for (int q = 0; q < kLW; ++q)
+                    if (q < lw) (X + (long long)(c0 + q) * ld)[(unsigned)row] = xr[j][q];
+            }
+        }
+        // V of the wave's rows 64 wv + NT j ... + 63, staged in LDS by the wave
+        // for itself: from the registers for one row per thread, else read
+        // back (so that the leaf's registers are free from here on).
+        double* const sv = s_v[wv];
+        auto load_v = [&](int j, double (&v)[kLW]) __attribute__((always_inline)) {
+            if constexpr (J == 1) {
+#pragma unroll
+                for (int q = 0; q < kLW; ++q) v[q] = xr[0][q];
+            } else {
+                const unsigned at = min(tid + NT * j, nr - 1);
+#pragma unroll
+                for (int q = 0; q < kLW; ++q) v[q] = (X + (long long)(c0 + min(q, lw - 1)) * ld)[at];
+            }
+        };
+        auto stage = [&](int j, const double (&v)[kLW]) __attribute__((always_inline)) {
+            const int row = tid + NT * j;
+            __builtin_amdgcn_wave_barrier();
+            if (j > 0 && lw == kLW) {             // no pivots here: V is the leaf as it is
+                int in = row < nr ? -1 : 0;
+                asm("" : "+v"(in));
+#pragma unroll
+                for (int q = 0; q < kLW; ++q) sv[q * VS + lane] = keep_if(v[q], in);
+            } else {
+#pragma unroll
+                for (int q = 0; q < kLW; ++q) {
+                    const int kr = c0 + q - r0;
+                    int in = row > kr && row < nr && q < lw ? -1 : 0;
+                    asm("" : "+v"(in));
+                    sv[q * VS + lane] = row == kr && q < lw ? 1.0 : keep_if(v[q], in);
+                }
+            }
+            __builtin_amdgcn_wave_barrier();
+        };
+        const int nother = nb - lw, nblk = (nother + 15) / 16;
+        const int nc = nb - c0 - lw;              // later columns of the panel
+        d4 w4[kOther / 16];
+#pragma unroll
+        for (int q = 0; q < kOther / 16; ++q) w4[q] = d4{0, 0, 0, 0};
+        if (nother > 0) {
+            // This lane's 16 rows of column cb + l % 16 in the wave's j-th 64 rows.
+            auto load_y = [&](int q, int j, double (&yv)[16]) __attribute__((always_inline)) {
+                const int cb = 16 * q < c0 ? 16 * q : 16 * q + lw;
+                const int base = 64 * wv + NT * j, row = base + 16 * lg;
+                const double* y = X + (long long)min(cb + l16, nb - 1) * ld;
+                if (base + 64 <= nr) {
+#pragma unroll
+                    for (int u = 0; u < 16; u += 2) {
+                        const dpair_u t = *reinterpret_cast<const dpair_u*>(y + row + u);
+                        yv[u] = t[0];
+                        yv[u + 1] = t[1];
+                    }
+                } else {
+#pragma unroll
+                    for (int u = 0; u < 16; ++u) yv[u] = y[min(row + u, nr - 1)];
+                }
+            };
+            auto product = [&](const double (&yv)[16], d4 w) __attribute__((always_inline)) {
+#pragma unroll
+                for (int u = 0; u < 16; ++u) w = mfma_f64_16x16x4(sv[l16 * VS + 16 * lg + u], yv[u], w);
+                return w;
+            };
+#pragma unroll 1
+            for (int j = 0; j < J; ++j) {
+                if (64 * wv + NT * j >= nr) break;
+                double v[kLW], yv[kOther / 16][16];
+                load_v(j, v);
+#pragma unroll
+                for (int q = 0; q < kOther / 16; ++q)
+                    if (q < nblk) load_y(q, j, yv[q]);
+                stage(j, v);
+#pragma unroll
+                for (int q = 0; q < kOther / 16; ++q)
+                    if (q < nblk) w4[q] = product(yv[q], w4[q]);
+            }
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int q = 0; q < kOther / 16; ++q)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) sv[Mfma<double>::row(lane, e) * kOther + 16 * q + l16] = w4[q][e];
+        }
+        __syncthreads();
+        // T_s: T[i][c] = -tau_c sum_{i <= l < c} T[i][l] (V^T V)[l][c], T[c][c] = tau_c (lane i: row i).
+        if (wv == NW - 1) {
+            double row[kLW];
+#pragma unroll
+            for (int c = 0; c < kLW; ++c) {
+                const double t = c < lw ? s_tau[c0 + c] : 0.0;
+                double s0 = 0.0, s1 = 0.0;
+                if (c < lw) {
+#pragma unroll
+                    for (int l = 0; l < c; ++l) {
+                        const double z = s_G[upper_at(c0 + l, c0 + c)];
+                        if (l & 1) s1 += row[l] * z;
+                        else s0 += row[l] * z;
+                    }
+                }
+                row[c] = l16 == c ? t : (l16 < c ? -t * (s0 + s1) : 0.0);
+            }
+            if (lane < kLW) {
+#pragma unroll
+                for (int c = 0; c < kLW; ++c) s_Ts[leaf][lane][c] = row[c];
+            }
+        }
+        if (nother > 0) {
+            for (int t = tid; t < kLW * kOther; t += NT) {
+                double s = s_v[0][t];
+#pragma unroll
+                for (int w = 1; w < NW; ++w) s += s_v[w][t];
+                s_W[t] = s;
+            }
+        }
+        __syncthreads();
+        if (nother <= 0) break;
+        if constexpr (MULTI) leaf_exchange(leaf, g == 0 || nc > 0);
+        if (g == 0) {                             // V_prev^T V_s
+            for (int t = tid; t < c0 * lw; t += NT) {
+                const int q = t / lw, i = t % lw;
+                s_G[upper_at(q, c0 + i)] = s_W[i * kOther + q];
+            }
+        }
+        if (nc > 0) {
+            // -W2 = -T_s^T (V_s^T C): the MFMA leaves W2[l / 16 + 4 e][l % 16]
+            // in element e of lane l, the operand of step e below.
+            d4 w2[kOther / 16];
+#pragma unroll
+            for (int q = 0; q < kOther / 16; ++q) {
+                w2[q] = d4{0, 0, 0, 0};
+                if (16 * q < nc) {
+#pragma unroll
+                    for (int s = 0; s < 4; ++s)
+                        w2[q] = mfma_f64_16x16x4(-s_Ts[leaf][4 * s + lg][l16],
+                                                 s_W[(4 * s + lg) * kOther + min(c0 + 16 * q + l16, kOther - 1)], w2[q]);
+                }
+            }
+            // C goes through the MFMA 16 columns x 16 rows at a time, the next
+            // tile's loads issued before this tile's stores.  Rows past the slab
+            // and columns past the panel load valid addresses and are not stored.
+            unsigned long long off[kOther / 4];   // column offsets of this lane
+#pragma unroll
+            for (int q = 0; q < kOther / 4; ++q)
+                off[q] = (unsigned long long)(unsigned)min(4 * q + lg, nc - 1) * (unsigned)ld;
+            double* const Cl = X + (long long)(c0 + lw) * ld;
+            auto load_c = [&](int row, d4 (&cv)[kOther / 16]) __attribute__((always_inline)) {
+                const double* p = Cl + min(row, nr - 1);
+#pragma unroll
+                for (int q = 0; q < kOther / 16; ++q)
+                    if (16 * q < nc) {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) cv[q][e] = p[off[4 * q + e]];
+                    }
+            };
+#pragma unroll 1
+            for (int j = 0; j < J; ++j) {
+                const int base = 64 * wv + NT * j;
+                if (base >= nr) break;
+                double v[kLW];
+                d4 cv[2][kOther / 16];
+                load_v(j, v);
+                load_c(base + l16, cv[0]);
+                stage(j, v);
+#pragma unroll
+                for (int rt = 0; rt < 4; ++rt) {
+                    const int row = base + 16 * rt + l16;
+                    if (rt < 3) load_c(row + 16, cv[(rt + 1) & 1]);
+                    double bv[4];
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) bv[s] = sv[(4 * s + lg) * VS + 16 * rt + l16];
+                    double* p = Cl + row;
+#pragma unroll
+                    for (int q = 0; q < kOther / 16; ++q)
+                        if (16 * q < nc) {
+                            d4& c = cv[rt & 1][q];
+#pragma unroll
+                            for (int s = 0; s < 4; ++s) c = mfma_f64_16x16x4(w2[q][s], bv[s], c);
+                            if (row < nr) {
+                                if (16 * q + 16 <= nc) {
+#pragma unroll
+                                    for (int e = 0; e < 4; ++e) p[off[4 * q + e]] = c[e];
+                                } else {
+#pragma unroll
+                                    for (int e = 0; e < 4; ++e)
+                                        if (16 * q + 4 * e + lg < nc) p[off[4 * q + e]] = c[e];
+                                }
+                            }
+                        }
+                }
+            }
+        }
+        __syncthreads();
+    }
+    if (g != 0) return;
+    // The first workgroup holds the top block: R's diagonal block saved, V
+    // made explicit (1 on the diagonal, 0 above), so that the GEMMs can use
+    // the stored panel as V.
+    double* Rd = a.Rd + b * a.srd;
+    for (int e = tid; e < kNB * kNB; e += NT) {
+        const int i = e % kNB, j = e / kNB;
+        const bool in = i < nb && j < nb && i < a.L;
+        const double v = in ? X[i + j * ld] : 0.0;
+        Rd[e] = (in && i <= j) ? v : 0.0;
+        if (in && i <= j) X[i + j * ld] = (i == j) ? 1.0 : 0.0;
+    }
+    // T from the leaves' T_s and V^T V: T12 = -T1 (V1^T V2) T2 for 16 and 32
+    // columns a side, on the matrix cores.
+    double* const T = s_v[0];                     // T[i][j] at i + j TS
+    for (int e = tid; e < kNB * TS; e += NT) {
+        const int i = e % TS, j = e / TS;
+        T[e] = (i < kNB && i / kLW == j / kLW && j / kLW * kLW < nb) ? s_Ts[j / kLW][i % kLW][j % kLW] : 0.0;
+    }
+    __syncthreads();
+    for (int s = kLW; s < kNB; s *= 2) {
+        const int ts = s / 16, per = ts * ts, total = kNB / (2 * s) * per;   // 2, 4 tiles
+        const int o = wv / per * 2 * s, ti = wv % per % ts * 16, tj = wv % per / ts * 16;
+        for (int phase = 0; phase < 2; ++phase) {
+            d4 acc = d4{0, 0, 0, 0};
+            if (wv < total) {
+                for (int k = 0; k < s; k += 4) {
+                    double x, y;
+                    if (phase == 0) {             // Y = (V1^T V2) T2 into the place of T12
+                        const int i = o + ti + l16, l = o + s + k + lg;
+                        x = l < nb ? s_G[upper_at(i, l)] : 0.0;
+                        y = T[o + s + k + lg + (o + s + tj + l16) * TS];
+                    } else {
+                        x = -T[o + ti + l16 + (o + k + lg) * TS];
+                        y = T[o + k + lg + (o + s + tj + l16) * TS];
+                    }
+                    acc = mfma_f64_16x16x4(x, y, acc);
+                }
+            }
+            __syncthreads();
+            if (wv < total) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    T[o + ti + Mfma<double>::row(lane, e) + (o + s + tj + l16) * TS] = acc[e];
+            }
+            __syncthreads();
+        }
+    }
+    double* Tb = a.T + b * a.st;
+    for (int e = tid; e < kNB * kNB; e += NT) {
+        const int i = e % kNB, j = e / kNB;
+        Tb[e] = i <= j && j < nb ? T[i + j * TS] : 0.0;
     }
 }
 
@@ -755,8 +1192,28 @@ __global__ void assemble_r_kernel(int n, const double* __restrict__ M, long long
 
 struct Geometry {
     int G, rows;
-    bool lds;
+    int variant;   // index into kLeafVariants, or -1: panel_kernel
 };
+
+// The register-leaf kernel's shapes, by the rows a workgroup holds.
+struct LeafVariant {
+    int nt, rows;
+    const void* solo;    // one workgroup per matrix
+    const void* multi;   // several, cooperative
+};
+const LeafVariant kLeafVariants[] = {
+    {256, 256, (const void*)panel_leaf_kernel<256, 1, false>, (const void*)panel_leaf_kernel<256, 1, true>},
+    {512, 512, (const void*)panel_leaf_kernel<512, 1, false>, (const void*)panel_leaf_kernel<512, 1, true>},
+    {512, 1024, (const void*)panel_leaf_kernel<512, 2, false>, (const void*)panel_leaf_kernel<512, 2, true>},
+    {512, 2048, (const void*)panel_leaf_kernel<512, 4, false>, (const void*)panel_leaf_kernel<512, 4, true>},
+};
+constexpr int kNumLeafVariants = sizeof(kLeafVariants) / sizeof(kLeafVariants[0]);
+
+// One workgroup per matrix up to this many live rows.  Measured on gfx950, one
+// 64-column panel, one workgroup against 256-row workgroups with their column
+// exchange: 512 rows 141 against 213 us, 1024 rows 206 against 222 us (one
+// matrix or eight alike), 2048 rows 420 against 220 us.
+constexpr int kSoloRows = 1024;
 
 // Rows each workgroup owns when the slab stays in global memory.
 constexpr int kPanelRowsTarget = 256;
@@ -764,29 +1221,13 @@ constexpr int kPanelRowsTarget = 256;
 // Panels of the solves of zolo_pd_batched with at most this many live rows
 // take one workgroup per matrix: an ordinary launch on the solve's own
 // stream, instead of a cooperative launch on the panel stream that all
-// concurrent solves share.  Slower per column, but the panels of different
-// solves overlap; measured on gfx950 over 512 matrices with
-// n in [64, 1024], m in [n, 2n] (live rows up to 2112), 4 solves at once:
-// 3.34 s with cooperative panels, 2.81 s with single-workgroup panels.
-constexpr int kSinglePanelRows = 2304;
+// concurrent solves share: 420 us at 2048 rows where a cooperative panel takes
+// 220, but the panels of sixteen solves overlap.
+constexpr int kSinglePanelRows = 2048;
 
-constexpr int kStaticLds = (kNB * (kNB + 1) / 2 + kLW * kOther + 5 * kLW) * 8 + 256;
-
-int lds_limit() {
-    static int v = [] {
-        int dev = 0, bytes = 0;
-        if (hipGetDevice(&dev) != hipSuccess) return 0;
-        if (hipDeviceGetAttribute(&bytes, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess) return 0;
-        if (hipFuncSetAttribute((const void*)panel_kernel<false, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                bytes - kStaticLds) != hipSuccess)
-            return 0;
-        if (hipFuncSetAttribute((const void*)panel_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                bytes - kStaticLds) != hipSuccess)
-            return 0;
-        return bytes;
-    }();
-    return v;
-}
+// At most this many workgroups share a matrix's panel: every column polls
+// and sums one slot per workgroup.
+constexpr int kPanelMaxG = 64;
 
 int cu_count() {
     static int v = [] {
@@ -798,56 +1239,50 @@ int cu_count() {
     return v;
 }
 
-// Co-resident workgroups of the LDS panel kernel with an R-row slab.
-int lds_coresident(int R) {
-    static std::map<int, int> cache;
+// Co-resident workgroups of a multi-workgroup register-leaf shape.
+int leaf_coresident(int v) {
+    static int cache[kNumLeafVariants] = {};
     static std::mutex mu;
     std::lock_guard<std::mutex> lock(mu);
-    auto it = cache.find(R);
-    if (it != cache.end()) return it->second;
-    int per_cu = 0;
-    const size_t dyn = (size_t)R * kNB * sizeof(double);
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)panel_kernel<true>, kPT, dyn) !=
-        hipSuccess)
-        per_cu = 0;
-    return cache[R] = per_cu * cu_count();
+    if (cache[v] == 0) {
+        int per_cu = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kLeafVariants[v].multi, kLeafVariants[v].nt, 0) !=
+            hipSuccess)
+            per_cu = 0;
+        cache[v] = per_cu > 0 ? per_cu * cu_count() : -1;
+    }
+    return cache[v] > 0 ? cache[v] : 0;
 }
 
 // Co-resident workgroups of the global-memory panel kernel.
 int global_coresident() {
     static int v = [] {
         int per_cu = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)panel_kernel<false>, kPT, 0) !=
-            hipSuccess)
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)panel_kernel, kPT, 0) != hipSuccess)
             return 0;
         return per_cu * cu_count();
     }();
     return v;
 }
 
-// At most this many workgroups share one matrix's panel: every column's
-// exchange polls and sums one partial per workgroup, so beyond this the
-// exchange costs more than the shorter sweep saves.  Measured on gfx950 for
-// one 8256-row panel per launch (QR-type steps of degree 1 at n = 8192):
-// 129 workgroups (the co-residency limit) 0.80 ms per 64-column panel, 64
-// workgroups 0.61 ms, 32 workgroups 0.53 ms, 16 (global-memory slabs)
-// 0.86 ms; eight panels per launch already take 31 workgroups each.
-constexpr int kPanelMaxG = 32;
-
-Geometry panel_geometry(int L, int batch) {
-    // Slab in LDS when every workgroup of the launch can be resident with it.
-    const int limit = lds_limit();
-    if (limit > 0) {
-        const int max_rows = (limit - kStaticLds) / (kNB * (int)sizeof(double));
-        // Taller slabs than the LDS holds fall back to the most rows it does.
-        const int rmin = std::max(64, std::min(((L + kPanelMaxG - 1) / kPanelMaxG + 15) / 16 * 16, max_rows / 16 * 16));
-        for (int R = rmin; R <= max_rows; R += 16) {
-            const int G = (L + R - 1) / R;
-            if (G * batch <= lds_coresident(R)) {
-                const int rows = (L + G - 1) / G;
-                return {G, rows, true};
-            }
-        }
+// One workgroup per matrix where that is enough (above), else the smallest
+// workgroups that all fit on the GPU at once, at most kPanelMaxG a matrix: 256
+// rows each measured fastest wherever they fit (one matrix of 4160 rows: 254 us
+// against 269 with 512 rows and 323 with 1024; 8256 rows: 290, 298, 325), and
+// eight matrices of 8256 rows, 264 such workgroups for 256 CUs, take 512 rows
+// each.  Matrices too tall for the last shape go to panel_kernel.
+Geometry panel_geometry(int L, int batch, bool single) {
+    if (L <= (single ? kSinglePanelRows : kSoloRows)) {
+        int v = 0;
+        while (L > kLeafVariants[v].rows) ++v;
+        return {1, L, v};
+    }
+    for (int v = 0; v < kNumLeafVariants; ++v) {
+        int G = (L + kLeafVariants[v].rows - 1) / kLeafVariants[v].rows;
+        if (G > kPanelMaxG || G * (long long)batch > leaf_coresident(v)) continue;
+        const int rows = ((L + G - 1) / G + 15) / 16 * 16;
+        G = (L + rows - 1) / rows;
+        return {G, rows, v};
     }
     const int target = kPanelRowsTarget;
     int G = (L + target - 1) / target;
@@ -858,7 +1293,7 @@ Geometry panel_geometry(int L, int batch) {
     int rows = (L + G - 1) / G;
     if (rows < 64) rows = 64;
     G = (L + rows - 1) / rows;
-    return {G, rows, false};
+    return {G, rows, -1};
 }
 
 inline int live_rows(int m, int e, int p0, int nb) {
@@ -873,8 +1308,28 @@ inline int live_rows(int m, int e, int p0, int nb) {
 // of per-workgroup partial sums and flags.
 int panel_max_coresident() {
     int v = global_coresident();
-    if (lds_limit() > 0) v = std::max(v, lds_coresident(64));
+    for (int i = 0; i < kNumLeafVariants; ++i) v = std::max(v, leaf_coresident(i));
     return v;
+}
+
+__global__ void cooperative_noop_kernel() {}
+
+// One empty cooperative launch per device, before the library's first own
+// stream beside the callers'.  The HIP runtime runs cooperative kernels on a queue of its own, made for the first of
+// them; made after the process's streams have taken the hardware queues (4 by
+// default) it shares one, and every later panel launch waits for it: a
+// structured QR of 1025 x 881 x 5 took 10.0 ms where it takes 6.5.
+hipError_t open_cooperative_queue(int device, hipStream_t st) {
+    static std::mutex mu;
+    static unsigned long long opened = 0;
+    if (device < 0 || device >= 64) return hipSuccess;
+    std::lock_guard<std::mutex> lock(mu);
+    if (opened >> device & 1) return hipSuccess;
+    void* args[] = {nullptr};
+    const hipError_t e =
+        hipLaunchCooperativeKernel((const void*)cooperative_noop_kernel, dim3(1), dim3(64), args, 0, st);
+    if (e == hipSuccess) opened |= 1ull << device;
+    return e;
 }
 
 hipError_t stack_init(int m, int n, const double* X, long long ldx, double* M, long long ld, long long sm,
@@ -902,17 +1357,12 @@ hipError_t assemble_r(int n, const double* M, long long ld, long long sm, int ba
 
 namespace {
 
-// Cooperative launch of the panel kernel for panel p (columns p0 .. p0+nb-1).
+// Launch of the panel kernel for panel p (columns p0 .. p0+nb-1).
 hipError_t run_panel(int m, int e, int p, int nb, double* M, long long ld, long long sm, int batch, const QrWork& w,
                      long long stT, hipStream_t st) {
     const int p0 = p * kNB;
     const int L = live_rows(m, e, p0, nb);
-    Geometry geo = panel_geometry(L, batch);
-    if (geo.G > 1 && w.single_panels && L <= kSinglePanelRows) {
-        const int limit = lds_limit();
-        const int max_rows = limit > 0 ? (limit - kStaticLds) / (kNB * (int)sizeof(double)) : 0;
-        geo = {1, L, L <= max_rows};
-    }
+    const Geometry geo = panel_geometry(L, batch, w.single_panels);
     // The partial-sum and flag buffers hold max_coresident workgroups.
     if ((long long)geo.G * batch > w.max_coresident && geo.G > 1) return hipErrorInvalidValue;
     PanelArgs pa;
@@ -921,31 +1371,22 @@ hipError_t run_panel(int m, int e, int p, int nb, double* M, long long ld, long 
     pa.T = w.T + (long long)p * kNB * kNB; pa.st = stT;
     pa.Rd = w.Rd + (long long)p * kNB * kNB; pa.srd = stT;
     pa.partials = w.partials;
+    pa.colslots = w.colslots;
     pa.flags = w.flags;
     pa.seq = (unsigned)p * kPanelExchanges;
     pa.error_flag = w.error_flag;
     pa.spin_limit = 1u << 24;
-    pa.lds_stride = geo.rows;
+    const double flops = 4.0 * L * (double)nb * nb * batch, bytes = 16.0 * L * (double)nb * batch;
     void* args[] = {&pa};
     hipError_t err;
-    if (geo.G == 1) {
+    if (geo.variant >= 0 && geo.G == 1) {
         // One workgroup per matrix needs no co-residency: an ordinary launch
-        // on the solve's own stream, free to overlap other solves.  A slab
-        // that the LDS does not hold keeps each leaf on chip while it is
-        // factored when it has at most kResRows rows.
-        const bool res = !geo.lds && L <= kResRows && lds_limit() > 0;
-        const int res_rows = std::max(L - kPT * kResJ, 0);
-        if (res) pa.lds_stride = std::max(res_rows, 1);
-        StatScope sc(geo.lds ? "panel_kernel<lds>" : (res ? "panel_kernel<resident>" : "panel_kernel<global>"), st,
-                     4.0 * L * (double)nb * nb * batch, 16.0 * L * (double)nb * batch);
-        if (geo.lds)
-            panel_kernel<true><<<batch, kPT, (size_t)geo.rows * kNB * sizeof(double), st>>>(pa);
-        else if (res)
-            panel_kernel<false, true><<<batch, kPT, (size_t)res_rows * kLW * sizeof(double), st>>>(pa);
-        else
-            panel_kernel<false><<<batch, kPT, 0, st>>>(pa);
+        // on the solve's own stream, free to overlap other solves.
+        const LeafVariant& v = kLeafVariants[geo.variant];
+        StatScope sc("panel_leaf<one workgroup>", st, flops, bytes);
+        err = hipLaunchKernel(v.solo, dim3(batch), dim3(v.nt), args, 0, st);
         sc.end();
-        return hipGetLastError();
+        return err;
     }
     // Several solves at once (zolo_pd_batched): every cooperative panel goes
     // to one shared stream, so two panels never wait for each other's
@@ -956,13 +1397,13 @@ hipError_t run_panel(int m, int e, int p, int nb, double* M, long long ld, long 
         if ((err = hipEventRecord(w.ev_ready, st)) != hipSuccess) return err;
         if ((err = hipStreamWaitEvent(ps, w.ev_ready, 0)) != hipSuccess) return err;
     }
-    StatScope sc(geo.lds ? "panel_kernel<lds>" : "panel_kernel<global>", ps, 4.0 * L * (double)nb * nb * batch,
-                 16.0 * L * (double)nb * batch);
-    if (geo.lds)
-        err = hipLaunchCooperativeKernel((const void*)panel_kernel<true>, dim3(pa.G * batch), dim3(kPT), args,
-                                         (size_t)geo.rows * kNB * sizeof(double), ps);
-    else
-        err = hipLaunchCooperativeKernel((const void*)panel_kernel<false>, dim3(pa.G * batch), dim3(kPT), args, 0, ps);
+    StatScope sc(geo.variant >= 0 ? "panel_leaf<workgroups>" : "panel_kernel<global>", ps, flops, bytes);
+    if (geo.variant >= 0) {
+        const LeafVariant& v = kLeafVariants[geo.variant];
+        err = hipLaunchCooperativeKernel(v.multi, dim3(pa.G * batch), dim3(v.nt), args, 0, ps);
+    } else {
+        err = hipLaunchCooperativeKernel((const void*)panel_kernel, dim3(pa.G * batch), dim3(kPT), args, 0, ps);
+    }
     sc.end();
     if (err == hipSuccess && ps != st) {
         if ((err = hipEventRecord(w.ev_done, ps)) != hipSuccess) return err;
@@ -1086,8 +1527,13 @@ hipError_t structured_geqrf(int m, int e, int n, double* M, long long ld, long l
     const long long stT = (long long)npanels * kNB * kNB;
     const long long stb = (long long)nblocks * kQrBlock * kQrBlock;
     const long long sts = (long long)nsuper * kQrSuper * kQrSuper;
-    hipError_t err = zero_ints(reinterpret_cast<int*>(w.flags), (int)w.flag_elems, st);
-    if (err != hipSuccess) return err;
+    hipError_t err = hipSuccess;
+    // Tags and flags start from zero; the first panel has the most live rows.
+    if (panel_geometry(live_rows(m, e, 0, std::min(n, kNB)), batch, w.single_panels).G > 1) {
+        if ((err = zero_ints(reinterpret_cast<int*>(w.flags), (int)w.flag_elems, st)) != hipSuccess) return err;
+        if ((err = zero_ints(reinterpret_cast<int*>(w.colslots), (int)(2 * w.colslot_elems), st)) != hipSuccess)
+            return err;
+    }
     const bool lookahead = batch == 1 && !w.single_panels && w.side_stream && w.side_stream != st &&
                            w.ev_side_ready && w.ev_side_done && w.W_side && w.W2_side && w.splitk_side &&
                            (size_t)kQrSuper * n <= qr_w_elems(n, 1);

@@ -43,6 +43,7 @@
 
 namespace zolo {
 int panel_max_coresident();
+hipError_t open_cooperative_queue(int device, hipStream_t st);
 hipError_t scratch_address(int device, char** out);
 }
 
@@ -84,6 +85,7 @@ struct Work {
     double *sk, *feat;  // sketch scratch and the 39 features (learned l)
     float* mlp;         // network activations for one feature vector
     size_t bytes;
+    size_t counted;     // bytes without the tail that zolo_pd_noalloc's scratch holds beside its 256 MiB
 };
 
 // Lay out (or size, if base == nullptr) the workspace for m x n and degree
@@ -142,6 +144,10 @@ Work layout(char* base, int m, int n, int rmax, int panel_coresident, bool mixed
         w.s.trtri = ar.take<float>(nn * rmax / 2 + (size_t)64 * 64 * rmax + 64);
         w.s.potrf = ar.take<float>((size_t)64 * 64 * rmax);
     }
+    w.counted = ar.off + 256;
+    w.qr.colslot_elems = std::max(qr_colslot_elems(m, n, rmax, panel_coresident),
+                                  qr_colslot_elems(m, 0, 1, panel_coresident));
+    w.qr.colslots = ar.take<unsigned long long>(w.qr.colslot_elems);
     w.bytes = ar.off + 256;
     return w;
 }
@@ -425,11 +431,13 @@ int check_pd_args(zolo_handle h, int m, int n, const double* A, int lda, double 
 }
 
 // Device workspace one solve of m x n with degree r (<= 0: any) needs.
-size_t workspace_bytes(zolo_handle h, int m, int n, int r, const zolo_opts& opts) {
+size_t workspace_bytes(zolo_handle h, int m, int n, int r, const zolo_opts& opts, size_t* counted) {
     const int rmax = r >= 1 ? r : kMaxR;
     // The dense QR variant factors (m + n) x n matrices as plain ones.
     const int mq = opts.qr_variant == 1 ? m + n : m;
-    return layout(nullptr, mq, n, rmax, h->panel_coresident, opts.precision == 1).bytes;
+    const Work w = layout(nullptr, mq, n, rmax, h->panel_coresident, opts.precision == 1);
+    if (counted) *counted = w.counted;
+    return w.bytes;
 }
 
 #define HIPFIN(x)                                         \
@@ -762,9 +770,14 @@ int zolo_predict(double l, int r, int m, int n, double chol_switch, char* kinds,
 }
 
 // The QR look-ahead's stream and events (non-blocking, default priority);
-// without them the look-ahead's two parts run on the caller's stream.
-static void ensure_side_stream(zolo_handle h) {
-    if (h->side_stream) return;
+// without them the look-ahead's two parts run on the caller's stream.  Made
+// for the first n whose trailing updates have a far part, and not for the
+// solves of zolo_pd_batched, which do not use it: every stream takes a share
+// of the hardware queues (4 by default).  The cooperative panels' queue comes
+// first (see open_cooperative_queue).
+static void ensure_side_stream(zolo_handle h, int n) {
+    if (h->side_stream || h->single_panels || n <= 2 * kQrSuper) return;
+    if (open_cooperative_queue(h->device, h->stream) != hipSuccess) return;
     hipStream_t s = nullptr;
     hipEvent_t a = nullptr, b = nullptr;
     if (hipStreamCreateWithFlags(&s, hipStreamNonBlocking) != hipSuccess) return;
@@ -789,7 +802,7 @@ int zolo_pd(zolo_handle h, int m, int n, const double* A, int lda, double alpha,
     if (rc) return report(info, rc);
     const size_t bytes = workspace_bytes(h, m, n, r, opts);
     if ((rc = ensure(h, bytes))) return report(info, rc);
-    ensure_side_stream(h);
+    ensure_side_stream(h, n);
     return pd_core(h, h->arena, m, n, A, lda, alpha, l, r, Qp, ldq, H, ldh, opts, info);
 }
 

@@ -33,3 +33,73 @@ def test_alpha_estimate(z, m, n):
     _, _, info = z.pd(dev(A))
     assert info["status"] == 0
     assert abs(info["alpha"] / (1.01 * 3.7) - 1.0) <= 1e-9
+
+
+def check_qr(z, m, n, pivots, batch, seed):
+    """QR of [Y; p I] (or of Y): the bounds of the structured-QR block tests,
+    and R against LAPACK up to row signs."""
+    rng = np.random.default_rng(seed)
+    Y = rng.standard_normal((batch, m, n)) / np.sqrt(m)
+    import torch
+    Q, R = z.structured_qr(torch.from_numpy(Y).to("cuda"), pivots, form_q=True)
+    Q, R = Q.cpu().numpy(), R.cpu().numpy()
+    for b in range(batch):
+        S = np.vstack([Y[b], pivots[b] * np.eye(n)]) if pivots else Y[b]
+        assert np.linalg.norm(Q[b].T @ Q[b] - np.eye(n)) <= 1e-14 * n, b
+        assert np.linalg.norm(Q[b] @ R[b] - S) <= 1e-14 * n * np.linalg.norm(S), b
+        assert np.array_equal(np.tril(R[b], -1), np.zeros((n, n)))
+        Rl = np.linalg.qr(S, mode="r")
+        s = np.sign(np.diag(R[b])) * np.sign(np.diag(Rl))
+        assert np.abs(R[b] * s[:, None] - Rl).max() <= 1e-12 * np.abs(Rl).max(), b
+
+
+# Live rows (m + 64, or m without pivots) around each shape of the
+# register-leaf panel: 256, 512, 1024 rows in one workgroup, then several
+# workgroups with a ragged last slab; columns around the 16-column leaves and
+# the 64-column panels; a single column; the shortest panels.
+@pytest.mark.parametrize("m,n,batch,stacked", [
+    (1, 1, 2, True), (5, 3, 1, True), (17, 17, 2, False), (33, 31, 1, True), (64, 64, 1, False), (65, 65, 2, True),
+    (192, 64, 2, True), (193, 79, 1, True), (256, 20, 1, False), (257, 64, 1, False), (448, 64, 1, True),
+    (449, 96, 2, True), (960, 65, 1, True), (1024, 64, 1, False), (1025, 64, 3, False), (1217, 130, 1, True),
+    (2111, 64, 2, True)])
+def test_panel_shapes(z, m, n, batch, stacked):
+    pivots = [0.7 / (b + 1) for b in range(batch)] if stacked else None
+    check_qr(z, m, n, pivots, batch, 31 * m + n)
+
+
+def test_panel_beyond_the_tallest_shape(z):
+    # 16 matrices of 33 000 rows: more 2048-row slabs than the GPU holds at once.
+    check_qr(z, 33000, 66, None, 16, 5)
+
+
+def test_panel_zero_and_graded_columns(z):
+    # A zero column (no reflector), equal columns, and columns over 140 decades.
+    import torch
+    rng = np.random.default_rng(9)
+    Y = rng.standard_normal((1, 300, 70))
+    Y[0, :, 5] = 0.0
+    Y[0, :, 20] = Y[0, :, 19]
+    Y[0] *= np.power(10.0, -np.linspace(0.0, 140.0, 70))
+    Q, R = z.structured_qr(torch.from_numpy(Y).to("cuda"), None, form_q=True)
+    Q, R = Q[0].cpu().numpy(), R[0].cpu().numpy()
+    assert np.linalg.norm(Q.T @ Q - np.eye(70)) <= 1e-14 * 70
+    d = np.linalg.norm(Q @ R - Y[0], axis=0)
+    assert np.all(d <= 1e-14 * 70 * np.linalg.norm(Y[0], axis=0))
+
+
+@pytest.mark.parametrize("m,n", [(1024 - 64, 130), (1985, 70), (2048 - 64, 200), (2100, 100)])
+def test_batched_panels_one_workgroup(z, m, n):
+    # The many-matrix call's panels: one workgroup up to 2048 live rows, more
+    # past that; one stream and several give the same bits.
+    A, U, s, V = W.svd_matrix(m, n, 1e3, 600 + m, 700 + n)
+    mats = [dev(A), dev(A[:200, :50] + np.eye(200, 50)), dev(A)]
+    Q1, H1, i1 = z.pd_batched(mats, alphas=[1.0, 3.0, 1.0], ls=[1e-3, 1e-3, 1e-3], batch_streams=1)
+    Q2, H2, i2 = z.pd_batched(mats, alphas=[1.0, 3.0, 1.0], ls=[1e-3, 1e-3, 1e-3], batch_streams=3)
+    for a, b in zip(Q1 + H1, Q2 + H2):
+        assert np.array_equal(a.cpu().numpy(), b.cpu().numpy())
+    assert i1[0]["kinds"][0] == "Q"
+    Hx = (V * s) @ V.T
+    for k in (0, 2):
+        assert np.linalg.norm(H1[k].cpu().numpy() - Hx) <= 1e-12 * np.linalg.norm(Hx)
+        Q = Q1[k].cpu().numpy()
+        assert np.linalg.norm(Q.T @ Q - np.eye(n)) <= 1e-13 * np.sqrt(n)
