@@ -40,143 +40,166 @@ __device__ inline T lane_bcast(T x, int l) {
     }
 }
 
-// Inverse of the upper-triangular 64 x 64 matrix S (LDS; identity beyond the
-// matrix) into Si (LDS), by the workgroup's 256 threads.  The four 16 x 16
-// diagonal blocks are inverted at once (wave w inverts block w: lane j
-// back-substitutes column j in registers); then the off-diagonal blocks at
-// distance d = 1, 2, 3 follow from
-//     Si[I][J] = -Si[I][I] sum_{K=I+1..J} S[I][K] Si[K][J].
+// The upper triangle of the kb x kb block at Z into S (LDS), the identity
+// beyond it, by 256 threads with all loads in flight together.
 template <class T>
-__device__ void lds_upper_inverse(const T (*S)[kB + 1], T (*Si)[kB + 1]) {
-    __shared__ T Y[3][kDB][kDB + 1];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int o = w * kDB;
-    for (int e = tid; e < kB * kB; e += 256) Si[e % kB][e / kB] = 0;
-    __syncthreads();
-    if (lane < kDB) {
-        const int j = lane;
-        T x[kDB];
+__device__ void load_upper(const T* Z, long long ld, int kb, T (*S)[kB + 1]) {
+    const int i = threadIdx.x % kB, j0 = threadIdx.x / kB;
+    T v[kB / 4];
 #pragma unroll
-        for (int i = kDB - 1; i >= 0; --i) {
-            T s = (i == j) ? (T)1 : (T)0;
+    for (int u = 0; u < kB / 4; ++u) v[u] = Z[min(i, kb - 1) + (long long)min(j0 + 4 * u, kb - 1) * ld];
 #pragma unroll
-            for (int k = i + 1; k < kDB; ++k) s -= S[o + i][o + k] * x[k];
-            x[i] = i <= j ? s / S[o + i][o + i] : (T)0;
-        }
-#pragma unroll
-        for (int i = 0; i < kDB; ++i) Si[o + i][o + j] = x[i];
-    }
-    __syncthreads();
-    for (int d = 1; d < 4; ++d) {
-        const int nblk = 4 - d;
-        // Y_I = sum_{K=I+1..I+d} S[I][K] Si[K][I+d]
-        for (int e = tid; e < nblk * kDB * kDB; e += 256) {
-            const int I = e / (kDB * kDB), r = e % kDB, c = (e / kDB) % kDB;
-            const int J = I + d;
-            T acc = 0;
-            for (int k = (I + 1) * kDB; k < (J + 1) * kDB; ++k) acc += S[I * kDB + r][k] * Si[k][J * kDB + c];
-            Y[I][r][c] = acc;
-        }
-        __syncthreads();
-        // Si[I][J] = -Si[I][I] Y_I
-        for (int e = tid; e < nblk * kDB * kDB; e += 256) {
-            const int I = e / (kDB * kDB), r = e % kDB, c = (e / kDB) % kDB;
-            const int J = I + d;
-            T acc = 0;
-#pragma unroll
-            for (int k = 0; k < kDB; ++k) acc += Si[I * kDB + r][I * kDB + k] * Y[I][k][c];
-            Si[I * kDB + r][J * kDB + c] = -acc;
-        }
-        __syncthreads();
+    for (int u = 0; u < kB / 4; ++u) {
+        const int j = j0 + 4 * u;
+        const int in = opaque(((i < kb) & (j < kb) & (i <= j)) ? -1 : 0);
+        S[i][j] = keep_if(v[u], in) + (T)((i == j) & (i >= kb) ? 1 : 0);
     }
 }
 
+// Inverse of the upper-triangular 64 x 64 matrix S (LDS; identity beyond the
+// matrix) into Si (LDS), by the workgroup's 256 threads; rcp holds 1 / S[i][i].
+// The four 16 x 16 diagonal blocks are inverted at once (wave w inverts block
+// w: lane j back-substitutes column j in registers); then neighbouring blocks
+// of 16 and of 32 are merged on the matrix cores,
+//     Si12 = -Si11 (S12 Si22).
+template <class T>
+__device__ void lds_upper_inverse(const T (*S)[kB + 1], const T* rcp, T (*Si)[kB + 1]) {
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, l16 = lane & 15, lg = lane >> 4;
+    for (int e = tid; e < kB * kB; e += 256) {
+        const int i = e / kB, j = e % kB;
+        if (i / kDB != j / kDB) Si[i][j] = 0;
+    }
+    {
+        const int o = w * kDB;
+        T x[kDB];
+#pragma unroll
+        for (int i = kDB - 1; i >= 0; --i) {
+            T s0 = (i == l16) ? (T)1 : (T)0, s1 = 0;
+#pragma unroll
+            for (int k = i + 1; k < kDB; ++k) {
+                if (k & 1) s1 -= S[o + i][o + k] * x[k];
+                else s0 -= S[o + i][o + k] * x[k];
+            }
+            x[i] = i <= l16 ? (s0 + s1) * rcp[o + i] : (T)0;
+        }
+        if (lane < kDB) {
+#pragma unroll
+            for (int i = 0; i < kDB; ++i) Si[o + i][o + lane] = x[i];
+        }
+    }
+    __syncthreads();
+    for (int s = kDB; s < kB; s *= 2) {
+        const int ts = s / kDB, per = ts * ts, total = kB / (2 * s) * per;   // 2, 4 tiles
+        const int o = w / per * 2 * s, ti = w % per % ts * kDB, tj = w % per / ts * kDB;
+        for (int phase = 0; phase < 2; ++phase) {   // S12 Si22 into the place of Si12, then -Si11 times it
+            typename Mfma<T>::acc acc = {0, 0, 0, 0};
+            if (w < total) {
+                for (int k = 0; k < s; k += 4) {
+                    const T x = phase == 0 ? S[o + ti + l16][o + s + k + lg] : -Si[o + ti + l16][o + k + lg];
+                    const T y = phase == 0 ? Si[o + s + k + lg][o + s + tj + l16] : Si[o + k + lg][o + s + tj + l16];
+                    acc = Mfma<T>::run(x, y, acc);
+                }
+            }
+            __syncthreads();
+            if (w < total) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) Si[o + ti + Mfma<T>::row(lane, e)][o + s + tj + l16] = acc[e];
+            }
+            __syncthreads();
+        }
+    }
+}
+
+// sqrt(d) and 1 / sqrt(d) of a positive, finite d: the hardware estimate
+// refined to the last bit or so (the library's square root and divide, one
+// after the other, are most of a pivot's latency).
+__device__ inline void sqrt_rcp(double d, double& r, double& ri) {
+    if (d < 1e-280) {   // the residuals below would underflow
+        r = sqrt(d);
+        ri = 1.0 / r;
+        return;
+    }
+    const double y = __builtin_amdgcn_rsq(d);
+    double g = d * y, h = 0.5 * y;
+    double t = fma(-h, g, 0.5);
+    g = fma(g, t, g);
+    h = fma(h, t, h);
+    t = fma(-g, g, d);
+    g = fma(t, h, g);
+    t = fma(-g, g, d);
+    r = fma(t, h, g);
+    const double z = h + h;
+    ri = fma(fma(-r, z, 1.0), z, z);
+}
+__device__ inline void sqrt_rcp(float d, float& r, float& ri) {
+    r = sqrtf(d);
+    ri = 1.0f / r;
+}
 
 // Upper Cholesky of the kb x kb diagonal block at (k0, k0) of each matrix
-// (one workgroup per matrix), its inverse into work.  16-column blocks: wave
-// 0 factors the 16 x 16 diagonal block in registers (lane j holds column j,
-// rows broadcast with readlane), one thread per column solves the row panel
-// to its right, and the trailing block takes the rank-16 update, so the
-// factorisation needs 3 barriers per 16 columns.  A non-positive pivot is
-// reported (1-based global column) and replaced by 1 so that every wave
-// finishes; the caller discards the result.
+// (one workgroup per matrix), its inverse into work.  Four steps of 16 rows:
+// wave 0 holds the 16 rows of all 64 columns (lane = column) and factors them
+// in registers, the diagonal block and the row panel to its right in the same
+// instructions (the multipliers of a row reach all lanes by readlane); then the
+// rows below take their rank-16 update on the matrix cores, a 16 x 16 tile per
+// wave.  Rows and columns past kb are those of the identity.  A non-positive
+// pivot is reported (1-based global column) and replaced by 1 so that every
+// wave finishes; the caller discards the result.  Bound: latency of the 64
+// dependent pivots.  One launch in a solve takes 28 us (FP32: 23); with a block at
+// a time factored, its panel solved one thread per column and the trailing and
+// inverse blocks summed element by element it took 58 (51): 2.8 of the 10.9 ms of a
+// 3001 x 1501 solve by Cholesky-type steps, 1.6 of 4.1 ms of four FP32 factors at
+// n = 2000.
 template <class T>
 __global__ __launch_bounds__(256) void potrf_diag_kernel(int k0, int kb, T* Z, long long ldz, long long sz,
                                                          int* info, T* work) {
     __shared__ T S[kB][kB + 1];
     __shared__ T Si[kB][kB + 1];
-    __shared__ T s_rcp[kDB];
-    __shared__ int s_bad;
-    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+    __shared__ T s_rcp[kB];
+    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, lg = lane >> 4;
     T* Zb = Z + b * sz + k0 + (long long)k0 * ldz;
-    for (int e = tid; e < kB * kB; e += 256) {
-        const int i = e % kB, j = e / kB;
-        S[i][j] = (i < kb && j < kb && i <= j) ? Zb[i + (long long)j * ldz] : (T)0;
-    }
-    if (tid == 0) s_bad = 0;
+    load_upper<T>(Zb, ldz, kb, S);
     __syncthreads();
-    for (int jb = 0; jb < kb; jb += kDB) {
-        const int bw = kb - jb < kDB ? kb - jb : kDB;
-        if (tid < 64) {
-            // Lane j < 16 holds column jb + j of the diagonal block.
+    int bad = 0;
+#pragma unroll 1
+    for (int jb = 0; jb < kB; jb += kDB) {
+        if (wave == 0) {
             T c[kDB];
 #pragma unroll
-            for (int i = 0; i < kDB; ++i) c[i] = (lane < bw && i < bw) ? S[jb + i][jb + (lane & 15)] : (T)0;
-            int bad = 0;
+            for (int i = 0; i < kDB; ++i) c[i] = S[jb + i][lane];
 #pragma unroll
             for (int i = 0; i < kDB; ++i) {
-                if (i < bw) {
-                    T d = lane_bcast(c[i], i);
-                    if (!(d > (T)0) || !isfinite(d)) {
-                        if (bad == 0) bad = k0 + jb + i + 1;
-                        d = 1;
-                    }
-                    const T r = sqrt(d), ri = (T)1 / r;
-                    if (lane == 0) s_rcp[i] = ri;
-                    c[i] = lane == i ? r : (lane > i ? c[i] * ri : c[i]);
-#pragma unroll
-                    for (int l = i + 1; l < kDB; ++l) {
-                        const T ril = lane_bcast(c[i], l);  // R[i][jb + l]
-                        if (lane >= l) c[l] -= ril * c[i];
-                    }
+                T d = lane_bcast(c[i], jb + i);
+                if (!(d > (T)0) || !isfinite(d)) {
+                    if (bad == 0) bad = k0 + jb + i + 1;
+                    d = 1;
                 }
-            }
-            if (lane < bw) {
+                T r, ri;
+                sqrt_rcp(d, r, ri);
+                c[i] = lane == jb + i ? r : c[i] * ri;
+                if (lane == 0) s_rcp[jb + i] = ri;
 #pragma unroll
-                for (int i = 0; i < kDB; ++i)
-                    if (i < bw) S[jb + i][jb + lane] = i <= lane ? c[i] : (T)0;
+                for (int l = i + 1; l < kDB; ++l) c[l] -= lane_bcast(c[i], jb + l) * c[i];   // R[i][jb + l]
             }
-            if (lane == 0 && bad != 0 && s_bad == 0) s_bad = bad;
+#pragma unroll
+            for (int i = 0; i < kDB; ++i) S[jb + i][lane] = lane >= jb + i ? c[i] : (T)0;
         }
         __syncthreads();
-        const int c0 = jb + bw, w = kb - c0;
-        if (w <= 0) break;
-        // Row panel: R[jb:jb+bw, c] = R_d^{-T} Z[jb:jb+bw, c], one thread per column.
-        if (tid < w) {
-            const int col = c0 + tid;
-            T x[kDB];
+        // Rows below (upper tiles): S[i][j] -= sum_k R[jb+k][i] R[jb+k][j].
+        const int c0 = jb + kDB, nt = (kB - c0) / kDB;
+        for (int t = wave; t < nt * (nt + 1) / 2; t += 4) {
+            int ti = 0, tj = t;
+            while (tj >= nt - ti) tj -= nt - ti++;
+            tj += ti;
+            T* const row = &S[c0 + kDB * ti][c0 + kDB * tj + l16];
+            typename Mfma<T>::acc acc;
 #pragma unroll
-            for (int i = 0; i < kDB; ++i) {
-                if (i < bw) {
-                    T s0 = S[jb + i][col];
+            for (int e = 0; e < 4; ++e) acc[e] = row[Mfma<T>::row(lane, e) * (kB + 1)];
 #pragma unroll
-                    for (int k = 0; k < i; ++k) s0 -= S[jb + k][jb + i] * x[k];
-                    x[i] = s0 * s_rcp[i];
-                    S[jb + i][col] = x[i];
-                }
-            }
-        }
-        __syncthreads();
-        // Trailing block (upper part): S[i][j] -= sum_k R[jb+k][i] R[jb+k][j].
-        for (int e = tid; e < w * w; e += 256) {
-            const int i = c0 + e % w, j = c0 + e / w;
-            if (i <= j) {
-                T acc = 0;
+            for (int k = 0; k < kDB; k += 4)
+                acc = Mfma<T>::run(-S[jb + k + lg][c0 + kDB * ti + l16], S[jb + k + lg][c0 + kDB * tj + l16], acc);
 #pragma unroll
-                for (int k = 0; k < kDB; ++k)
-                    if (k < bw) acc += S[jb + k][i] * S[jb + k][j];
-                S[i][j] -= acc;
-            }
+            for (int e = 0; e < 4; ++e) row[Mfma<T>::row(lane, e) * (kB + 1)] = acc[e];
         }
         __syncthreads();
     }
@@ -184,16 +207,10 @@ __global__ __launch_bounds__(256) void potrf_diag_kernel(int k0, int kb, T* Z, l
         const int i = e % kb, j = e / kb;
         Zb[i + (long long)j * ldz] = (i <= j) ? S[i][j] : (T)0;
     }
-    if (tid >= kb && tid < kB) S[tid][tid] = 1;  // identity beyond the block
-    __syncthreads();
-    lds_upper_inverse<T>(S, Si);
-    __syncthreads();
+    lds_upper_inverse<T>(S, s_rcp, Si);
     T* wb = work + (long long)b * kB * kB;
-    for (int e = tid; e < kB * kB; e += 256) {
-        const int i = e % kB, j = e / kB;
-        wb[e] = Si[i][j];
-    }
-    if (tid == 0 && s_bad != 0 && info[b] == 0) info[b] = s_bad;
+    for (int e = tid; e < kB * kB; e += 256) wb[e] = Si[e % kB][e / kB];
+    if (tid == 0 && bad != 0 && info[b] == 0) info[b] = bad;
 }
 
 // Invert every 64 x 64 diagonal block of R_b into Rinv_b.
@@ -206,12 +223,12 @@ __global__ __launch_bounds__(256) void trtri_diag_kernel(int n, const T* R, long
     const int o = blk * kB, kb = min(kB, n - o);
     const T* Rb = R + b * sr + o + (long long)o * ldr;
     T* Ib = Rinv + b * si + o + (long long)o * ldi;
-    for (int e = tid; e < kB * kB; e += 256) {
-        const int i = e % kB, j = e / kB;
-        S[i][j] = (i < kb && j < kb && i <= j) ? Rb[i + (long long)j * ldr] : (T)(i == j ? 1 : 0);
-    }
+    load_upper<T>(Rb, ldr, kb, S);
     __syncthreads();
-    lds_upper_inverse<T>(S, Si);
+    __shared__ T s_rcp[kB];
+    if (tid < kB) s_rcp[tid] = (T)1 / S[tid][tid];
+    __syncthreads();
+    lds_upper_inverse<T>(S, s_rcp, Si);
     for (int e = tid; e < kb * kb; e += 256) {
         const int i = e % kb, j = e / kb;
         Ib[i + (long long)j * ldi] = Si[i][j];

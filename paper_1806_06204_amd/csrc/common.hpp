@@ -142,6 +142,20 @@ template <> struct Mfma<float> {
     __device__ static int row(int lane, int e) { return 4 * (lane >> 4) + e; }
 };
 
+// x where mask is -1, +0 where it is 0.  With a mask the compiler cannot see
+// through (opaque), a load into x stays unconditional: `in ? load : 0` may
+// become a branch around each load, which then waits for them one by one.
+__device__ inline double keep_if(double x, int mask) {
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
+    const unsigned lo = (unsigned)u & (unsigned)mask, hi = (unsigned)(u >> 32) & (unsigned)mask;
+    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+__device__ inline float keep_if(float x, int mask) { return __int_as_float(__float_as_int(x) & mask); }
+__device__ inline int opaque(int x) {
+    asm("" : "+v"(x));
+    return x;
+}
+
 __device__ inline double wave_sum(double v) {
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
     return v;

@@ -665,13 +665,6 @@ __device__ inline void ring_turn(double (&xr)[kLW], double c, double v) {
     }
 }
 
-// x where mask is -1, +0 where it is 0.
-__device__ inline double keep_if(double x, int mask) {
-    const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
-    const unsigned lo = (unsigned)u & (unsigned)mask, hi = (unsigned)(u >> 32) & (unsigned)mask;
-    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
-}
-
 // Packed strict upper triangle: (i, j), i < j.
 __device__ inline int upper_at(int i, int j) { return j * (j - 1) / 2 + i; }
 
@@ -793,8 +786,7 @@ __global__ __launch_bounds__(NT) void panel_leaf_kernel(PanelArgs a) {
         const int lw = min(kLW, nb - c0), leaf = c0 / kLW;
         double xr[J][kLW];
         // Loads from valid addresses, then zeros for rows past the slab and
-        // columns past a short leaf, by a mask the compiler cannot turn back
-        // into a branch around each load (which would wait for them one by one).
+        // columns past a short leaf.
 #pragma unroll
         for (int j = 0; j < J; ++j) {
             const unsigned at = min(tid + NT * j, nr - 1);
@@ -803,8 +795,7 @@ __global__ __launch_bounds__(NT) void panel_leaf_kernel(PanelArgs a) {
         }
 #pragma unroll
         for (int j = 0; j < J; ++j) {
-            int in = tid + NT * j < nr ? -1 : 0;
-            asm("" : "+v"(in));
+            const int in = opaque(tid + NT * j < nr ? -1 : 0);
 #pragma unroll
             for (int q = 0; q < kLW; ++q) xr[j][q] = keep_if(xr[j][q], q < lw ? in : 0);
         }
@@ -916,16 +907,14 @@ __global__ __launch_bounds__(NT) void panel_leaf_kernel(PanelArgs a) {
             const int row = tid + NT * j;
             __builtin_amdgcn_wave_barrier();
             if (j > 0 && lw == kLW) {             // no pivots here: V is the leaf as it is
-                int in = row < nr ? -1 : 0;
-                asm("" : "+v"(in));
+                const int in = opaque(row < nr ? -1 : 0);
 #pragma unroll
                 for (int q = 0; q < kLW; ++q) sv[q * VS + lane] = keep_if(v[q], in);
             } else {
 #pragma unroll
                 for (int q = 0; q < kLW; ++q) {
                     const int kr = c0 + q - r0;
-                    int in = row > kr && row < nr && q < lw ? -1 : 0;
-                    asm("" : "+v"(in));
+                    const int in = opaque(((row > kr) & (row < nr) & (q < lw)) ? -1 : 0);
                     sv[q * VS + lane] = row == kr && q < lw ? 1.0 : keep_if(v[q], in);
                 }
             }

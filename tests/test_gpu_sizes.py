@@ -103,3 +103,50 @@ def test_batched_panels_one_workgroup(z, m, n):
         assert np.linalg.norm(H1[k].cpu().numpy() - Hx) <= 1e-12 * np.linalg.norm(Hx)
         Q = Q1[k].cpu().numpy()
         assert np.linalg.norm(Q.T @ Q - np.eye(n)) <= 1e-13 * np.sqrt(n)
+
+
+# Orders around the 16-row steps and the 64-column blocks of the Cholesky and
+# of the triangular inverse, in both precisions.
+@pytest.mark.parametrize("dtype", ["float64", "float32"])
+@pytest.mark.parametrize("n", [1, 2, 15, 16, 17, 33, 48, 63, 64, 65, 100, 127, 129, 257])
+def test_cholesky_and_inverse_edges(z, n, dtype):
+    import torch
+    rng = np.random.default_rng(40 + n)
+    X = rng.standard_normal((3, 2 * n + 3, n)) / np.sqrt(2 * n)
+    Z = (np.transpose(X, (0, 2, 1)) @ X + 0.1 * np.eye(n)).astype(dtype)
+    R, info = z.potrf(torch.from_numpy(Z).to("cuda"))
+    Ri = z.trtri(R).cpu().numpy().astype(np.float64)
+    R = R.cpu().numpy().astype(np.float64)
+    u = np.finfo(dtype).eps / 2
+    assert info == [0, 0, 0]
+    for b in range(3):
+        assert np.array_equal(R[b], np.triu(R[b])) and np.array_equal(Ri[b], np.triu(Ri[b]))
+        Zb = Z[b].astype(np.float64)
+        # Backward errors of the two algorithms: (n + 1) u |R^T||R| and n u |Ri||R||Ri| to first order.
+        assert np.all(np.abs(R[b].T @ R[b] - Zb) <= 2 * (n + 8) * u * (np.abs(R[b]).T @ np.abs(R[b])))
+        assert np.linalg.norm(R[b] @ Ri[b] - np.eye(n)) <= 4 * (n + 8) * u * np.linalg.norm(R[b]) * np.linalg.norm(Ri[b])
+
+
+@pytest.mark.parametrize("at", [0, 15, 16, 40, 63, 64, 99])
+def test_cholesky_breakdown_column(z, at):
+    import torch
+    n = 100
+    Z = np.eye(n) * 4.0
+    Z[at, at] = -1.0
+    if at + 1 < n:
+        Z[at + 1, at + 1] = 0.0   # the first bad pivot is the one reported
+    R, info = z.potrf(torch.from_numpy(np.stack([Z, np.eye(n)])).to("cuda"))
+    assert info == [at + 1, 0]
+    assert np.array_equal(R.cpu().numpy()[1], np.eye(n))
+
+
+def test_cholesky_scaled(z):
+    # Pivots from 1e-300 to 1e300: R scales exactly by powers of two.
+    import torch
+    rng = np.random.default_rng(3)
+    X = rng.standard_normal((90, 70))
+    Z = X.T @ X
+    R0 = z.potrf(torch.from_numpy(Z[None]).to("cuda"))[0].cpu().numpy()[0]
+    for e in (-996, -400, 400, 980):
+        R = z.potrf(torch.from_numpy(np.ldexp(Z, e)[None]).to("cuda"))[0].cpu().numpy()[0]
+        assert np.abs(R - np.ldexp(R0, e // 2)).max() <= 1e-14 * np.ldexp(np.abs(R0).max(), e // 2)
