@@ -52,7 +52,7 @@ __device__ void load_upper(const T* Z, long long ld, int kb, T (*S)[kB + 1]) {
     for (int u = 0; u < kB / 4; ++u) {
         const int j = j0 + 4 * u;
         const int in = opaque(((i < kb) & (j < kb) & (i <= j)) ? -1 : 0);
-        S[i][j] = keep_if(v[u], in) + (T)((i == j) & (i >= kb) ? 1 : 0);
+        S[i][j] = keep_if(v[u], in) + (T)(((i == j) & (i >= kb)) ? 1 : 0);
     }
 }
 

@@ -32,7 +32,7 @@ constexpr int kTB = 32;       // tridiagonalisation panel width
 constexpr int kBT = 256;      // reflectors per block of the back-transformation
 constexpr int kFT = 128;      // reflectors whose T factor one workgroup forms in LDS
 constexpr int kET = 256;      // threads per workgroup
-constexpr int kMaxG = 512;    // workgroups of the row-parallel kernels (partial sums)
+constexpr int kMaxG = 512;    // workgroups of trd_product (partial sums)
 
 __device__ inline double block_sum256(double v, double* sh) {
     v = wave_sum(v);
@@ -43,19 +43,17 @@ __device__ inline double block_sum256(double v, double* sh) {
     return (sh[0] + sh[1]) + (sh[2] + sh[3]);
 }
 
-// Sum of the first g partials in a fixed order (every workgroup gets the same value).
-__device__ inline double sum_partials(const double* p, int g, double* sh) {
-    double s = 0.0;
-    for (int i = threadIdx.x; i < g; i += blockDim.x) s += p[i];
-    // fixed-order reduction: per-thread strided sums, then the block tree
-    return block_sum256(s, sh);
-}
-
 // ---------------------------------------------------------------------------
 // Stage 1.  Panel starting at column j0; column j = j0 + c.  V's columns are
 // the reflectors v_{j0..j-1}, stored in A below their explicit unit (row
 // j' + 1 of column j'); W holds w'_c (before the alpha_c v_c term, which
 // consumers add on the fly: w_c = w'_c + alpha_c v_c).
+//
+// Two launches per column.  trd_product multiplies the trailing matrix by the
+// column x below its first subdiagonal entry as it stands, before the norm of x
+// is known: with v = [1; s x], A v = A e_1 + s A x, and the same for V^T v, W^T v and
+// v^T A v.  trd_column then forms the reflector, w' of its column and the
+// update of the next column on the same rows, so that V and W are read once.
 // ---------------------------------------------------------------------------
 struct TrdArgs {
     int n, j, j0, c;
@@ -64,149 +62,259 @@ struct TrdArgs {
     double* alpha;                 // kTB: alpha_c
     double* tau;                   // n: tau_j
     double* d; double* e;          // n: diagonal, off-diagonal of T
-    double* sc;                    // n: 1 / (a - beta) of each column
-    double* y;                     // n: A22 v
-    double* pq;                    // 2 kTB: V^T v, W'^T v
-    double* partA; double* partW;  // kMaxG each
-    int gA, gW;                    // partial counts written by the producers
+    double* xa;                    // n: first subdiagonal entry of each column before its reflector
+    double* yr; double* a1;        // n: (A x)_i over rows >= j + 2, and A[j + 1][i]
+    double* pq;                    // 2 kTB: V^T x, W'^T x over the same rows
+    double* partA;                 // kMaxG: sums of squares of x
+    double* partY;                 // 2 kMaxG: sums of a1_i x_i and yr_i x_i, i >= j + 2
+    int gA, gY;                    // partial counts written by the producers
+    double* P; double* Q;          // n x 2 kTB: [V W] and [W V] of the panel's trailing rows
 };
 
-// A[j:n, j] -= V[j:n, 0:c] W[j, 0:c]^T + W[j:n, 0:c] V[j, 0:c]^T, then the
-// partial sums of a[j+2:n, j]^2.  First alpha_{c-1} = -tau_{c-1} (w'_{c-1}^T v_{c-1}) / 2.
-__global__ __launch_bounds__(kET) void trd_update_col(TrdArgs a) {
-    __shared__ double sh[4];
-    __shared__ double wj[kTB], vj[kTB], al[kTB];
-    const int n = a.n, j = a.j, c = a.c, j0 = a.j0;
+constexpr int kTrdRows = 64;       // rows per workgroup of trd_column
+
+// With c > 0: the reflector of column p = j - 1 (beta, tau, v), then
+//   w' = tau (y - V (W^T v) - W (V^T v)) on rows >= j, y = A22 v,
+//   alpha = -tau (w'^T v) / 2,  w'^T v = tau (v^T y - 2 (V^T v)^T (W^T v)),
+// v and w' stored.  Then, unless `finish`, column j takes the panel's update,
+//   A[j:n, j] -= V[j:n] W[j]^T + W[j:n] V[j]^T,
+// with its diagonal, its first subdiagonal entry and the partial sums of
+// a[j+2:n, j]^2; `finish` (end of a panel) writes the operands [V W], [W V] of
+// the trailing update instead.  One row per lane, the earlier columns of V
+// and W spread over the four waves; what every row needs of row j is formed
+// by each workgroup for itself from values this launch does not change.
+__global__ __launch_bounds__(kET) void trd_column(TrdArgs a, int finish) {
+    __shared__ double sh[3][4];
+    __shared__ double s_p[kTB], s_q[kTB], s_al[kTB], s_wj[kTB], s_vj[kTB], s_sc[4];
+    __shared__ double s_acc[4][kTrdRows][2];
+    const int n = a.n, j = a.j, c = a.c, j0 = a.j0, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // Everything that does not wait for the reflector is loaded first: the
+    // wave's share of the earlier columns on this lane's row, and what wave 0
+    // needs of row j and of the row itself.
+    const int row = j + blockIdx.x * kTrdRows + lane, rc = min(row, n - 1);
+    constexpr int S = kTB / 4;
+    double vr[S], wr[S];
+#pragma unroll
+    for (int u = 0; u < S; ++u) {
+        const int k = min(wave + 4 * u, max(c - 2, 0));
+        vr[u] = a.A[rc + (long long)(j0 + k) * a.lda];
+        wr[u] = a.W[rc + (long long)k * a.ldw];
+    }
+    const int kl = min(lane, max(c - 2, 0));
+    const double rv = a.A[j + (long long)(j0 + kl) * a.lda], rw = a.W[j + (long long)kl * a.ldw];
+    const double ral = a.alpha[kl], rpv = a.pq[kl], rpw = a.pq[kTB + kl];
+    const double x1 = a.xa[max(j - 1, 0)], y1 = a.a1[j], y2 = a.yr[j];
+    const double ca1 = a.a1[rc], cyr = a.yr[rc], cp = a.A[rc + (long long)max(j - 1, 0) * a.lda];
+    const double cj = a.A[rc + (long long)j * a.lda];
     if (c > 0) {
-        const double s = sum_partials(a.partW, a.gW, sh);
-        if (threadIdx.x == 0) {
-            const double t = a.tau[j - 1];
-            al[c - 1] = -0.5 * t * s;
-            if (blockIdx.x == 0) a.alpha[c - 1] = al[c - 1];
+        double s0 = 0.0, s1 = 0.0, s2 = 0.0;
+        for (int i = tid; i < a.gA; i += kET) s0 += a.partA[i];
+        for (int i = tid; i < a.gY; i += kET) {
+            s1 += a.partY[2 * i];
+            s2 += a.partY[2 * i + 1];
         }
-    }
-    if ((int)threadIdx.x < c - 1) al[threadIdx.x] = a.alpha[threadIdx.x];
-    __syncthreads();
-    if ((int)threadIdx.x < c) {
-        const int q = threadIdx.x;
-        const double v = a.A[j + (long long)(j0 + q) * a.lda];      // V[j, q] (1 for q = c - 1)
-        vj[q] = v;
-        wj[q] = a.W[j + (long long)q * a.ldw] + al[q] * v;         // W[j, q]
-    }
-    __syncthreads();
-    double part = 0.0;
-    for (int row = j + blockIdx.x * kET + threadIdx.x; row < n; row += gridDim.x * kET) {
-        double x = a.A[row + (long long)j * a.lda];
-        for (int q = 0; q < c; ++q) {
-            const double vr = a.A[row + (long long)(j0 + q) * a.lda];
-            const double wr = a.W[row + (long long)q * a.ldw] + al[q] * vr;
-            x -= vr * wj[q] + wr * vj[q];
-        }
-        a.A[row + (long long)j * a.lda] = x;
-        if (row >= j + 2) part += x * x;
-    }
-    part = block_sum256(part, sh);
-    if (threadIdx.x == 0) a.partA[blockIdx.x] = part;
-}
-
-// The reflector of column j (beta, tau, v = [1; a[j+2:n, j] / (alpha - beta)]),
-// then y_i = A[j+1:n, i]^T v for the trailing columns i > j and the 2c dots
-// V^T v, W'^T v.  One wave per column; v is formed on the fly from column j.
-__global__ __launch_bounds__(kET) void trd_symv(TrdArgs a) {
-    __shared__ double sh[4];
-    __shared__ double s_scale;
-    const int n = a.n, j = a.j, c = a.c;
-    const double s2 = sum_partials(a.partA, a.gA, sh);
-    if (threadIdx.x == 0) {
-        const double al = a.A[(j + 1) + (long long)j * a.lda];
-        double beta = al, t = 0.0, scale = 0.0;
-        if (s2 > 0.0) {
-            const double nrm = sqrt(al * al + s2);
-            beta = al >= 0.0 ? -nrm : nrm;
-            t = (beta - al) / beta;
-            scale = 1.0 / (al - beta);
-        }
-        s_scale = scale;
-        if (blockIdx.x == 0) {
-            a.d[j] = a.A[j + (long long)j * a.lda];
-            a.e[j] = beta;
-            a.tau[j] = t;
-            a.sc[j] = scale;
-        }
-    }
-    __syncthreads();
-    const double scale = s_scale;
-    const int lane = threadIdx.x & 63;
-    const int nw = gridDim.x * (kET / 64);
-    const int items = (n - j - 1) + 2 * c;
-    const double* colj = a.A + (long long)j * a.lda;
-    for (int it = blockIdx.x * (kET / 64) + (threadIdx.x >> 6); it < items; it += nw) {
-        const double* col;
-        if (it < n - j - 1) col = a.A + (long long)(j + 1 + it) * a.lda;
-        else if (it - (n - j - 1) < c) col = a.A + (long long)(a.j0 + it - (n - j - 1)) * a.lda;
-        else col = a.W + (long long)(it - (n - j - 1) - c) * a.ldw;
-        double s = 0.0;
-        for (int row = j + 1 + lane; row < n; row += 64) {
-            const double v = row == j + 1 ? 1.0 : scale * colj[row];
-            s += col[row] * v;
-        }
-        s = wave_sum(s);
+        s0 = wave_sum(s0);
+        s1 = wave_sum(s1);
+        s2 = wave_sum(s2);
         if (lane == 0) {
-            if (it < n - j - 1) a.y[j + 1 + it] = s;
-            else a.pq[it - (n - j - 1)] = s;
+            sh[0][wave] = s0;
+            sh[1][wave] = s1;
+            sh[2][wave] = s2;
+        }
+        __syncthreads();
+        if (wave == 0) {
+            const double xx = (sh[0][0] + sh[0][1]) + (sh[0][2] + sh[0][3]);
+            const double ax = (sh[1][0] + sh[1][1]) + (sh[1][2] + sh[1][3]);
+            const double yx = (sh[2][0] + sh[2][1]) + (sh[2][2] + sh[2][3]);
+            double beta = x1, t = 0.0, scale = 0.0;
+            if (xx > 0.0) {
+                const double nrm = sqrt(x1 * x1 + xx);
+                beta = x1 >= 0.0 ? -nrm : nrm;
+                t = (beta - x1) / beta;
+                scale = 1.0 / (x1 - beta);
+            }
+            const int k = lane;
+            double vk = 0.0, wk = 0.0, pk = 0.0, qk = 0.0, alk = 0.0;
+            if (k < c - 1) {
+                alk = ral;
+                vk = rv;
+                pk = vk + scale * rpv;                                   // V^T v
+                qk = rw + scale * rpw + alk * pk;                        // W^T v
+                wk = rw + alk * vk;                                      // W[j][k]
+            }
+            const double pq = wave_sum(pk * qk), vq = wave_sum(vk * qk + wk * pk);
+            const double yj = y1 + scale * y2;
+            const double al = -0.5 * t * t * (yj + scale * (ax + scale * yx) - 2.0 * pq);
+            if (k == c - 1) {
+                alk = al;
+                vk = 1.0;
+                wk = t * (yj - vq) + al;
+            }
+            if (k < c) {
+                s_p[k] = pk;
+                s_q[k] = qk;
+                s_al[k] = alk;
+                s_vj[k] = vk;
+                s_wj[k] = wk;
+            }
+            if (lane == 0) {
+                s_sc[0] = t;
+                s_sc[1] = scale;
+                if (blockIdx.x == 0) {
+                    a.e[j - 1] = beta;
+                    a.tau[j - 1] = t;
+                    a.alpha[c - 1] = al;
+                }
+            }
+        }
+        __syncthreads();
+    }
+    // This lane's row: the sums over the wave's share of the earlier columns.
+    double u0 = 0.0, u1 = 0.0;
+#pragma unroll
+    for (int u = 0; u < S; ++u) {
+        const int k = wave + 4 * u;
+        if (k >= c - 1) break;
+        const double v = vr[u], w = wr[u] + s_al[k] * v;
+        u0 += v * s_q[k] + w * s_p[k];
+        u1 += v * s_wj[k] + w * s_vj[k];
+        if (finish && row < n) {
+            const long long at = row + (long long)k * n, jb = (long long)c * n;
+            a.P[at] = v;
+            a.P[at + jb] = w;
+            a.Q[at] = w;
+            a.Q[at + jb] = v;
         }
     }
-}
-
-// w'_c = tau (y - V (W^T v) - W (V^T v)) on rows j+1..n-1 (W = W' + alpha V),
-// v stored into A[j+1:n, j] (explicit unit), partial sums of w'^T v.
-__global__ __launch_bounds__(kET) void trd_w(TrdArgs a) {
-    __shared__ double sh[4];
-    __shared__ double p[kTB], q[kTB], al[kTB];
-    const int n = a.n, j = a.j, c = a.c, j0 = a.j0;
-    if ((int)threadIdx.x < c) {
-        const int t = threadIdx.x;
-        al[t] = a.alpha[t];
-        p[t] = a.pq[t];                              // V^T v
-        q[t] = a.pq[c + t] + a.alpha[t] * a.pq[t];   // W^T v
-    }
+    s_acc[wave][lane][0] = u0;
+    s_acc[wave][lane][1] = u1;
     __syncthreads();
-    const double t = a.tau[j], scale = a.sc[j];
+    if (wave != 0) return;
     double part = 0.0;
-    for (int row = j + 1 + blockIdx.x * kET + threadIdx.x; row < n; row += gridDim.x * kET) {
-        const double v = row == j + 1 ? 1.0 : scale * a.A[row + (long long)j * a.lda];
-        double x = a.y[row];
-        for (int k = 0; k < c; ++k) {
-            const double vr = a.A[row + (long long)(j0 + k) * a.lda];
-            const double wr = a.W[row + (long long)k * a.ldw] + al[k] * vr;
-            x -= vr * q[k] + wr * p[k];
+    if (row < n) {
+        u0 = (s_acc[0][lane][0] + s_acc[1][lane][0]) + (s_acc[2][lane][0] + s_acc[3][lane][0]);
+        u1 = (s_acc[0][lane][1] + s_acc[1][lane][1]) + (s_acc[2][lane][1] + s_acc[3][lane][1]);
+        double v = 0.0, w = 0.0;
+        if (c > 0) {
+            const double t = s_sc[0], scale = s_sc[1];
+            v = row == j ? 1.0 : scale * cp;
+            const double w1 = t * (ca1 + scale * cyr - u0);
+            a.A[row + (long long)(j - 1) * a.lda] = v;
+            a.W[row + (long long)(c - 1) * a.ldw] = w1;
+            w = w1 + s_al[c - 1] * v;
         }
-        x *= t;
-        a.W[row + (long long)c * a.ldw] = x;
-        a.A[row + (long long)j * a.lda] = v;
-        part += x * v;
+        if (finish) {
+            const long long at = row + (long long)(c - 1) * n, jb = (long long)c * n;
+            a.P[at] = v;
+            a.P[at + jb] = w;
+            a.Q[at] = w;
+            a.Q[at + jb] = v;
+        } else {
+            double x = cj;
+            if (c > 0) x -= u1 + v * s_wj[c - 1] + w * s_vj[c - 1];
+            a.A[row + (long long)j * a.lda] = x;
+            if (row == j) a.d[j] = x;
+            if (row == j + 1) a.xa[j] = x;
+            if (row >= j + 2) part = x * x;
+        }
     }
-    part = block_sum256(part, sh);
-    if (threadIdx.x == 0) a.partW[blockIdx.x] = part;
+    if (finish) return;
+    part = wave_sum(part);
+    if (lane == 0) a.partA[blockIdx.x] = part;
 }
 
-// End of a panel: alpha of its last column, then W = W' + alpha V on the
-// trailing rows r0..n-1 (the operands of the rank-2 kTB update).
-__global__ __launch_bounds__(kET) void trd_finish_panel(TrdArgs a, int jb, int r0) {
-    __shared__ double sh[4];
-    __shared__ double al[kTB];
-    const double s = sum_partials(a.partW, a.gW, sh);
-    if (threadIdx.x == 0) {
-        al[jb - 1] = -0.5 * a.tau[a.j0 + jb - 1] * s;
-        if (blockIdx.x == 0) a.alpha[jb - 1] = al[jb - 1];
+// x = A[j+2:n, j]: yr_i = A[j+2:n, i]^T x and a1_i = A[j+1][i] for the trailing
+// columns i > j, V^T x and W'^T x, and per workgroup the sums of a1_i x_i and
+// yr_i x_i.  A wave takes C columns at a time (x is read once for them), two
+// rows per lane and load.  Bound: the trailing matrix read once per column,
+// n^3 / 3 doubles over the reduction: 4.8 TB/s at n = 2048-4096 (15.9 us a
+// column), launch latency below.  One wave per column with one 8-byte load at a
+// time took 20 us a column over the whole reduction of n = 4096, and the column
+// update and w two launches of 5.3 us; with these two kernels and one rank-64
+// trailing update per panel in place of two of rank 32, Zolo-SVD went from 231 to
+// 166 ms, 900 x 600 from 20.5 to 16.6 ms.
+template <int C>
+__global__ __launch_bounds__(kET) void trd_product(TrdArgs a) {
+    typedef double pair_u __attribute__((ext_vector_type(2), aligned(8)));
+    constexpr int U = C == 1 ? 4 : (C == 2 ? 4 : 2);   // 16-byte loads in flight per column
+    __shared__ double sh[2][4];
+    const int n = a.n, j = a.j, c = a.c, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int nt = n - j - 1, items = nt + 2 * c, nw = gridDim.x * 4;
+    const double* x = a.A + (long long)j * a.lda;
+    double ax = 0.0, yx = 0.0;
+    for (int g = blockIdx.x * 4 + wave; g * C < items; g += nw) {
+        const double* col[C];
+#pragma unroll
+        for (int u = 0; u < C; ++u) {
+            const int it = min(g * C + u, items - 1);
+            col[u] = it < nt ? a.A + (long long)(j + 1 + it) * a.lda
+                             : (it < nt + c ? a.A + (long long)(a.j0 + it - nt) * a.lda
+                                            : a.W + (long long)(it - nt - c) * a.ldw);
+        }
+        double s[C][2];
+#pragma unroll
+        for (int u = 0; u < C; ++u) s[u][0] = s[u][1] = 0.0;
+        int r0 = j + 2;
+        for (; r0 + 128 * U <= n; r0 += 128 * U) {
+            pair_u xv[U], cv[C][U];
+#pragma unroll
+            for (int q = 0; q < U; ++q) xv[q] = *reinterpret_cast<const pair_u*>(x + r0 + 128 * q + 2 * lane);
+#pragma unroll
+            for (int u = 0; u < C; ++u)
+#pragma unroll
+                for (int q = 0; q < U; ++q) cv[u][q] = *reinterpret_cast<const pair_u*>(col[u] + r0 + 128 * q + 2 * lane);
+#pragma unroll
+            for (int u = 0; u < C; ++u)
+#pragma unroll
+                for (int q = 0; q < U; ++q) {
+                    s[u][0] += cv[u][q][0] * xv[q][0];
+                    s[u][1] += cv[u][q][1] * xv[q][1];
+                }
+        }
+        // The rest (fewer than 128 U rows), single rows from clamped addresses.
+        if (r0 < n) {
+            double xv[2 * U], cv[C][2 * U];
+#pragma unroll
+            for (int q = 0; q < 2 * U; ++q) xv[q] = x[min(r0 + 64 * q + lane, n - 1)];
+#pragma unroll
+            for (int u = 0; u < C; ++u)
+#pragma unroll
+                for (int q = 0; q < 2 * U; ++q) cv[u][q] = col[u][min(r0 + 64 * q + lane, n - 1)];
+#pragma unroll
+            for (int q = 0; q < 2 * U; ++q) {
+                const double xq = keep_if(xv[q], opaque(r0 + 64 * q + lane < n ? -1 : 0));
+#pragma unroll
+                for (int u = 0; u < C; ++u) s[u][q & 1] += cv[u][q] * xq;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < C; ++u) {
+            const double y = wave_sum(s[u][0] + s[u][1]);
+            const int it = g * C + u;
+            if (lane == 0 && it < items) {
+                if (it < nt) {
+                    const double first = col[u][j + 1];
+                    a.yr[j + 1 + it] = y;
+                    a.a1[j + 1 + it] = first;
+                    if (it > 0) {
+                        const double xi = x[j + 1 + it];
+                        ax += first * xi;
+                        yx += y * xi;
+                    }
+                } else {
+                    a.pq[it < nt + c ? it - nt : kTB + it - nt - c] = y;
+                }
+            }
+        }
     }
-    if ((int)threadIdx.x < jb - 1) al[threadIdx.x] = a.alpha[threadIdx.x];
+    if (lane == 0) {
+        sh[0][wave] = ax;
+        sh[1][wave] = yx;
+    }
     __syncthreads();
-    const long long rows = a.n - r0;
-    for (long long e = blockIdx.x * (long long)kET + threadIdx.x; e < rows * jb; e += (long long)gridDim.x * kET) {
-        const int q = (int)(e / rows);
-        const int row = r0 + (int)(e - q * rows);
-        a.W[row + (long long)q * a.ldw] += al[q] * a.A[row + (long long)(a.j0 + q) * a.lda];
+    if (threadIdx.x < 2) {
+        const double* p = sh[threadIdx.x];
+        a.partY[2 * blockIdx.x + threadIdx.x] = (p[0] + p[1]) + (p[2] + p[3]);
     }
 }
 
@@ -588,11 +696,14 @@ T* carve(char*& p, size_t count) {
 
 }  // namespace
 
+static size_t row_groups_max(int n) { return ((size_t)n + kTrdRows - 1) / kTrdRows; }
+
 size_t syevd_work_bytes(int n) {
     const size_t nn = (size_t)n * n, N = (size_t)n + 64;
     const size_t nblk = ((size_t)n + kBT - 1) / kBT;
     return 3 * (nn * 8 + 256) + (size_t)n * kTB * 8 + 256 + nblk * (2 * kBT * kBT + kFT * kFT) * 8 + 768 +
-           20 * (N * 8 + 256) + 10 * (N * 4 + 256) + 4 * (kMaxG * 8 + 256) + 4096;
+           2 * ((size_t)n * 2 * kTB * 8 + 256) + 22 * (N * 8 + 256) + 10 * (N * 4 + 256) +
+           (row_groups_max(n) + 2 * kMaxG) * 8 + 4096;
 }
 
 // Eigen-decomposition of the symmetric n x n matrix A (lower triangle used;
@@ -613,8 +724,9 @@ hipError_t syevd(int n, double* A, long long lda, double* w_host, double* Z, lon
     double* Tf = carve<double>(p, (size_t)nblk * kBT * kBT);
     double* Y = carve<double>(p, (size_t)nblk * kFT * kFT);
     const size_t N = (size_t)n + 64;
-    double *d = carve<double>(p, N), *e = carve<double>(p, N), *tau = carve<double>(p, N), *sc = carve<double>(p, N);
-    double *y = carve<double>(p, N), *pq = carve<double>(p, N), *alpha = carve<double>(p, N);
+    double *d = carve<double>(p, N), *e = carve<double>(p, N), *tau = carve<double>(p, N), *xa = carve<double>(p, N);
+    double *yr = carve<double>(p, N), *a1 = carve<double>(p, N), *pq = carve<double>(p, N), *alpha = carve<double>(p, N);
+    double *P = carve<double>(p, (size_t)n * 2 * kTB), *Q = carve<double>(p, (size_t)n * 2 * kTB);
     double *D = carve<double>(p, N), *ds = carve<double>(p, N), *zs = carve<double>(p, N);
     double *pole = carve<double>(p, N), *zp = carve<double>(p, N), *dval = carve<double>(p, N);
     double *rc = carve<double>(p, N), *rs = carve<double>(p, N), *dtau = carve<double>(p, N);
@@ -622,51 +734,43 @@ hipError_t syevd(int n, double* A, long long lda, double* w_host, double* Z, lon
     int *colsrc = carve<int>(p, N), *src = carve<int>(p, N), *ri = carve<int>(p, N), *rj = carve<int>(p, N);
     int *org = carve<int>(p, N), *inv = carve<int>(p, N), *Kc = carve<int>(p, N), *nrot = carve<int>(p, N);
     int* perm = carve<int>(p, N);
-    double* partA = carve<double>(p, kMaxG);
-    double* partW = carve<double>(p, kMaxG);
+    double* partA = carve<double>(p, row_groups_max(n));
+    double* partY = carve<double>(p, 2 * kMaxG);
     hipError_t err;
 
     // --- Stage 1: tridiagonalisation ----------------------------------------
     TrdArgs ta;
     ta.n = n; ta.A = A; ta.lda = lda; ta.W = W; ta.ldw = n; ta.alpha = alpha; ta.tau = tau;
-    ta.d = d; ta.e = e; ta.sc = sc; ta.y = y; ta.pq = pq; ta.partA = partA; ta.partW = partW;
+    ta.d = d; ta.e = e; ta.xa = xa; ta.yr = yr; ta.a1 = a1; ta.pq = pq; ta.partA = partA; ta.partY = partY;
+    ta.P = P; ta.Q = Q;
+    auto row_groups = [](int rows) { return (rows + kTrdRows - 1) / kTrdRows; };
     for (int j0 = 0; j0 < n - 1; j0 += kTB) {
         const int jb = std::min(kTB, n - 1 - j0);
         ta.j0 = j0;
         for (int c = 0; c < jb; ++c) {
             const int j = j0 + c;
             ta.j = j; ta.c = c;
-            const int rows = n - j;
-            const int gA = std::max(1, std::min(kMaxG, (rows + kET - 1) / kET));
-            ta.gA = gA;
-            trd_update_col<<<gA, kET, 0, st>>>(ta);
-            const int items = (n - j - 1) + 2 * c;
-            const int gB = std::max(1, std::min(2048, (items + 3) / 4));
-            trd_symv<<<gB, kET, 0, st>>>(ta);
-            const int gW = std::max(1, std::min(kMaxG, (rows - 1 + kET - 1) / kET));
-            trd_w<<<gW, kET, 0, st>>>(ta);
-            ta.gW = gW;
+            trd_column<<<row_groups(n - j), kET, 0, st>>>(ta, 0);
+            ta.gA = row_groups(n - j);
+            // Columns per wave: enough waves to fill the chip first (256 CUs,
+            // four waves a workgroup), then fewer reads of x.
+            const int items = (n - j - 1) + 2 * c, C = items >= 4096 ? 4 : (items >= 2048 ? 2 : 1);
+            ta.gY = std::min(kMaxG, ((items + C - 1) / C + 3) / 4);
+            if (C == 4) trd_product<4><<<ta.gY, kET, 0, st>>>(ta);
+            else if (C == 2) trd_product<2><<<ta.gY, kET, 0, st>>>(ta);
+            else trd_product<1><<<ta.gY, kET, 0, st>>>(ta);
         }
         const int r0 = j0 + jb;
         const int nt = n - r0;
-        {
-            const long long tot = (long long)nt * jb;
-            const int g = (int)std::max(1LL, std::min<long long>(1024, (tot + kET - 1) / kET));
-            trd_finish_panel<<<g, kET, 0, st>>>(ta, jb, r0);
-        }
-        if (nt > 0) {
-            GemmDesc g1;  // A22 -= V W^T
-            g1.m = nt; g1.n = nt; g1.k = jb; g1.transb = 1;
-            g1.A = A + r0 + (long long)j0 * lda; g1.lda = lda;
-            g1.B = W + r0; g1.ldb = n;
-            g1.Cin = A + r0 + (long long)r0 * lda; g1.ldcin = lda; g1.beta = 1.0; g1.alpha = -1.0;
-            g1.C = A + r0 + (long long)r0 * lda; g1.ldc = lda;
-            if ((err = gemm(g1, st)) != hipSuccess) return err;
-            GemmDesc g2 = g1;  // A22 -= W V^T
-            g2.A = W + r0; g2.lda = n;
-            g2.B = A + r0 + (long long)j0 * lda; g2.ldb = lda;
-            if ((err = gemm(g2, st)) != hipSuccess) return err;
-        }
+        ta.j = r0; ta.c = jb;
+        trd_column<<<row_groups(nt), kET, 0, st>>>(ta, 1);
+        GemmDesc g;  // A22 -= [V W] [W V]^T
+        g.m = nt; g.n = nt; g.k = 2 * jb; g.transb = 1;
+        g.A = P + r0; g.lda = n;
+        g.B = Q + r0; g.ldb = n;
+        g.Cin = A + r0 + (long long)r0 * lda; g.ldcin = lda; g.beta = 1.0; g.alpha = -1.0;
+        g.C = A + r0 + (long long)r0 * lda; g.ldc = lda;
+        if ((err = gemm(g, st)) != hipSuccess) return err;
     }
     trd_cleanup<<<std::max(1, std::min(2048, (int)(((long long)n * n + kET - 1) / kET))), kET, 0, st>>>(n, A, lda, d);
     if ((err = hipGetLastError()) != hipSuccess) return err;
