@@ -34,10 +34,8 @@ constexpr int kBK = 16;
 constexpr int kPad = 4;
 constexpr int kTileGroup = 8;   // tiles are ordered in groups of 8 tile-rows
 
-// 128 x 128 tiles hold 128 accumulator doubles per lane: one wave per SIMD
-// (512 registers); smaller tiles run two.
 template <class T, int BM, int BN, bool TA, bool TB>
-__global__ __launch_bounds__(256, (BM * BN >= 128 * 128) ? 1 : 2) void gemm_kernel(GemmDescT<T> d) {
+__global__ __launch_bounds__(256, 2) void gemm_kernel(GemmDescT<T> d) {
     typedef typename Mfma<T>::acc acc_t;
     constexpr int BK = kBK;
     constexpr int FM = BM / 32, FN = BN / 32;
@@ -270,11 +268,8 @@ __global__ void splitk_reduce_kernel(GemmDescT<T> d) {
         if (!ok) continue;
         T s = 0;
         for (int z = 0; z < d.splitk; ++z) s += d.work[((long long)z * nout + ob) * mn + r];
-        T v = s;
-        if (!d.prescaled) {
-            v = (T)d.alpha * s;
-            if (d.Cin && d.beta != 0.0) v += (T)d.beta * d.Cin[ob * d.strideCin + gi + (long long)gj * d.ldcin];
-        }
+        T v = (T)d.alpha * s;
+        if (d.Cin && d.beta != 0.0) v += (T)d.beta * d.Cin[ob * d.strideCin + gi + (long long)gj * d.ldcin];
         d.C[ob * d.strideC + gi + (long long)gj * d.ldc] = v;
     }
 }
@@ -400,290 +395,8 @@ hipError_t launch_bm_bn(const GemmDescT<T>& desc, hipStream_t s) {
     return hipGetLastError();
 }
 
-// FP64 GEMM on the vector units.  On gfx950 the FP64 FMA pipes outrun the
-// FP64 matrix cores (measured peaks 67 and 36-40 TFLOP/s; 61 TFLOP/s for
-// this kernel's inner loop with operands from LDS), so large FP64 products
-// run here.  128 x 128 tiles, 256 threads, 8 x 8 outputs per thread in
-// registers, operands read from LDS as 16-byte pairs (8 reads per 64 FMAs).
-// Thread (tx, ty) = (tid % 16, tid / 16) owns rows 32 q + 2 tx + {0, 1} and
-// columns 32 q + 2 ty + {0, 1}, q = 0..3, so the 16 lanes of a row group
-// read 256 contiguous bytes.  beta * Cin seeds the accumulators and
-// alpha * alpha_b scales A as it is staged, so results are stored straight
-// from the k-loop (in split-K mode piece 0 carries beta * Cin).  Staging,
-// tile order, structure flags and split-K follow gemm_kernel.
 typedef double dpair __attribute__((ext_vector_type(2)));
-constexpr int kValuBK = 8;   // k-slice: 4 staged values per operand and thread
-
-// acc[i][j] += a[i] b[j] for one k step (a, b as 4 pairs each).
-__device__ inline void fma_8x8(double (&acc)[8][8], const dpair (&a)[4], const dpair (&b)[4]) {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const double ai = (i & 1) ? a[i >> 1].y : a[i >> 1].x;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) acc[i][j] = fma(ai, (j & 1) ? b[j >> 1].y : b[j >> 1].x, acc[i][j]);
-    }
-}
-
-template <bool TA, bool TB>
-__global__ __launch_bounds__(256, 2) void dgemm_valu_kernel(GemmDescT<double> d) {
-    constexpr int BM = 128, BN = 128, BK = kValuBK;
-    constexpr int APT = BM * BK / 256, BPT = BN * BK / 256;
-    __shared__ double As[2][BK][BM + kPad];
-    __shared__ double Bs[2][BK][BN + kPad];
-
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-    const int tiles_m = (d.m + BM - 1) / BM, tiles_n = (d.n + BN - 1) / BN;
-    const int nblocks = tiles_m * tiles_n;
-    int lin;
-    if (d.xbal) {
-        const int x = blockIdx.x % kNumXcd, idx = blockIdx.x / kNumXcd;
-        lin = d.xsplit[x] + idx;
-        if (lin >= d.xsplit[x + 1]) return;
-    } else {
-        lin = xcd_remap(blockIdx.x, nblocks);
-    }
-    const int in_group = kTileGroup * tiles_n;
-    const int first_m = (lin / in_group) * kTileGroup;
-    const int gsize = min(tiles_m - first_m, kTileGroup);
-    const int tm = first_m + (lin % in_group) % gsize;
-    const int tn = (lin % in_group) / gsize;
-    const int row0 = tm * BM, col0 = tn * BN;
-    if ((d.flags & kCUpperTiles) && row0 > col0 + BN - 1) return;
-
-    const unsigned fl = d.flags;
-    int kb = 0, ke = d.k;
-    if (fl & kAUpper) kb = max(kb, row0);
-    if (fl & kBLower) kb = max(kb, col0);
-    if (fl & kALower) ke = min(ke, row0 + BM);
-    if (fl & kBUpper) ke = min(ke, col0 + BN);
-    const int nk = ke > kb ? (ke - kb + BK - 1) / BK : 0;
-    const int nbatch = d.reduce ? d.batch : 1;
-    const int bfirst = d.reduce ? 0 : blockIdx.y;
-    const int ntiles = nk * nbatch;
-    const bool split = d.splitk > 1;
-    const int z2 = split ? 0 : blockIdx.z;
-    const int t_begin = split ? (int)((long long)blockIdx.z * ntiles / d.splitk) : 0;
-    const int t_end = split ? (int)((long long)(blockIdx.z + 1) * ntiles / d.splitk) : ntiles;
-    const int nt = t_end - t_begin;
-
-    const int ob = d.reduce ? 0 : blockIdx.y;
-    double* __restrict__ C = d.C + (long long)ob * d.strideC + (long long)z2 * d.strideC2;
-    const double* Cin = d.Cin ? d.Cin + (long long)ob * d.strideCin + (long long)z2 * d.strideCin2 : nullptr;
-
-    double acc[8][8];
-    if (Cin != nullptr && d.beta != 0.0 && (!split || blockIdx.z == 0)) {
-        const double beta = d.beta;
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int gi = row0 + 32 * (i >> 1) + 2 * tx + (i & 1);
-                const int gj = col0 + 32 * (j >> 1) + 2 * ty + (j & 1);
-                const bool ok = gi < d.m && gj < d.n;
-                const double v = Cin[ok ? gi + (long long)gj * d.ldcin : 0];
-                acc[i][j] = ok ? beta * v : 0.0;
-            }
-    } else {
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-#pragma unroll
-            for (int j = 0; j < 8; ++j) acc[i][j] = 0.0;
-    }
-
-    // Staging.  A slice that lies inside the matrices and off the diagonal
-    // of a triangular operand (the common case) loads without masks from
-    // per-thread offsets fixed for the whole k-loop, so the vector units
-    // spend their cycles on FMAs; edge and diagonal slices take the masked
-    // path.  Both decisions are uniform over the workgroup.
-    double ra[APT], rb[BPT];
-    unsigned amask = 0, bmask = 0;
-    double al_cur = 1;
-    bool fast_cur = false;
-    // Thread tid stages elements e = tid + 256 s: their offsets differ by a
-    // uniform step in s (2 k-rows or 32 rows/columns of the tile).
-    const long long ka = TA ? 1 : d.lda, kbs = TB ? d.ldb : 1;   // offset step per k
-    const long long offa0 = TA ? (long long)(row0 + tid / BK) * d.lda + tid % BK
-                               : (row0 + tid % BM) + (long long)(tid / BM) * d.lda;
-    const long long offb0 = TB ? (col0 + tid % BN) + (long long)(tid / BN) * d.ldb
-                               : (long long)(col0 + tid / BK) * d.ldb + tid % BK;
-    const long long sa = TA ? (256 / BK) * d.lda : (256 / BM) * d.lda;
-    const long long sb = TB ? (256 / BN) * d.ldb : (256 / BK) * d.ldb;
-    const bool rows_in = row0 + BM <= d.m, cols_in = col0 + BN <= d.n;
-    auto gload = [&](int t) {
-        const int bi = t / nk;
-        const int k0 = kb + (t - bi * nk) * BK;
-        const int b = bfirst + bi;
-        const double* __restrict__ A = d.A + (long long)b * d.strideA + (long long)z2 * d.strideA2;
-        const double* __restrict__ B = d.B + (long long)b * d.strideB + (long long)z2 * d.strideB2;
-        al_cur = d.alpha * (d.nalpha > 0 ? d.alphas[b] : 1.0);
-        bool fast = rows_in && cols_in && k0 + BK <= ke;
-        if (fl & kAUpper) fast = fast && k0 >= row0 + BM - 1;
-        if (fl & kALower) fast = fast && k0 + BK - 1 <= row0;
-        if (fl & kBUpper) fast = fast && k0 + BK - 1 <= col0;
-        if (fl & kBLower) fast = fast && k0 >= col0 + BN - 1;
-        fast_cur = fast;
-        if (fast) {
-            const double* __restrict__ Ak = A + (long long)k0 * ka + offa0;
-            const double* __restrict__ Bk = B + (long long)k0 * kbs + offb0;
-#pragma unroll
-            for (int s = 0; s < APT; ++s) ra[s] = Ak[s * sa];
-#pragma unroll
-            for (int s = 0; s < BPT; ++s) rb[s] = Bk[s * sb];
-            return;
-        }
-        amask = 0;
-        bmask = 0;
-#pragma unroll
-        for (int s = 0; s < APT; ++s) {
-            const int e = tid + 256 * s;
-            const int i = TA ? e / BK : e % BM;
-            const int kk = TA ? e % BK : e / BM;
-            const int gi = row0 + i, gk = k0 + kk;
-            bool ok = gi < d.m && gk < ke;
-            if (fl & kAUpper) ok = ok && gk >= gi;
-            if (fl & kALower) ok = ok && gk <= gi;
-            const long long off = TA ? gk + (long long)gi * d.lda : gi + (long long)gk * d.lda;
-            ra[s] = A[ok ? off : 0];
-            amask |= ok ? (1u << s) : 0u;
-        }
-#pragma unroll
-        for (int s = 0; s < BPT; ++s) {
-            const int e = tid + 256 * s;
-            const int j = TB ? e % BN : e / BK;
-            const int kk = TB ? e / BN : e % BK;
-            const int gj = col0 + j, gk = k0 + kk;
-            bool ok = gj < d.n && gk < ke;
-            if (fl & kBUpper) ok = ok && gk <= gj;
-            if (fl & kBLower) ok = ok && gk >= gj;
-            const long long off = TB ? gj + (long long)gk * d.ldb : gk + (long long)gj * d.ldb;
-            rb[s] = B[ok ? off : 0];
-            bmask |= ok ? (1u << s) : 0u;
-        }
-    };
-    auto lstore = [&](int buf) {
-        if (fast_cur) {
-#pragma unroll
-            for (int s = 0; s < APT; ++s) {
-                const int e = tid + 256 * s;
-                As[buf][TA ? e % BK : e / BM][TA ? e / BK : e % BM] = ra[s] * al_cur;
-            }
-#pragma unroll
-            for (int s = 0; s < BPT; ++s) {
-                const int e = tid + 256 * s;
-                Bs[buf][TB ? e / BN : e % BK][TB ? e % BN : e / BK] = rb[s];
-            }
-            return;
-        }
-#pragma unroll
-        for (int s = 0; s < APT; ++s) {
-            const int e = tid + 256 * s;
-            const int i = TA ? e / BK : e % BM;
-            const int kk = TA ? e % BK : e / BM;
-            As[buf][kk][i] = (amask >> s) & 1u ? ra[s] * al_cur : 0.0;
-        }
-#pragma unroll
-        for (int s = 0; s < BPT; ++s) {
-            const int e = tid + 256 * s;
-            const int j = TB ? e % BN : e / BK;
-            const int kk = TB ? e / BN : e % BK;
-            Bs[buf][kk][j] = (bmask >> s) & 1u ? rb[s] : 0.0;
-        }
-    };
-
-    if (nt > 0) {
-        gload(t_begin);
-        lstore(0);
-        __syncthreads();
-        if (nt > 1) gload(t_begin + 1);
-        for (int u = 0; u < nt; ++u) {
-            const int cur = u & 1;
-            // Operands of step k+1 are read into the other register set
-            // while the FMAs of step k run (the loop is kept rolled so that
-            // only two sets are live).
-            const double* Ak = &As[cur][0][2 * tx];
-            const double* Bk = &Bs[cur][0][2 * ty];
-            dpair a0[4], b0[4], a1[4], b1[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                a0[q] = *reinterpret_cast<const dpair*>(Ak + 32 * q);
-                b0[q] = *reinterpret_cast<const dpair*>(Bk + 32 * q);
-            }
-#pragma unroll 1
-            for (int k = 0; k < BK; k += 2) {
-                const int k1 = (k + 1) * (BM + kPad), k2 = ((k + 2) % BK) * (BM + kPad);
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    a1[q] = *reinterpret_cast<const dpair*>(Ak + k1 + 32 * q);
-                    b1[q] = *reinterpret_cast<const dpair*>(Bk + k1 + 32 * q);
-                }
-                fma_8x8(acc, a0, b0);
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    a0[q] = *reinterpret_cast<const dpair*>(Ak + k2 + 32 * q);
-                    b0[q] = *reinterpret_cast<const dpair*>(Bk + k2 + 32 * q);
-                }
-                fma_8x8(acc, a1, b1);
-            }
-            if (u + 1 < nt) {
-                lstore(cur ^ 1);
-                __syncthreads();
-                if (u + 2 < nt) gload(t_begin + u + 2);
-            }
-        }
-    }
-
-    if (split) {
-        const int nout = d.reduce ? 1 : d.batch;
-        double* __restrict__ Wp = d.work + ((long long)blockIdx.z * nout + ob) * ((long long)d.m * d.n);
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int gi = row0 + 32 * (i >> 1) + 2 * tx + (i & 1);
-                const int gj = col0 + 32 * (j >> 1) + 2 * ty + (j & 1);
-                if (gi < d.m && gj < d.n) Wp[gi + (long long)gj * d.m] = acc[i][j];
-            }
-        return;
-    }
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int gi = row0 + 32 * (i >> 1) + 2 * tx + (i & 1);
-            const int gj = col0 + 32 * (j >> 1) + 2 * ty + (j & 1);
-            bool ok = gi < d.m && gj < d.n;
-            if (fl & kCStoreUpper) ok = ok && gi <= gj;
-            if (fl & kCStoreLower) ok = ok && gi >= gj;
-            if (ok) C[gi + (long long)gj * d.ldc] = acc[i][j];
-        }
-}
-
-hipError_t launch_valu(const GemmDescT<double>& desc, hipStream_t s) {
-    GemmDescT<double> d = desc;
-    d.prescaled = 1;
-    const int gx = balance_xcds<double, 128, 128>(d, (d.m + 127) / 128, (d.n + 127) / 128);
-    dim3 grid(gx, d.reduce ? 1 : d.batch, d.splitk > 1 ? d.splitk : d.batch2);
-    char name[64];
-    if (stats_on()) {
-        snprintf(name, sizeof(name), "dgemm_valu<128,128,%c,%c>", d.transa ? 'T' : 'N', d.transb ? 'T' : 'N');
-    } else {
-        name[0] = 0;
-    }
-    StatScope sc(name, s, gemm_flops(d), gemm_bytes(d));
-    const int which = (d.transa ? 2 : 0) + (d.transb ? 1 : 0);
-    if (which == 0) dgemm_valu_kernel<false, false><<<grid, 256, 0, s>>>(d);
-    else if (which == 1) dgemm_valu_kernel<false, true><<<grid, 256, 0, s>>>(d);
-    else if (which == 2) dgemm_valu_kernel<true, false><<<grid, 256, 0, s>>>(d);
-    else dgemm_valu_kernel<true, true><<<grid, 256, 0, s>>>(d);
-    if (d.splitk > 1) {
-        const long long total = (long long)d.m * d.n * (d.reduce ? 1 : d.batch);
-        long long g = (total + 255) / 256;
-        if (g > 2048) g = 2048;
-        splitk_reduce_kernel<double><<<(int)g, 256, 0, s>>>(d);
-    }
-    sc.end();
-    return hipGetLastError();
-}
+typedef double dpair_u __attribute__((ext_vector_type(2), aligned(8)));   // a pair at any element
 
 // ---------------------------------------------------------------------------
 // Pipelined FP64 MFMA GEMM.  Each k-slice (BK = 16) of both operands is
@@ -815,12 +528,12 @@ __global__ __launch_bounds__(256, 2) void dgemm_pipe_kernel(GemmDescT<double> d)
 
     // Each lane loads 16-byte chunks (two elements adjacent in memory) of
     // the slice into registers and later stores them to its slots of the
-    // LDS layout.  The dispatcher only sends launches whose chunks are all
-    // 16-byte aligned and never straddle an edge of op(A) or op(B) (even
-    // extents along pairs, even leading dimensions and strides), so every
-    // slice issues the same loads from in-bounds addresses: rows of op(A)
-    // past m (columns of op(B) past n) are clamped to the last pair (they
-    // only reach outputs that are never stored), a ragged last slice is
+    // LDS layout.  A chunk needs no alignment beyond its elements' (a 16-byte
+    // global load may start at any multiple of 4 bytes), so odd leading
+    // dimensions, offsets and strides take the same loads.  Every slice issues
+    // the same loads from in-bounds addresses: rows of op(A) past m (columns of
+    // op(B) past n) are clamped to the last pair (they only reach outputs that
+    // are never stored; see fix_a for an odd edge), a ragged last slice is
     // shifted back to end at ke (below), and elements outside the slice's
     // k-range or the triangle of a triangular operand are set to zero in
     // registers before the store.
@@ -852,13 +565,12 @@ __global__ __launch_bounds__(256, 2) void dgemm_pipe_kernel(GemmDescT<double> d)
     if (fl & kALower) kfull_hi = min(kfull_hi, row0 + 1);
     if (fl & kBUpper) kfull_hi = min(kfull_hi, col0 + 1);
 
-    // Odd k with an operand contiguous along k: the pairs of the ragged last
-    // slice would straddle the end of k, so that slice is taken after the
-    // loop with element-wise loads (the dispatcher sends such products only
-    // in launches that do not sum over the batch, so the ragged slice ends
-    // the sequence of the workgroup that has it).
-    const bool peel = (TA || !TB) && (ke & 1) && t_end == ntiles;
-    const int t_main = peel ? t_end - 1 : t_end;   // end of the pipelined slices
+    // An odd extent along the pairs (rows of A as is, columns of B transposed):
+    // the last row or column would start a pair that reaches past the edge; its
+    // chunk loads the pair before and takes the second value of it.
+    const bool fix_a = !TA && (d.m & 1) && row0 + BM > d.m;
+    const bool fix_b = TB && (d.n & 1) && col0 + BN > d.n;
+    if (fix_a || fix_b) kfull_lo = ke;   // every slice takes the rare path of the store below
 
     // Load slice t of the (batch, k) sequence into registers.  A ragged
     // last slice loads the last BK values of k instead (ke >= BK here), the
@@ -868,18 +580,18 @@ __global__ __launch_bounds__(256, 2) void dgemm_pipe_kernel(GemmDescT<double> d)
     // issues the same loads, and the compiler's wait counts let the newer
     // register set stay in flight while the older one is stored.
     auto gload = [&](int t, dpair (&ra)[KA], dpair (&rb)[KB]) __attribute__((always_inline)) {
-        t = min(t, t_main - 1);
+        t = min(t, t_end - 1);
         const int bi = t / nk;
         const int k0 = min(kb + (t - bi * nk) * BK, ke - BK);
         const int b = bfirst + bi;
         const double* __restrict__ Ak = d.A + (long long)b * d.strideA + (long long)z2 * d.strideA2 + (long long)k0 * ka;
         const double* __restrict__ Bk = d.B + (long long)b * d.strideB + (long long)z2 * d.strideB2 + (long long)k0 * kbs;
 #pragma unroll
-        for (int q = 0; q < KA; ++q) ra[q] = *reinterpret_cast<const dpair*>(Ak + dA[q]);
+        for (int q = 0; q < KA; ++q) ra[q] = *reinterpret_cast<const dpair_u*>(Ak + dA[q]);
 #pragma unroll
-        for (int q = 0; q < KB; ++q) rb[q] = *reinterpret_cast<const dpair*>(Bk + dB[q]);
+        for (int q = 0; q < KB; ++q) rb[q] = *reinterpret_cast<const dpair_u*>(Bk + dB[q]);
     };
-    // Zero the elements of slice t that lie outside [kq, ke) (kq: the
+    // Mend the pairs of an odd edge and zero the elements of slice t that lie outside [kq, ke) (kq: the
     // slice's first k; below it only for a shifted ragged slice) or outside
     // the triangle of a triangular operand (rare: the ragged last slice and
     // the diagonal blocks), then store the slice to an LDS stage.
@@ -887,6 +599,22 @@ __global__ __launch_bounds__(256, 2) void dgemm_pipe_kernel(GemmDescT<double> d)
         const int kq = kb + (t % nk) * BK;
         const int k0 = min(kq, ke - BK);
         if (kq < kfull_lo || kq + BK > kfull_hi) {
+            if (fix_a) {
+#pragma unroll
+                for (int q = 0; q < KA; ++q) {
+                    int r, kk;
+                    LA::coords((wv * KA + q) * 64 + lane, r, kk);
+                    ra[q][0] = row0 + r == d.m - 1 ? ra[q][1] : ra[q][0];
+                }
+            }
+            if (fix_b) {
+#pragma unroll
+                for (int q = 0; q < KB; ++q) {
+                    int r, kk;
+                    LB::coords((wv * KB + q) * 64 + lane, r, kk);
+                    rb[q][0] = col0 + r == d.n - 1 ? rb[q][1] : rb[q][0];
+                }
+            }
 #pragma unroll
             for (int q = 0; q < KA; ++q)
 #pragma unroll
@@ -1000,58 +728,7 @@ __global__ __launch_bounds__(256, 2) void dgemm_pipe_kernel(GemmDescT<double> d)
         }
         if (u < nt) compute_k(sA0, sB0, t_begin + u, scale_);
     };
-    // The peeled slice: element-wise loads, zero outside [k0, ke) and the
-    // triangle of a triangular operand, stored straight to LDS stage 0.
-    auto peel_store = [&](int t) __attribute__((always_inline)) {
-        const int bi = t / nk;
-        const int k0 = kb + (t - bi * nk) * BK;
-        const int b = bfirst + bi;
-        const double* __restrict__ A = d.A + (long long)b * d.strideA + (long long)z2 * d.strideA2;
-        const double* __restrict__ B = d.B + (long long)b * d.strideB + (long long)z2 * d.strideB2;
-#pragma unroll 1
-        for (int q = 0; q < KA; ++q) {
-            int r, kk;
-            LA::coords((wv * KA + q) * 64 + lane, r, kk);
-            double v[2];
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int gi = row0 + r + (TA ? 0 : h), gk = k0 + kk + (TA ? h : 0);
-                bool ok = gi < d.m && gk < ke;
-                if (fl & kAUpper) ok = ok && gk >= gi;
-                if (fl & kALower) ok = ok && gk <= gi;
-                const long long off = TA ? gk + (long long)gi * d.lda : gi + (long long)gk * d.lda;
-                const double x = A[ok ? off : 0];
-                v[h] = ok ? x : 0.0;
-            }
-            *reinterpret_cast<dpair*>(sA0 + 2 * ((wv * KA + q) * 64 + lane)) = dpair{v[0], v[1]};
-        }
-#pragma unroll 1
-        for (int q = 0; q < KB; ++q) {
-            int r, kk;
-            LB::coords((wv * KB + q) * 64 + lane, r, kk);
-            double v[2];
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int gj = col0 + r + (TB ? h : 0), gk = k0 + kk + (TB ? 0 : h);
-                bool ok = gj < d.n && gk < ke;
-                if (fl & kBUpper) ok = ok && gk <= gj;
-                if (fl & kBLower) ok = ok && gk >= gj;
-                const long long off = TB ? gj + (long long)gk * d.ldb : gk + (long long)gj * d.ldb;
-                const double x = B[ok ? off : 0];
-                v[h] = ok ? x : 0.0;
-            }
-            *reinterpret_cast<dpair*>(sB0 + 2 * ((wv * KB + q) * 64 + lane)) = dpair{v[0], v[1]};
-        }
-    };
-    auto kloop = [&](auto scale_) __attribute__((always_inline)) {
-        kloop_main(scale_, t_main - t_begin);
-        if (peel) {
-            barrier();   // every wave is past its reads of stage 0
-            peel_store(t_main);
-            barrier();
-            compute_k(sA0, sB0, t_main, scale_);
-        }
-    };
+    auto kloop = [&](auto scale_) __attribute__((always_inline)) { kloop_main(scale_, t_end - t_begin); };
     if (d.nalpha > 0) kloop(std::true_type{});
     else kloop(std::false_type{});
 
@@ -1279,50 +956,27 @@ hipError_t dispatch_pipe_tuned(const GemmDescT<double>& d, int static_choice, hi
     return launch_pipe_cand(static_choice, d, s);
 }
 
-// Kernel and tile shape for a descriptor: 0/1 = MFMA gemm_kernel with
-// 64 x 64 / 64 x 128 tiles, 4 = dgemm_valu_kernel (128 x 128),
-// 5/6 = dgemm_pipe_kernel with 64 x 128 / 64 x 64 tiles.  Measured on gfx950
-// (FP64, TFLOP/s; gemm_kernel / vector / the pipelined kernel's earlier form
-// with direct global -> LDS copies):
-//   8192^3 N,N                          39.7 / 46.0 / 56.9
-//   8192^3 T,N upper tiles (Gram)       37.3 / 35.3 / 52.9
-//   8192^3 x 8 N,T batch-reduced        38.5 / 43.3 / 51.2
-//   128 x 8064 x 8320 x 8 T,N, split 4  18.6 / 18.2 / 25.6
-//   4096^3 x 8 N,N triangular A         35.6 / 35.7 / 46.7
-//   8320 x 8064 x 128 x 8 N,N (k=128)   14.2 / 16.0 / 15.9
-//   7936^2 x 64 x 8 T,N upper (k=64)    18.6 / 20.8 / 18.9
-//   8320 x 7936 x 256 x 8 N,N (k=256)   30.5 / 36.2 / 37.9 (64 x 64 tiles: 40.5)
-// (counting the nonzeros of trapezoidal operands).  The pipelined kernel as
-// it stands: 8192^3 N,N 68.3, T,N 68.5, N,T 63.5; 256 x 8192 x 8256 x 8 T,N
-// 65.1; 8256 x 8192 x 256 x 8 N,N with C read 50.1.  Up to k = 256 it runs
-// 64 x 64 tiles, three workgroups per CU, with Cin loaded before the k-loop;
-// beyond, 64 x 128 tiles.  128 x 128 tiles (one workgroup per CU) were
-// slower in both the earlier and the current form.  64-row MFMA tiles of
-// gemm_kernel run two workgroups per CU and beat its 128 x 128 tiles on
-// every shape (35 against 40 at 8192^3).
+// Kernel and tile shape for a descriptor: 0/1 = gemm_kernel with 64 x 64 /
+// 64 x 128 tiles, 5/6 = dgemm_pipe_kernel with 64 x 128 / 64 x 64 tiles.
+// FP64 runs the pipelined kernel wherever it has one whole slice along k and one
+// pair along an operand's contiguous rows or columns.  Measured on gfx950
+// (TFLOP/s): 8192^3 N,N 68.3, T,N 68.5, N,T 63.5 (gemm_kernel 39.7); 256 x 8192 x
+// 8256 x 8 T,N 65.1; 8256 x 8192 x 256 x 8 N,N with C read 50.1.  Odd extents,
+// leading dimensions and offsets, which gemm_kernel used to take: a 3001 x 1501
+// solve by Cholesky-type steps 9.4 -> 6.8 ms, 1000 x 777 estimated 15.2 -> 12.7.
+// Up to k = 128 gemm_kernel, or a vector-FMA kernel with 128 x 128 tiles from 512
+// of them on, used to run: 256 x 128 1.01 -> 0.95 ms, n = 2048 27.0 -> 26.4, 8192
+// r = 8 651 -> 648 (the vector kernel's products alone within 0.2 %).  Up to
+// k = 256 64 x 64 tiles, three workgroups per CU, with Cin loaded before the
+// k-loop; beyond, 64 x 128 tiles.  128 x 128 tiles (one workgroup per CU) were
+// slower.  gemm_kernel: FP32, k < 16 and single rows or columns.
 template <class T>
 int pick_tile(const GemmDescT<T>& d) {
     const long long nb = (long long)(d.reduce ? 1 : d.batch) * d.batch2;
     const long long t1 = (long long)((d.m + 63) / 64) * ((d.n + 127) / 128) * nb;
     if constexpr (sizeof(T) == 8) {
-        if (d.k <= 128) {
-            if (d.m >= 256 && d.n >= 256) {
-                const long long t128 = (long long)((d.m + 127) / 128) * ((d.n + 127) / 128) * nb;
-                if (t128 >= 512) return 4;
-            }
-            return 0;
-        }
-        // dgemm_pipe_kernel loads 16-byte pairs: they must be aligned and
-        // must not straddle an edge of op(A) or op(B); with odd k and an
-        // operand contiguous along k it takes the ragged last slice apart,
-        // which only works when that slice ends the sequence (no sum over
-        // the batch).
-        const bool even_edges = (d.transa || (d.m & 1) == 0) && (!d.transb || (d.n & 1) == 0) &&
-                                ((!d.transa && d.transb) || (d.k & 1) == 0 || !(d.reduce && d.batch > 1));
-        const bool even_ld = (d.lda & 1) == 0 && (d.ldb & 1) == 0;
-        const bool aligned = ((reinterpret_cast<uintptr_t>(d.A) | reinterpret_cast<uintptr_t>(d.B)) & 15) == 0 &&
-                             ((d.strideA | d.strideB | d.strideA2 | d.strideB2) & 1) == 0;
-        if (even_edges && even_ld && aligned) return (d.k > 256 && d.m >= 128 && d.n >= 128 && t1 >= 256) ? 5 : 6;
+        if (d.k >= kBK && (d.transa || d.m >= 2) && (!d.transb || d.n >= 2))
+            return (d.k > 256 && d.m >= 128 && d.n >= 128 && t1 >= 256) ? 5 : 6;
     }
     if (d.k <= 128) return 0;
     if (d.m >= 128 && d.n >= 128 && t1 >= 256) return 1;
@@ -1330,8 +984,8 @@ int pick_tile(const GemmDescT<T>& d) {
 }
 
 inline void tile_dims(int t, int& bm, int& bn) {
-    bm = t == 4 ? 128 : 64;
-    bn = (t == 1 || t == 4 || t == 5) ? 128 : 64;
+    bm = 64;
+    bn = (t == 1 || t == 5) ? 128 : 64;
 }
 
 template <class T>
@@ -1342,16 +996,10 @@ hipError_t gemm_dispatch(const GemmDescT<T>& d, hipStream_t s) {
     if (d.splitk > 1 && (d.batch2 != 1 || d.work == nullptr)) return hipErrorInvalidValue;
     const int t = pick_tile(d);
     if constexpr (sizeof(T) == 8) {
-        if (t == 4) return launch_valu(d, s);
         if (t == 5) return dispatch_pipe_tuned(d, 0, s);
         if (t == 6) return dispatch_pipe_tuned(d, 1, s);
     }
-    switch (t) {
-        case 0: return launch_bm_bn<T, 64, 64>(d, s);
-        case 1: return launch_bm_bn<T, 64, 128>(d, s);
-        case 2: return launch_bm_bn<T, 128, 64>(d, s);
-        default: return launch_bm_bn<T, 128, 128>(d, s);
-    }
+    return t == 1 ? launch_bm_bn<T, 64, 128>(d, s) : launch_bm_bn<T, 64, 64>(d, s);
 }
 
 }  // namespace

@@ -150,3 +150,46 @@ def test_cholesky_scaled(z):
     for e in (-996, -400, 400, 980):
         R = z.potrf(torch.from_numpy(np.ldexp(Z, e)[None]).to("cuda"))[0].cpu().numpy()[0]
         assert np.abs(R - np.ldexp(R0, e // 2)).max() <= 1e-14 * np.ldexp(np.abs(R0).max(), e // 2)
+
+
+# Every orientation of the pipelined FP64 product at odd extents and at its
+# smallest sizes, and the products that stay with the register-staged kernel
+# (k < 16, single rows or columns).  Whole numbers: the results are exact.
+@pytest.mark.parametrize("m,n,k", [(2, 2, 16), (1, 7, 40), (7, 1, 40), (3, 5, 15), (3, 2, 17), (65, 63, 33),
+                                   (64, 64, 64), (129, 131, 100), (191, 65, 129), (63, 257, 257), (130, 258, 1001),
+                                   (515, 517, 70), (1031, 1029, 300)])
+@pytest.mark.parametrize("ta", [False, True])
+@pytest.mark.parametrize("tb", [False, True])
+def test_products_of_whole_numbers(z, m, n, k, ta, tb):
+    import torch
+    rng = np.random.default_rng(m * n + k)
+    A = rng.integers(-9, 10, (2, k, m) if ta else (2, m, k)).astype(np.float64)
+    B = rng.integers(-9, 10, (2, n, k) if tb else (2, k, n)).astype(np.float64)
+    C = rng.integers(-9, 10, (2, m, n)).astype(np.float64)
+    got = z.gemm(torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda(), torch.from_numpy(C).cuda(), transa=ta,
+                 transb=tb, alpha=2.0, beta=-3.0).cpu().numpy()
+    opa = np.transpose(A, (0, 2, 1)) if ta else A
+    opb = np.transpose(B, (0, 2, 1)) if tb else B
+    assert np.array_equal(got, 2.0 * (opa @ opb) - 3.0 * C)
+
+
+@pytest.mark.parametrize("off,lda,ldb,ldc", [(0, 131, 133, 135), (1, 132, 134, 136), (1, 131, 134, 137)])
+def test_products_at_odd_offsets(z, off, lda, ldb, ldc):
+    # Raw calls: operands that start and step at odd elements.
+    import ctypes
+    import torch
+    rng = np.random.default_rng(off + lda)
+    m, n, k, batch = 130, 97, 131, 2
+    buf = {c: rng.integers(-9, 10, off + batch * ld * 140 + 1).astype(np.float64) for c, ld in
+           (("A", lda), ("B", ldb), ("C", ldc))}
+    dv = {c: torch.from_numpy(x).cuda() for c, x in buf.items()}
+    ptr = {c: ctypes.c_void_p(t.data_ptr() + 8 * off) for c, t in dv.items()}
+    rc = z.lib.zolo_dgemm(z.h, 1, 0, m, n, k, 1.0, ptr["A"], lda, lda * 131 + 1, ptr["B"], ldb, ldb * 97 + 1, 1.0,
+                          ptr["C"], ldc, ldc * 97 + 2, batch)
+    assert rc == 0
+    for b in range(batch):
+        a = buf["A"][off + b * (lda * 131 + 1):][:lda * m].reshape(m, lda)[:, :k]
+        x = buf["B"][off + b * (ldb * 97 + 1):][:ldb * n].reshape(n, ldb)[:, :k].T
+        c = buf["C"][off + b * (ldc * 97 + 2):][:ldc * n].reshape(n, ldc)[:, :m].T
+        got = dv["C"].cpu().numpy()[off + b * (ldc * 97 + 2):][:ldc * n].reshape(n, ldc)[:, :m].T
+        assert np.array_equal(got, a @ x + c)
