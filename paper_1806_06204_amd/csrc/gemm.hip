@@ -1014,10 +1014,15 @@ hipError_t gemm(const SGemmDesc& d, hipStream_t s) { return gemm_dispatch(d, s);
 // (2 per CU) partly empty, up to 1.6x the balanced time; four pieces are the
 // fastest or within 3% of it across the whole range (more pieces add the
 // partial-sum traffic, fewer leave the rounds uneven).  Below 256 tiles the
-// pieces are raised to about 1024 workgroups in all.
+// pieces are raised to about 1024 workgroups in all, of at least 512 of k each.
+// Products of a handful of tiles (the updates inside a superblock) would still
+// leave most of the chip idle: below 256 workgroups the pieces are cut down to
+// 128 of k, for about 512 workgroups.  One piece of 512 takes 31 us, of 128 11 us,
+// and the sum 5-6 us: structured QR 1025 x 881 x 5 6.2 -> 5.7 ms, 1000 x 777 solve
+// 12.7 -> 11.8, n = 2048 26.4 -> 25.5.
 hipError_t gemm_split(GemmDesc d, double* work, size_t work_elems, hipStream_t s) {
     d.splitk = 1;
-    if (work != nullptr && d.batch2 == 1 && d.k >= 1024 && d.m > 0 && d.n > 0 && d.batch > 0 &&
+    if (work != nullptr && d.batch2 == 1 && d.k >= 512 && d.m > 0 && d.n > 0 && d.batch > 0 &&
         !(d.flags & kCUpperTiles)) {
         int bm, bn;
         tile_dims(pick_tile(d), bm, bn);
@@ -1026,6 +1031,7 @@ hipError_t gemm_split(GemmDesc d, double* work, size_t work_elems, hipStream_t s
             long long sk = std::max(4LL, (1024 + tiles - 1) / tiles);
             sk = std::min(sk, (long long)d.k / 512);             // at least 512 of k per piece
             sk = std::min(sk, 32LL);
+            if (tiles * sk < 256) sk = std::max(sk, std::min({32LL, (long long)d.k / 128, (512 + tiles - 1) / tiles}));
             const long long per = (long long)d.m * d.n * (d.reduce ? 1 : d.batch);
             if (sk * per > (long long)work_elems) sk = (long long)work_elems / per;
             if (sk > 1) {
