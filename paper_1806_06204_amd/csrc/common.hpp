@@ -59,6 +59,7 @@ struct GemmDescT {
     // second kernel sums them in order into C.
     int splitk = 1;
     T* work = nullptr;
+    int keep_pieces = 0;     // leave the pieces in `work` (the caller sums them)
     // Set by the launcher when the work per tile is uneven (triangular
     // operands, upper-tile outputs): XCD x takes the tiles [xsplit[x],
     // xsplit[x+1]) of the launch order, ranges cut to equal estimated work.
@@ -73,7 +74,9 @@ hipError_t gemm(const GemmDesc& d, hipStream_t stream);
 hipError_t gemm(const SGemmDesc& d, hipStream_t stream);
 // As gemm(), but a product whose output has too few tiles to fill the chip
 // and a long k-range is split along k into `work` (up to work_elems doubles).
-hipError_t gemm_split(GemmDesc d, double* work, size_t work_elems, hipStream_t stream);
+// With `pieces`, the pieces are left unsummed in `work` and *pieces says how
+// many there are (1: the product is in C as usual).
+hipError_t gemm_split(GemmDesc d, double* work, size_t work_elems, hipStream_t stream, int* pieces = nullptr);
 
 // Nonzeros of a trapezoidal operand with `r` rows (the side that is not k)
 // and depth k: "from diagonal" = zero where k < r-index (upper op(A), lower

@@ -385,7 +385,7 @@ hipError_t launch_bm_bn(const GemmDescT<T>& desc, hipStream_t s) {
     else if (which == 1) gemm_kernel<T, BM, BN, false, true><<<grid, 256, 0, s>>>(d);
     else if (which == 2) gemm_kernel<T, BM, BN, true, false><<<grid, 256, 0, s>>>(d);
     else gemm_kernel<T, BM, BN, true, true><<<grid, 256, 0, s>>>(d);
-    if (d.splitk > 1) {
+    if (d.splitk > 1 && !d.keep_pieces) {
         const long long total = (long long)d.m * d.n * (d.reduce ? 1 : d.batch);
         long long g = (total + 255) / 256;
         if (g > 2048) g = 2048;
@@ -813,7 +813,7 @@ hipError_t launch_pipe(const GemmDescT<double>& desc, hipStream_t s) {
             }
             break;
     }
-    if (d.splitk > 1) {
+    if (d.splitk > 1 && !d.keep_pieces) {
         const long long total = (long long)d.m * d.n * (d.reduce ? 1 : d.batch);
         long long g = (total + 255) / 256;
         if (g > 2048) g = 2048;
@@ -1020,8 +1020,9 @@ hipError_t gemm(const SGemmDesc& d, hipStream_t s) { return gemm_dispatch(d, s);
 // 128 of k, for about 512 workgroups.  One piece of 512 takes 31 us, of 128 11 us,
 // and the sum 5-6 us: structured QR 1025 x 881 x 5 6.2 -> 5.7 ms, 1000 x 777 solve
 // 12.7 -> 11.8, n = 2048 26.4 -> 25.5.
-hipError_t gemm_split(GemmDesc d, double* work, size_t work_elems, hipStream_t s) {
+hipError_t gemm_split(GemmDesc d, double* work, size_t work_elems, hipStream_t s, int* pieces) {
     d.splitk = 1;
+    d.keep_pieces = pieces != nullptr;
     if (work != nullptr && d.batch2 == 1 && d.k >= 512 && d.m > 0 && d.n > 0 && d.batch > 0 &&
         !(d.flags & kCUpperTiles)) {
         int bm, bn;
@@ -1040,6 +1041,7 @@ hipError_t gemm_split(GemmDesc d, double* work, size_t work_elems, hipStream_t s
             }
         }
     }
+    if (pieces) *pieces = d.splitk;
     return gemm_dispatch(d, s);
 }
 

@@ -1401,6 +1401,86 @@ hipError_t run_panel(int m, int e, int p, int nb, double* M, long long ld, long 
     return err;
 }
 
+// Reflectors and columns of C up to which wy_t_kernel takes W2: the updates
+// inside a superblock (7-14 us against 16-20 in two launches).  With 256
+// reflectors the depth of the product takes it to 25 us.
+constexpr int kWyMaxRefl = 128, kWyMaxTrail = 256;
+
+// W2 = op(T) W of a block reflector for few columns: W given as `pieces`
+// partial products (sums over the split k-range, in order), T upper triangular
+// with stored zeros below its diagonal.  A workgroup sums 16 columns of W into
+// LDS and multiplies them on the matrix cores, a 16-row tile of the result per
+// wave at a time.  Lane l takes the k-values 4 (l / 16) + u, u = 0..3, of each
+// 16, so that T^T is read 32 contiguous bytes per lane.  Bound: launch and load
+// latency; it replaces the sum of the pieces and a product, two launches of 5.5
+// and 10-14 us, by one of 7-14.  With merge_wy_kernel: n = 2048 25.5 -> 24.7 ms,
+// 1000 x 777 11.8 -> 11.2, structured QR 1025 x 881 x 5 5.65 -> 5.3, 32 uneven
+// matrices 27.5 -> 25.9.
+constexpr int kWyCols = 16, kWyThreads = 512;
+__global__ __launch_bounds__(kWyThreads) void wy_t_kernel(int nbv, int trail, int transpose, const double* __restrict__ Tm,
+                                                   long long ldt, long long stt, const double* __restrict__ Wp,
+                                                   int pieces, long long ldw, long long sw, long long sz,
+                                                   double* __restrict__ W2, long long ldw2, long long sw2) {
+    __shared__ double s_w[kWyMaxRefl][kWyCols + 1];
+    const int b = blockIdx.y, c0 = blockIdx.x * kWyCols, tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4;
+    const int rows = (nbv + 15) / 16 * 16;
+    const double* Tb = Tm + b * stt;
+    const double* Wb = Wp + b * sw;
+    constexpr int UE = 4, UZ = 8;                 // elements and pieces whose loads are in flight together
+    for (int e0 = tid; e0 < rows * kWyCols; e0 += kWyThreads * UE) {
+        const double* p[UE];
+        double s[UE];
+#pragma unroll
+        for (int u = 0; u < UE; ++u) {
+            const int e = min(e0 + kWyThreads * u, rows * kWyCols - 1);
+            p[u] = Wb + min(e % rows, nbv - 1) + (long long)min(c0 + e / rows, trail - 1) * ldw;
+            s[u] = 0.0;
+        }
+        for (int z = 0; z < pieces; z += UZ) {
+            double v[UE][UZ];
+#pragma unroll
+            for (int u = 0; u < UE; ++u)
+#pragma unroll
+                for (int q = 0; q < UZ; ++q) v[u][q] = p[u][min(z + q, pieces - 1) * sz];
+#pragma unroll
+            for (int u = 0; u < UE; ++u)
+#pragma unroll
+                for (int q = 0; q < UZ; ++q) s[u] += keep_if(v[u][q], opaque(z + q < pieces ? -1 : 0));
+        }
+#pragma unroll
+        for (int u = 0; u < UE; ++u) {
+            const int e = e0 + kWyThreads * u;
+            if (e < rows * kWyCols) s_w[e % rows][e / rows] = keep_if(s[u], opaque(e % rows < nbv ? -1 : 0));
+        }
+    }
+    __syncthreads();
+    for (int rt = tid >> 6; rt * 16 < rows; rt += kWyThreads / 64) {
+        d4 acc = d4{0, 0, 0, 0};
+        const int i = 16 * rt + l16, ic = min(i, nbv - 1);
+        const int k0 = transpose ? 0 : 16 * rt, k1 = transpose ? 16 * rt + 16 : rows;   // T's nonzeros
+        for (int k = k0; k < k1; k += 64) {       // four blocks' loads in flight
+            double t[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) {
+                const int kc = min(k + 16 * (u >> 2) + 4 * lg + (u & 3), nbv - 1);
+                t[u] = transpose ? Tb[kc + ic * ldt] : Tb[ic + kc * ldt];
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (k + 16 * q < k1) {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        acc = mfma_f64_16x16x4(t[4 * q + u], s_w[k + 16 * q + 4 * lg + u][l16], acc);
+                }
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int r = 16 * rt + Mfma<double>::row(lane, e);
+            if (r < nbv && c0 + l16 < trail) W2[b * sw2 + r + (long long)(c0 + l16) * ldw2] = acc[e];
+        }
+    }
+}
+
 // Applies the block reflector I - V T V^T (forward: its transpose, as in the
 // factorisation; backward: itself, as in forming Q) of the nbv columns of V
 // starting at column c0 to `trail` columns C starting at column c0 + nbv, over
@@ -1421,15 +1501,26 @@ hipError_t apply_block(int L, int c0, int nbv, int trail, const double* Tm, long
     g1.B = C; g1.ldb = ld; g1.strideB = sm;
     g1.C = w.W; g1.ldc = kQrSuper; g1.strideC = sw;
     g1.batch = batch; g1.flags = kAUpper;
-    hipError_t err = gemm_split(g1, w.splitk, w.splitk_elems, st);
-    if (err != hipSuccess) return err;
-    GemmDesc g2;  // W2 = T^T W (forward) or T W (backward)
-    g2.m = nbv; g2.n = trail; g2.k = nbv; g2.transa = transpose_t ? 1 : 0;
-    g2.A = Tm; g2.lda = ldt; g2.strideA = stt;
-    g2.B = w.W; g2.ldb = kQrSuper; g2.strideB = sw;
-    g2.C = w.W2; g2.ldc = kQrSuper; g2.strideC = sw;
-    g2.batch = batch; g2.flags = transpose_t ? kALower : kAUpper;
-    if ((err = gemm(g2, st)) != hipSuccess) return err;
+    hipError_t err;
+    if (nbv <= kWyMaxRefl && trail <= kWyMaxTrail) {  // W2 = T^T W (forward) or T W (backward)
+        int pieces = 1;
+        if ((err = gemm_split(g1, w.splitk, w.splitk_elems, st, &pieces)) != hipSuccess) return err;
+        const long long per = (long long)nbv * trail;
+        const bool split = pieces > 1;
+        wy_t_kernel<<<dim3((trail + kWyCols - 1) / kWyCols, batch), kWyThreads, 0, st>>>(
+            nbv, trail, transpose_t ? 1 : 0, Tm, ldt, stt, split ? w.splitk : w.W, pieces, split ? nbv : kQrSuper,
+            split ? per : sw, per * batch, w.W2, kQrSuper, sw);
+        if ((err = hipGetLastError()) != hipSuccess) return err;
+    } else {
+        if ((err = gemm_split(g1, w.splitk, w.splitk_elems, st)) != hipSuccess) return err;
+        GemmDesc g2;
+        g2.m = nbv; g2.n = trail; g2.k = nbv; g2.transa = transpose_t ? 1 : 0;
+        g2.A = Tm; g2.lda = ldt; g2.strideA = stt;
+        g2.B = w.W; g2.ldb = kQrSuper; g2.strideB = sw;
+        g2.C = w.W2; g2.ldc = kQrSuper; g2.strideC = sw;
+        g2.batch = batch; g2.flags = transpose_t ? kALower : kAUpper;
+        if ((err = gemm(g2, st)) != hipSuccess) return err;
+    }
     GemmDesc g3;  // C -= V W2
     g3.m = L; g3.n = trail; g3.k = nbv;
     g3.A = V; g3.lda = ld; g3.strideA = sm;
@@ -1440,21 +1531,86 @@ hipError_t apply_block(int L, int c0, int nbv, int trail, const double* Tm, long
     return gemm(g3, st);
 }
 
-// To = [T1, -T1 (V1^T V2) T2; 0, T2]: the compact-WY factor of the product
-// of the block reflectors of columns [c1, c1 + n1) (factor T1) and
-// [c2, c2 + n2), c2 = c1 + n1 (factor T2).  The T12 block is written by the
-// GEMMs before this kernel; the rest is copied or zeroed here.
-__global__ void assemble_wy_kernel(int n1, int n2, const double* __restrict__ T1, long long ld1, long long st1,
-                                   const double* __restrict__ T2, long long ld2, long long st2,
-                                   double* __restrict__ To, long long ldo, long long sto) {
-    const int b = blockIdx.y, nt = n1 + n2;
-    for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < nt * nt; e += gridDim.x * blockDim.x) {
-        const int i = e % nt, j = e / nt;
-        if (i < n1 && j >= n1) continue;  // T12
-        double v = 0.0;
-        if (i < n1 && j < n1) v = T1[b * st1 + i + (long long)j * ld1];
-        else if (i >= n1 && j >= n1) v = T2[b * st2 + (i - n1) + (long long)(j - n1) * ld2];
-        To[b * sto + i + (long long)j * ldo] = v;
+// To = [T1, -T1 P T2; 0, T2], P = V1^T V2: the compact-WY factor of the product
+// of the block reflectors of columns [c1, c1 + n1) (factor T1) and [c2, c2 + n2),
+// c2 = c1 + n1 (factor T2); n1 a multiple of 16.  A workgroup takes 16 columns of
+// T2: Y = P T2 into LDS, then -T1 Y, on the matrix cores; the blocks copied and
+// zeroed are spread over the workgroups of a matrix.  Bound: launch and load
+// latency; it replaces two products and a copy, 26-30 us in three launches.
+constexpr int kMergeCols = 16, kMergeThreads = 512;
+__global__ __launch_bounds__(kMergeThreads) void merge_wy_kernel(int n1, int n2, const double* __restrict__ P,
+                                                                 long long ldp, long long sp,
+                                                                 const double* __restrict__ T1, long long ld1,
+                                                                 long long st1, const double* __restrict__ T2,
+                                                                 long long ld2, long long st2,
+                                                                 double* __restrict__ To, long long ldo,
+                                                                 long long sto) {
+    __shared__ double s_y[kQrBlock][kMergeCols + 1];
+    const int b = blockIdx.y, c0 = blockIdx.x * kMergeCols, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int l16 = lane & 15, lg = lane >> 4;
+    const double* Pb = P + b * sp;
+    const double* T1b = T1 + b * st1;
+    const double* T2b = T2 + b * st2;
+    double* Tob = To + b * sto;
+    constexpr int NW = kMergeThreads / 64;
+    // Four blocks of 16 along k have their loads in flight together; lane l
+    // takes the k-values 4 (l / 16) + u of each block.
+    for (int i0 = 16 * wave; i0 < n1; i0 += 16 * NW) {   // Y[:, c] = P T2[:, c], T2 zero below its diagonal
+        const int jc = min(c0 + l16, n2 - 1), kend = min(n2, c0 + kMergeCols);
+        d4 acc = d4{0, 0, 0, 0};
+        for (int k = 0; k < kend; k += 64) {
+            double x[16], y[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) {
+                const int kc = min(k + 16 * (u >> 2) + 4 * lg + (u & 3), n2 - 1);
+                x[u] = Pb[i0 + l16 + kc * ldp];
+                y[u] = T2b[kc + jc * ld2];
+            }
+#pragma unroll
+            for (int u = 0; u < 16; ++u) {
+                const int in = opaque(k + 16 * (u >> 2) + 4 * lg + (u & 3) < n2 ? -1 : 0);
+                acc = mfma_f64_16x16x4(keep_if(x[u], in), keep_if(y[u], in), acc);
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s_y[i0 + Mfma<double>::row(lane, e)][l16] = acc[e];
+    }
+    __syncthreads();
+    for (int i0 = 16 * wave; i0 < n1; i0 += 16 * NW) {   // T12 = -T1 Y, T1 upper triangular
+        d4 acc = d4{0, 0, 0, 0};
+        for (int k = i0; k < n1; k += 64) {
+            double x[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u)
+                x[u] = T1b[i0 + l16 + min(k + 16 * (u >> 2) + 4 * lg + (u & 3), n1 - 1) * ld1];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (k + 16 * q < n1) {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        acc = mfma_f64_16x16x4(-x[4 * q + u], s_y[k + 16 * q + 4 * lg + u][l16], acc);
+                }
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (c0 + l16 < n2) Tob[i0 + Mfma<double>::row(lane, e) + (n1 + c0 + l16) * ldo] = acc[e];
+    }
+    // The copied and the zero blocks.
+    const int nt = n1 + n2, stride = gridDim.x * kMergeThreads;
+    for (int e0 = blockIdx.x * kMergeThreads + tid; e0 < nt * nt; e0 += 8 * stride) {
+        double v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int e = min(e0 + u * stride, nt * nt - 1), i = e % nt, j = e / nt;
+            const double* src = j < n1 ? T1b + min(i, n1 - 1) + j * ld1 : T2b + max(i - n1, 0) + (j - n1) * ld2;
+            v[u] = *src;
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int e = e0 + u * stride, i = e % nt, j = e / nt;
+            if (e < nt * nt && (i >= n1 || j < n1))   // not T12
+                Tob[i + j * ldo] = keep_if(v[u], opaque(((i < n1) == (j < n1)) ? -1 : 0));
+        }
     }
 }
 
@@ -1465,7 +1621,6 @@ hipError_t merge_wy(int m, int e, int c1, int n1, const double* T1, long long ld
     const int k = live_rows(m, e, c1, n1) - n1;  // rows [c2, end of V1's live rows): V1 is zero below
     const long long ss = (long long)kQrBlock * kQrBlock;
     double* P = w.S;
-    double* Y = w.S + (long long)batch * ss;
     GemmDesc g;  // P = V1^T V2 (n1 x n2); V2's part above its diagonal (zeros, or R of an
                  // earlier panel of its block) is masked
     g.m = n1; g.n = n2; g.k = k; g.transa = 1;
@@ -1475,21 +1630,8 @@ hipError_t merge_wy(int m, int e, int c1, int n1, const double* T1, long long ld
     g.batch = batch; g.flags = kBLower;
     hipError_t err = gemm_split(g, w.splitk, w.splitk_elems, st);
     if (err != hipSuccess) return err;
-    GemmDesc y;  // Y = P T2 (T2 upper)
-    y.m = n1; y.n = n2; y.k = n2;
-    y.A = P; y.lda = kQrBlock; y.strideA = ss;
-    y.B = T2; y.ldb = ld2; y.strideB = st2;
-    y.C = Y; y.ldc = kQrBlock; y.strideC = ss;
-    y.batch = batch; y.flags = kBUpper;
-    if ((err = gemm(y, st)) != hipSuccess) return err;
-    GemmDesc t;  // T12 = -T1 Y (T1 upper) into To[0:n1, n1:n1+n2]
-    t.m = n1; t.n = n2; t.k = n1;
-    t.A = T1; t.lda = ld1; t.strideA = st1;
-    t.B = Y; t.ldb = kQrBlock; t.strideB = ss;
-    t.C = To + (long long)n1 * ldo; t.ldc = ldo; t.strideC = sto;
-    t.alpha = -1.0; t.batch = batch; t.flags = kAUpper;
-    if ((err = gemm(t, st)) != hipSuccess) return err;
-    assemble_wy_kernel<<<dim3(16, batch), 256, 0, st>>>(n1, n2, T1, ld1, st1, T2, ld2, st2, To, ldo, sto);
+    merge_wy_kernel<<<dim3((n2 + kMergeCols - 1) / kMergeCols, batch), kMergeThreads, 0, st>>>(
+        n1, n2, P, kQrBlock, ss, T1, ld1, st1, T2, ld2, st2, To, ldo, sto);
     return hipGetLastError();
 }
 
