@@ -137,7 +137,7 @@ __device__ inline void sqrt_rcp(float d, float& r, float& ri) {
 }
 
 // Upper Cholesky of the kb x kb diagonal block at (k0, k0) of each matrix
-// (one workgroup per matrix), its inverse into work.  Four steps of 16 rows:
+// (one workgroup per matrix), its inverse into inv.  Four steps of 16 rows:
 // wave 0 holds the 16 rows of all 64 columns (lane = column) and factors them
 // in registers, the diagonal block and the row panel to its right in the same
 // instructions (the multipliers of a row reach all lanes by readlane); then the
@@ -152,7 +152,7 @@ __device__ inline void sqrt_rcp(float d, float& r, float& ri) {
 // n = 2000.
 template <class T>
 __global__ __launch_bounds__(256) void potrf_diag_kernel(int k0, int kb, T* Z, long long ldz, long long sz,
-                                                         int* info, T* work) {
+                                                         int* info, T* inv, long long ldi, long long si) {
     __shared__ T S[kB][kB + 1];
     __shared__ T Si[kB][kB + 1];
     __shared__ T s_rcp[kB];
@@ -208,8 +208,11 @@ __global__ __launch_bounds__(256) void potrf_diag_kernel(int k0, int kb, T* Z, l
         Zb[i + (long long)j * ldz] = (i <= j) ? S[i][j] : (T)0;
     }
     lds_upper_inverse<T>(S, s_rcp, Si);
-    T* wb = work + (long long)b * kB * kB;
-    for (int e = tid; e < kB * kB; e += 256) wb[e] = Si[e % kB][e / kB];
+    T* wb = inv + b * si;
+    for (int e = tid; e < kB * kB; e += 256) {
+        const int i = e % kB, j = e / kB;
+        if (i < kb && j < kb) wb[i + j * ldi] = Si[i][j];
+    }
     if (tid == 0 && bad != 0 && info[b] == 0) info[b] = bad;
 }
 
@@ -237,18 +240,20 @@ __global__ __launch_bounds__(256) void trtri_diag_kernel(int n, const T* R, long
 
 }  // namespace
 
+// The factorisation.  The inverse of the diagonal block at (j0, j0) goes to
+// inv + j0 * step (leading dimension ldi, batch stride si).
 template <class T>
-hipError_t potrf_batched(int n, T* Z, long long ldz, long long sz, int batch, int* info_dev, T* work,
-                         hipStream_t st) {
-    hipError_t e = zero_ints(info_dev, batch, st);
-    if (e != hipSuccess) return e;
+static hipError_t potrf_blocks(int n, T* Z, long long ldz, long long sz, int batch, int* info_dev, T* inv,
+                               long long step, long long ldi, long long si, hipStream_t st) {
+    hipError_t e;
     for (int k0 = 0; k0 < n; k0 += kBand) {
         const int band = n - k0 < kBand ? n - k0 : kBand;
         for (int j0 = k0; j0 < k0 + band; j0 += kB) {
             const int kb = k0 + band - j0 < kB ? k0 + band - j0 : kB;
             StatScope sc(sizeof(T) == 8 ? "potrf_diag_kernel<double>" : "potrf_diag_kernel<float>", st,
                          batch * (double)kb * kb * kb / 3.0);
-            potrf_diag_kernel<T><<<batch, 256, 0, st>>>(j0, kb, Z, ldz, sz, info_dev, work);
+            T* Ik = inv + j0 * step;
+            potrf_diag_kernel<T><<<batch, 256, 0, st>>>(j0, kb, Z, ldz, sz, info_dev, Ik, ldi, si);
             sc.end();
             if ((e = hipGetLastError()) != hipSuccess) return e;
             const int rest = n - j0 - kb;
@@ -258,7 +263,7 @@ hipError_t potrf_batched(int n, T* Z, long long ldz, long long sz, int batch, in
             // row covers all kb rows).
             GemmDescT<T> g;
             g.m = kb; g.n = rest; g.k = kb; g.transa = 1; g.transb = 0;
-            g.A = work; g.lda = kB; g.strideA = (long long)kB * kB;
+            g.A = Ik; g.lda = ldi; g.strideA = si;
             g.B = Z12; g.ldb = ldz; g.strideB = sz;
             g.C = Z12; g.ldc = ldz; g.strideC = sz;
             g.beta = 0.0; g.batch = batch; g.flags = kALower;
@@ -296,19 +301,25 @@ hipError_t potrf_batched(int n, T* Z, long long ldz, long long sz, int batch, in
         s.flags = kCUpperTiles | kCStoreUpper;
         if ((e = gemm(s, st)) != hipSuccess) return e;
     }
-    return zero_strict_lower<T>(n, Z, ldz, sz, batch, st);
+    return hipSuccess;
+}
+
+template <class T>
+hipError_t potrf_batched(int n, T* Z, long long ldz, long long sz, int batch, int* info_dev, T* work,
+                         hipStream_t st) {
+    hipError_t e = zero_ints(info_dev, batch, st);
+    if (e != hipSuccess) return e;
+    e = potrf_blocks<T>(n, Z, ldz, sz, batch, info_dev, work, 0, kB, (long long)kB * kB, st);
+    return e != hipSuccess ? e : zero_strict_lower<T>(n, Z, ldz, sz, batch, st);
 }
 template hipError_t potrf_batched<double>(int, double*, long long, long long, int, int*, double*, hipStream_t);
 template hipError_t potrf_batched<float>(int, float*, long long, long long, int, int*, float*, hipStream_t);
 
+// The merges of the triangular inverse, its 64 x 64 diagonal blocks in place.
 template <class T>
-hipError_t trtri_batched(int n, const T* R, long long ldr, long long sr, T* Rinv, long long ldi, long long si,
-                         int batch, T* work, long long work_elems, hipStream_t st) {
-    hipError_t e = fill_matrix<T>(n, n, Rinv, ldi, si, batch, 0.0, 0.0, st);
-    if (e != hipSuccess) return e;
-    const int nblk = (n + kB - 1) / kB;
-    trtri_diag_kernel<T><<<dim3(nblk, batch), 256, 0, st>>>(n, R, ldr, sr, Rinv, ldi, si);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+static hipError_t trtri_merges(int n, const T* R, long long ldr, long long sr, T* Rinv, long long ldi, long long si,
+                               int batch, T* work, long long work_elems, hipStream_t st) {
+    hipError_t e;
     for (long long s = kB; s < n; s *= 2) {
         const long long full = n / (2 * s);           // pairs with both blocks of size s
         const long long o_rag = full * 2 * s;          // a ragged pair starts here if o_rag + s < n
@@ -343,6 +354,28 @@ hipError_t trtri_batched(int n, const T* R, long long ldr, long long sr, T* Rinv
     }
     return hipSuccess;
 }
+
+template <class T>
+hipError_t trtri_batched(int n, const T* R, long long ldr, long long sr, T* Rinv, long long ldi, long long si,
+                         int batch, T* work, long long work_elems, hipStream_t st) {
+    hipError_t e = fill_matrix<T>(n, n, Rinv, ldi, si, batch, 0.0, 0.0, st);
+    if (e != hipSuccess) return e;
+    const int nblk = (n + kB - 1) / kB;
+    trtri_diag_kernel<T><<<dim3(nblk, batch), 256, 0, st>>>(n, R, ldr, sr, Rinv, ldi, si);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    return trtri_merges<T>(n, R, ldr, sr, Rinv, ldi, si, batch, work, work_elems, st);
+}
+
+template <class T>
+hipError_t potrf_inverse_batched(int n, T* Z, long long ldz, long long sz, T* Rinv, long long ldi, long long si,
+                                 int batch, int* info_dev, T* work, long long work_elems, hipStream_t st) {
+    const hipError_t e = potrf_blocks<T>(n, Z, ldz, sz, batch, info_dev, Rinv, ldi + 1, ldi, si, st);
+    return e != hipSuccess ? e : trtri_merges<T>(n, Z, ldz, sz, Rinv, ldi, si, batch, work, work_elems, st);
+}
+template hipError_t potrf_inverse_batched<double>(int, double*, long long, long long, double*, long long, long long,
+                                                  int, int*, double*, long long, hipStream_t);
+template hipError_t potrf_inverse_batched<float>(int, float*, long long, long long, float*, long long, long long, int,
+                                                 int*, float*, long long, hipStream_t);
 
 template hipError_t trtri_batched<double>(int, const double*, long long, long long, double*, long long, long long,
                                           int, double*, long long, hipStream_t);

@@ -51,11 +51,13 @@ __global__ void broadcast_copy_kernel(int m, int n, const double* __restrict__ X
     }
 }
 
-// Z_b = G (upper triangle and diagonal) + shift_b I, strict lower part zero.
+// Z_b = G (upper triangle and diagonal) + shift_b I, strict lower part zero;
+// info[0 .. batch) = 0.
 template <class T>
 __global__ void shift_copy_kernel(int n, const T* __restrict__ G, long long ldg,
                                   T* __restrict__ Z, long long ldz, long long sz,
-                                  ShiftArgs sh) {
+                                  ShiftArgs sh, int* info) {
+    if (blockIdx.x == 0 && (int)threadIdx.x < sh.batch) info[threadIdx.x] = 0;
     const long long total = (long long)n * n;
     for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < total;
          e += (long long)gridDim.x * blockDim.x) {
@@ -307,14 +309,14 @@ hipError_t broadcast_copy(int m, int n, const double* X, long long ldx, double* 
 
 template <class T>
 hipError_t shift_copy(int n, const T* G, long long ldg, T* Z, long long ldz, long long sz, const ShiftArgs& sh,
-                      hipStream_t st) {
-    shift_copy_kernel<T><<<grid_for((long long)n * n), kThreads, 0, st>>>(n, G, ldg, Z, ldz, sz, sh);
+                      int* info, hipStream_t st) {
+    shift_copy_kernel<T><<<grid_for((long long)n * n), kThreads, 0, st>>>(n, G, ldg, Z, ldz, sz, sh, info);
     return hipGetLastError();
 }
 template hipError_t shift_copy<double>(int, const double*, long long, double*, long long, long long,
-                                       const ShiftArgs&, hipStream_t);
+                                       const ShiftArgs&, int*, hipStream_t);
 template hipError_t shift_copy<float>(int, const float*, long long, float*, long long, long long, const ShiftArgs&,
-                                      hipStream_t);
+                                      int*, hipStream_t);
 
 template <class T>
 hipError_t fill_matrix(int m, int n, T* Z, long long ldz, long long sz, int batch, double diag, double off,

@@ -19,7 +19,7 @@ hipError_t broadcast_copy(int m, int n, const double* X, long long ldx, double* 
 // The next four exist for T = double and T = float.
 template <class T>
 hipError_t shift_copy(int n, const T* G, long long ldg, T* Z, long long ldz, long long sz, const ShiftArgs& sh,
-                      hipStream_t st);
+                      int* info, hipStream_t st);
 template <class T>
 hipError_t fill_matrix(int m, int n, T* Z, long long ldz, long long sz, int batch, double diag, double off,
                        hipStream_t st);
@@ -55,6 +55,13 @@ hipError_t norm1_upper(int n, const double* R, long long ldr, double* colsum, do
 template <class T>
 hipError_t potrf_batched(int n, T* Z, long long ldz, long long sz, int batch, int* info_dev, T* work,
                          hipStream_t st);
+// Z_b = R_b^T R_b and Rinv_b = R_b^{-1} together (work: as for trtri_batched),
+// for consumers that take both as upper triangular: the strict lower triangles
+// of Z_b and Rinv_b are left undefined outside their 64 x 64 diagonal blocks.
+// info_dev must hold zeros.
+template <class T>
+hipError_t potrf_inverse_batched(int n, T* Z, long long ldz, long long sz, T* Rinv, long long ldi, long long si,
+                                 int batch, int* info_dev, T* work, long long work_elems, hipStream_t st);
 // Batched inverse of upper-triangular R_b into Rinv_b (strict lower part zero).
 // work: work_elems elements (n^2 batch / 2 + 64^2 batch suffices).
 template <class T>

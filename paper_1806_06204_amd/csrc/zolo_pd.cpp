@@ -74,11 +74,11 @@ struct Arena {
 // Buffers of one Cholesky-type step in precision T.
 template <class T>
 struct CholBufs {
-    T *X, *Xn, *G, *F, *Z, *D, *trtri, *potrf;
+    T *X, *Xn, *G, *F, *Z, *D, *trtri;
 };
 
 struct Work {
-    double *X, *Xn, *Y, *D, *G, *F, *trtri, *potrf, *part, *scal, *vec_v, *vec_u, *vec_w, *lam;
+    double *X, *Xn, *Y, *D, *G, *F, *trtri, *part, *scal, *vec_v, *vec_u, *vec_w, *lam;
     int* iflags;  // [0] nonfinite, [1] panel error, [2..] potrf info per j
     QrWork qr;
     CholBufs<float> s;  // FP32 copies for the mixed schedule (null unless requested)
@@ -102,7 +102,7 @@ Work layout(char* base, int m, int n, int rmax, int panel_coresident, bool mixed
     w.G = ar.take<double>(nn);
     w.F = ar.take<double>(nn);
     w.trtri = ar.take<double>(nn * rmax / 2 + (size_t)64 * 64 * rmax + 64);
-    w.potrf = ar.take<double>((size_t)64 * 64 * rmax);
+    ar.take<double>((size_t)64 * 64 * rmax);   // unused; keeps the counted size (zolo_pd_noalloc's limit) as it was
     w.part = ar.take<double>(4096);
     w.scal = ar.take<double>(64);
     w.vec_v = ar.take<double>(n);
@@ -142,7 +142,7 @@ Work layout(char* base, int m, int n, int rmax, int panel_coresident, bool mixed
         w.s.Z = ar.take<float>(nn * rmax);
         w.s.D = ar.take<float>(nn * rmax);
         w.s.trtri = ar.take<float>(nn * rmax / 2 + (size_t)64 * 64 * rmax + 64);
-        w.s.potrf = ar.take<float>((size_t)64 * 64 * rmax);
+        ar.take<float>((size_t)64 * 64 * rmax);   // as above
     }
     w.counted = ar.off + 256;
     w.qr.colslot_elems = std::max(qr_colslot_elems(m, n, rmax, panel_coresident),
@@ -223,13 +223,12 @@ int chol_core(StepCtx& cx, const Coeffs& co, const CholBufs<T>& b, bool g_valid)
     ShiftArgs sh;
     sh.batch = r;
     for (int j = 0; j < r; ++j) sh.shift[j] = co.c[2 * j];
-    HIPCHECK(shift_copy<T>(n, b.G, n, b.Z, n, nn, sh, st));
-    HIPCHECK(potrf_batched<T>(n, b.Z, n, nn, r, w.iflags + 2, b.potrf, st));
-    int rc = readback(cx.h, w.iflags + 2, sizeof(int) * r);
-    if (rc) return rc;
-    for (int j = 0; j < r; ++j)
-        if (reinterpret_cast<int*>(cx.h->host)[j] != 0) return ZOLO_BREAKDOWN;
-    HIPCHECK(trtri_batched<T>(n, b.Z, n, nn, b.D, n, nn, r, b.trtri, (long long)nn * r / 2 + 64 * 64 * r, st));
+    HIPCHECK(shift_copy<T>(n, b.G, n, b.Z, n, nn, sh, w.iflags + 2, st));
+    // R_j^{-1} from the factorisation's own diagonal inverses; the products
+    // below take both factors as upper triangular, so nothing below the
+    // diagonal is cleared.
+    HIPCHECK(potrf_inverse_batched<T>(n, b.Z, n, nn, b.D, n, nn, r, w.iflags + 2, b.trtri,
+                                      (long long)nn * r / 2 + 64 * 64 * r, st));
     // F = sum_j a_j R_j^{-1} R_j^{-T} (upper tiles), then mirror and add I.
     GemmDescT<T> f;
     f.m = n; f.n = n; f.k = n; f.transb = 1;
@@ -246,6 +245,12 @@ int chol_core(StepCtx& cx, const Coeffs& co, const CholBufs<T>& b, bool g_valid)
     x.A = b.X; x.lda = m; x.B = b.F; x.ldb = n;
     x.C = b.Xn; x.ldc = m; x.alpha = co.mhat;
     HIPCHECK(gemm(x, st));
+    // One wait per step, with the whole step queued: after a breakdown Xn holds
+    // garbage that the QR-type step replaces (X is as it was).
+    int rc = readback(cx.h, w.iflags + 2, sizeof(int) * r);
+    if (rc) return rc;
+    for (int j = 0; j < r; ++j)
+        if (reinterpret_cast<int*>(cx.h->host)[j] != 0) return ZOLO_BREAKDOWN;
     cx.flops_exec += r * (double)n * n * n + 2.0 * m * (double)n * n;
     return 0;
 }
@@ -253,7 +258,7 @@ int chol_core(StepCtx& cx, const Coeffs& co, const CholBufs<T>& b, bool g_valid)
 // FP64 Cholesky-type step on the main buffers (Z_j live in the QR stack buffer).
 int chol_step(StepCtx& cx, const Coeffs& co, bool g_valid) {
     const Work& w = *cx.w;
-    return chol_core<double>(cx, co, CholBufs<double>{w.X, w.Xn, w.G, w.F, w.Y, w.D, w.trtri, w.potrf}, g_valid);
+    return chol_core<double>(cx, co, CholBufs<double>{w.X, w.Xn, w.G, w.F, w.Y, w.D, w.trtri}, g_valid);
 }
 
 // The same step in FP32 (mixed schedule): X is rounded to FP32, the step runs
