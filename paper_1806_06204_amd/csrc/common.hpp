@@ -156,6 +156,12 @@ __device__ inline int opaque(int x) {
     return x;
 }
 
+// Sets a flag that the host may hold (pinned memory): a store that every
+// setter makes alike, no read-modify-write across the bus.
+__device__ inline void raise_flag(int* flag) {
+    __hip_atomic_store(flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 __device__ inline double wave_sum(double v) {
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
     return v;

@@ -36,7 +36,7 @@ __global__ void scale_copy_kernel(int m, int n, const double* __restrict__ A, lo
         if (!isfinite(v)) bad = 1;
         X[i + j * ldx] = v * s;
     }
-    if (bad && flag) atomicOr(flag, 1);
+    if (bad && flag) raise_flag(flag);
 }
 
 // Y_b = X for b < batch (X is m x n with ld ldx; Y_b has ld ldy, stride sy).
@@ -51,13 +51,11 @@ __global__ void broadcast_copy_kernel(int m, int n, const double* __restrict__ X
     }
 }
 
-// Z_b = G (upper triangle and diagonal) + shift_b I, strict lower part zero;
-// info[0 .. batch) = 0.
+// Z_b = G (upper triangle and diagonal) + shift_b I, strict lower part zero.
 template <class T>
 __global__ void shift_copy_kernel(int n, const T* __restrict__ G, long long ldg,
                                   T* __restrict__ Z, long long ldz, long long sz,
-                                  ShiftArgs sh, int* info) {
-    if (blockIdx.x == 0 && (int)threadIdx.x < sh.batch) info[threadIdx.x] = 0;
+                                  ShiftArgs sh) {
     const long long total = (long long)n * n;
     for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < total;
          e += (long long)gridDim.x * blockDim.x) {
@@ -309,14 +307,14 @@ hipError_t broadcast_copy(int m, int n, const double* X, long long ldx, double* 
 
 template <class T>
 hipError_t shift_copy(int n, const T* G, long long ldg, T* Z, long long ldz, long long sz, const ShiftArgs& sh,
-                      int* info, hipStream_t st) {
-    shift_copy_kernel<T><<<grid_for((long long)n * n), kThreads, 0, st>>>(n, G, ldg, Z, ldz, sz, sh, info);
+                      hipStream_t st) {
+    shift_copy_kernel<T><<<grid_for((long long)n * n), kThreads, 0, st>>>(n, G, ldg, Z, ldz, sz, sh);
     return hipGetLastError();
 }
 template hipError_t shift_copy<double>(int, const double*, long long, double*, long long, long long,
-                                       const ShiftArgs&, int*, hipStream_t);
+                                       const ShiftArgs&, hipStream_t);
 template hipError_t shift_copy<float>(int, const float*, long long, float*, long long, long long, const ShiftArgs&,
-                                      int*, hipStream_t);
+                                      hipStream_t);
 
 template <class T>
 hipError_t fill_matrix(int m, int n, T* Z, long long ldz, long long sz, int batch, double diag, double off,

@@ -19,7 +19,7 @@ hipError_t broadcast_copy(int m, int n, const double* X, long long ldx, double* 
 // The next four exist for T = double and T = float.
 template <class T>
 hipError_t shift_copy(int n, const T* G, long long ldg, T* Z, long long ldz, long long sz, const ShiftArgs& sh,
-                      int* info, hipStream_t st);
+                      hipStream_t st);
 template <class T>
 hipError_t fill_matrix(int m, int n, T* Z, long long ldz, long long sz, int batch, double diag, double off,
                        hipStream_t st);

@@ -173,7 +173,7 @@ __global__ __launch_bounds__(kPT) void panel_kernel(PanelArgs a) {
             unsigned spins = 0;
             while (__hip_atomic_load(&flg[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
                 if (++spins > a.spin_limit) {
-                    atomicOr(a.error_flag, 1);
+                    raise_flag(a.error_flag);
                     break;
                 }
                 __builtin_amdgcn_s_sleep(1);
@@ -225,7 +225,7 @@ __global__ __launch_bounds__(kPT) void panel_kernel(PanelArgs a) {
             unsigned spins = 0;
             while (__hip_atomic_load(&flg[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
                 if (++spins > a.spin_limit) {
-                    atomicOr(a.error_flag, 1);
+                    raise_flag(a.error_flag);
                     break;
                 }
                 __builtin_amdgcn_s_sleep(1);
@@ -708,7 +708,7 @@ __global__ __launch_bounds__(NT) void panel_leaf_kernel(PanelArgs a) {
             unsigned spins = 0;
             while (!dead && __hip_atomic_load(&flg[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
                 if (++spins > a.spin_limit) {
-                    atomicOr(a.error_flag, 1);
+                    raise_flag(a.error_flag);
                     dead = true;
                 }
                 __builtin_amdgcn_s_sleep(1);
@@ -769,7 +769,7 @@ __global__ __launch_bounds__(NT) void panel_leaf_kernel(PanelArgs a) {
                 for (int u = 0; u <= U; ++u) ok = ok && v[u][1] == tag && v[u][3] == tag;
                 if (__all(ok) || dead) break;
                 if (++spins > (a.spin_limit >> 4)) {   // a memory round trip each: about a second
-                    if (lane == 0) atomicOr(a.error_flag, 1);
+                    if (lane == 0) raise_flag(a.error_flag);
                     dead = true;
                 }
             }

@@ -79,7 +79,7 @@ struct CholBufs {
 
 struct Work {
     double *X, *Xn, *Y, *D, *G, *F, *trtri, *part, *scal, *vec_v, *vec_u, *vec_w, *lam;
-    int* iflags;  // [0] nonfinite, [1] panel error, [2..] potrf info per j
+    int* iflags;  // [0] nonfinite, [1] panel error, [2..] potrf info per j (with scal and lam in the pinned buffer)
     QrWork qr;
     CholBufs<float> s;  // FP32 copies for the mixed schedule (null unless requested)
     double *sk, *feat;  // sketch scratch and the 39 features (learned l)
@@ -189,6 +189,25 @@ int readback(zolo_handle h, const void* dev, size_t bytes) {
     return 0;
 }
 
+// Waits for what is queued; w.iflags, w.scal and w.lam are then up to date.
+int wait(zolo_handle h) {
+    HIPCHECK(hipStreamSynchronize(h->stream));
+    return 0;
+}
+
+// The scalars the host reads lie in the handle's pinned buffer: kernels store
+// them there and a wait is all the host needs.  (A copy of a few bytes costs a
+// launch and its gap, 8-10 us, five times in a solve.)  The first 2 KiB of the
+// buffer stay free for copies.
+void scalars_to_host(zolo_handle h, Work& w) {
+    char* p = reinterpret_cast<char*>(h->host);
+    w.iflags = reinterpret_cast<int*>(p + 2048);      // 64 ints
+    w.scal = reinterpret_cast<double*>(p + 2560);     // 64 doubles
+    w.lam = reinterpret_cast<double*>(p + 3072);      // 128 doubles
+    w.qr.error_flag = w.iflags + 1;
+    std::memset(w.iflags, 0, 64 * sizeof(int));
+}
+
 // G = X^T X (upper tiles; symmetric result in the upper triangle).
 template <class T>
 hipError_t gram(int m, int n, const T* X, long long ldx, T* G, hipStream_t st) {
@@ -223,7 +242,8 @@ int chol_core(StepCtx& cx, const Coeffs& co, const CholBufs<T>& b, bool g_valid)
     ShiftArgs sh;
     sh.batch = r;
     for (int j = 0; j < r; ++j) sh.shift[j] = co.c[2 * j];
-    HIPCHECK(shift_copy<T>(n, b.G, n, b.Z, n, nn, sh, w.iflags + 2, st));
+    std::memset(w.iflags + 2, 0, sizeof(int) * r);   // nothing that writes them is queued
+    HIPCHECK(shift_copy<T>(n, b.G, n, b.Z, n, nn, sh, st));
     // R_j^{-1} from the factorisation's own diagonal inverses; the products
     // below take both factors as upper triangular, so nothing below the
     // diagonal is cleared.
@@ -247,10 +267,9 @@ int chol_core(StepCtx& cx, const Coeffs& co, const CholBufs<T>& b, bool g_valid)
     HIPCHECK(gemm(x, st));
     // One wait per step, with the whole step queued: after a breakdown Xn holds
     // garbage that the QR-type step replaces (X is as it was).
-    int rc = readback(cx.h, w.iflags + 2, sizeof(int) * r);
-    if (rc) return rc;
+    if (int rc = wait(cx.h)) return rc;
     for (int j = 0; j < r; ++j)
-        if (reinterpret_cast<int*>(cx.h->host)[j] != 0) return ZOLO_BREAKDOWN;
+        if (w.iflags[2 + j] != 0) return ZOLO_BREAKDOWN;
     cx.flops_exec += r * (double)n * n * n + 2.0 * m * (double)n * n;
     return 0;
 }
@@ -287,12 +306,10 @@ int condition_estimate(StepCtx& cx, const double* X, double* l_out) {
     HIPCHECK(assemble_r(n, w.Y, m, mn, 1, w.qr, w.D, n, nn, st));
     HIPCHECK(trtri_batched(n, w.D, n, nn, w.G, n, nn, 1, w.trtri, nn / 2 + 64 * 64, st));
     HIPCHECK(norm1_upper(n, w.G, n, w.vec_u, w.scal, st));
-    // The norm and the panel error flag (a cooperative panel whose bounded
-    // wait gave up leaves R stale) in one read-back.
-    HIPCHECK(hipMemcpyAsync(w.scal + 1, w.iflags + 1, sizeof(int), hipMemcpyDeviceToDevice, st));
-    if (int rc = readback(cx.h, w.scal, 2 * sizeof(double))) return rc;
-    if (*reinterpret_cast<const int*>(cx.h->host + 1) != 0) return ZOLO_KERNEL;
-    const double nrm = cx.h->host[0];
+    if (int rc = wait(cx.h)) return rc;
+    // A cooperative panel whose bounded wait gave up leaves R stale.
+    if (w.iflags[1] != 0) return ZOLO_KERNEL;
+    const double nrm = w.scal[0];
     *l_out = (std::isfinite(nrm) && nrm > 0.0) ? 1.0 / (std::sqrt((double)n) * nrm) : kLMin;
     cx.flops_exec += 2.0 * m * (double)n * n + (double)n * n * n / 3.0;
     return 0;
@@ -371,7 +388,7 @@ int ensure_workers(zolo_handle h, int want, size_t need) {
         x->panel_stream = h->worker_panel_stream;
         x->single_panels = true;
         bool ok = hipStreamCreate(&x->stream) == hipSuccess;
-        ok = ok && hipHostMalloc((void**)&x->host, 4096) == hipSuccess;
+        ok = ok && hipHostMalloc((void**)&x->host, 4096, hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess;
         ok = ok && hipEventCreateWithFlags(&x->ev_ready, hipEventDisableTiming) == hipSuccess;
         ok = ok && hipEventCreateWithFlags(&x->ev_done, hipEventDisableTiming) == hipSuccess;
         h->workers.push_back(x);
@@ -463,6 +480,7 @@ int pd_core(zolo_handle h, char* base, int m, int n, const double* A, int lda, d
     const bool mixed = opts.precision == 1;
     const bool dense_qr = opts.qr_variant == 1;
     Work w = layout(base, dense_qr ? m + n : m, n, rmax, h->panel_coresident, mixed);
+    scalars_to_host(h, w);
     w.qr.panel_stream = h->panel_stream;
     w.qr.single_panels = h->single_panels;
     w.qr.ev_ready = h->ev_ready;
@@ -471,7 +489,6 @@ int pd_core(zolo_handle h, char* base, int m, int n, const double* A, int lda, d
     w.qr.ev_side_ready = h->ev_side_ready;
     w.qr.ev_side_done = h->ev_side_done;
     hipStream_t st = h->stream;
-    int* hi = reinterpret_cast<int*>(h->host);
     int rc = 0;
     // Stage times: drain the stream first so queued work is charged to the
     // stage that queued it.
@@ -488,7 +505,6 @@ int pd_core(zolo_handle h, char* base, int m, int n, const double* A, int lda, d
 
     StepCtx cx{h, &w, m, n};
     cx.dense_qr = dense_qr;
-    HIPFIN(zero_ints(w.iflags, 64, st));
     // Step 1: alpha (upper bound of sigma_max) and X0 = A / alpha.
     double lam = -1.0;  // Rayleigh quotient of A^T A, a lower bound on sigma_max(A)^2, if computed
     if (!(alpha > 0.0)) {
@@ -497,9 +513,9 @@ int pd_core(zolo_handle h, char* base, int m, int n, const double* A, int lda, d
         bool done = false;
         for (int chunk = 0; chunk < 10 && !done; ++chunk) {
             HIPFIN(power_steps(m, n, A, lda, 10, w.vec_v, w.vec_u, w.vec_w, w.lam, st));
-            if ((rc = readback(h, w.lam, sizeof(double) * 10))) return finish(rc);
+            if ((rc = wait(h))) return finish(rc);
             for (int it = 0; it < 10; ++it) {
-                lam = h->host[it];
+                lam = w.lam[it];
                 if ((chunk > 0 || it > 0) && std::fabs(lam - lam_prev) <= 1e-10 * lam) done = true;
                 lam_prev = lam;
             }
@@ -510,8 +526,8 @@ int pd_core(zolo_handle h, char* base, int m, int n, const double* A, int lda, d
     }
     inf.alpha = alpha;
     HIPFIN(scale_copy(m, n, A, lda, w.X, m, 1.0 / alpha, w.iflags, st));
-    if ((rc = readback(h, w.iflags, sizeof(int)))) return finish(rc);
-    if (hi[0]) return finish(ZOLO_NONFINITE);
+    if ((rc = wait(h))) return finish(rc);
+    if (w.iflags[0]) return finish(ZOLO_NONFINITE);
 
     // Step 2: l, a lower bound on sigma_min(X0).
     if (!(l > 0.0) && opts.l_source == 1 && h->est) {
@@ -529,8 +545,8 @@ int pd_core(zolo_handle h, char* base, int m, int n, const double* A, int lda, d
         } else {
             HIPFIN(fill_vector(n, w.vec_v, 1.0 / std::sqrt((double)n), st));
             HIPFIN(power_steps(m, n, w.X, m, 4, w.vec_v, w.vec_u, w.vec_w, w.lam, st));
-            if ((rc = readback(h, w.lam + 3, sizeof(double)))) return finish(rc);
-            b = std::sqrt(std::max(h->host[0], 0.0));
+            if ((rc = wait(h))) return finish(rc);
+            b = std::sqrt(std::max(w.lam[3], 0.0));
             inf.flops_exec += 4.0 * m * (double)n * 4;
         }
         b = std::min(1.0, b);
@@ -591,8 +607,8 @@ int pd_core(zolo_handle h, char* base, int m, int n, const double* A, int lda, d
         }
         if (kind == 'Q') {
             if ((rc = qr_step(cx, co))) return finish(rc);
-            if ((rc = readback(h, w.iflags + 1, sizeof(int)))) return finish(rc);
-            if (hi[0]) return finish(ZOLO_KERNEL);
+            if ((rc = wait(h))) return finish(rc);
+            if (w.iflags[1]) return finish(ZOLO_KERNEL);
             inf.t_stage[1] += lap();
         }
         g_valid = false;
@@ -605,8 +621,8 @@ int pd_core(zolo_handle h, char* base, int m, int n, const double* A, int lda, d
         if (opts.stop_rule == 1) {
             HIPFIN(frob2(m, n, w.Xn, m, w.X, m, w.part, w.scal, st));
             std::swap(w.X, w.Xn);
-            if ((rc = readback(h, w.scal, 2 * sizeof(double)))) return finish(rc);
-            const double rel = std::sqrt(h->host[0]) / std::sqrt(h->host[1]);
+            if ((rc = wait(h))) return finish(rc);
+            const double rel = std::sqrt(w.scal[0]) / std::sqrt(w.scal[1]);
             l = l_pred;
             inf.t_stage[3] += lap();
             if (rel <= std::pow(kEps, 1.0 / (2 * r + 1))) {
@@ -618,12 +634,12 @@ int pd_core(zolo_handle h, char* base, int m, int n, const double* A, int lda, d
             if (l_pred >= kConverged) {
                 HIPFIN(gram(m, n, w.X, m, w.G, st));
                 HIPFIN(orth2(n, w.G, n, w.part, w.scal, st));
-                if ((rc = readback(h, w.scal, sizeof(double)))) return finish(rc);
+                if ((rc = wait(h))) return finish(rc);
                 cx.flops_exec += (double)m * n * n;
                 inf.flops_paper += (double)m * n * n;
                 ++inf.checks;
                 g_valid = true;
-                const double d = std::sqrt(std::max(h->host[0], 0.0)) / std::sqrt((double)n);
+                const double d = std::sqrt(std::max(w.scal[0], 0.0)) / std::sqrt((double)n);
                 inf.orth_check = d;
                 inf.t_stage[3] += lap();
                 if (d <= opts.tau) {
@@ -674,9 +690,9 @@ int pd_core(zolo_handle h, char* base, int m, int n, const double* A, int lda, d
         HIPFIN(frob2(m, n, A, lda, w.Xn, m, w.part, w.scal, st));
         HIPFIN(gram(m, n, Qp, ldq, w.G, st));
         HIPFIN(orth2(n, w.G, n, w.part, w.scal + 2, st));
-        if ((rc = readback(h, w.scal, 3 * sizeof(double)))) return finish(rc);
-        inf.bwd_err = std::sqrt(h->host[0]) / std::sqrt(h->host[1]);
-        inf.orth_err = std::sqrt(std::max(h->host[2], 0.0)) / std::sqrt((double)n);
+        if ((rc = wait(h))) return finish(rc);
+        inf.bwd_err = std::sqrt(w.scal[0]) / std::sqrt(w.scal[1]);
+        inf.orth_err = std::sqrt(std::max(w.scal[2], 0.0)) / std::sqrt((double)n);
     }
     inf.flops_exec += cx.flops_exec;
     return finish(status);
@@ -710,7 +726,7 @@ int zolo_create(zolo_handle* out, void* stream) {
         delete h;
         return ZOLO_HIP;
     }
-    if (hipHostMalloc((void**)&h->host, 4096) != hipSuccess) {
+    if (hipHostMalloc((void**)&h->host, 4096, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
         delete h;
         return ZOLO_HIP;
     }
