@@ -38,6 +38,7 @@
 #include "misc.hpp"
 #include "stats.hpp"
 
+#include <type_traits>
 #include <algorithm>
 #include <mutex>
 
@@ -67,6 +68,7 @@ constexpr int kWaitVmcnt0 = 0x0F70;
 
 struct PanelArgs {
     int L, nb, G, rows_per_wg;
+    int batch, local;                    // local: each matrix's workgroups on one XCD (register-leaf kernel)
     double* P; long long ld, sp;         // panel top-left (row p0, column p0) of matrix 0
     double* T; long long st;             // T_b, kNB x kNB column-major
     double* Rd; long long srd;           // R diagonal block out, kNB x kNB
@@ -580,12 +582,18 @@ __global__ __launch_bounds__(kPT) void panel_kernel(PanelArgs a) {
 // After 16 columns the ring is in column order again.
 //
 // End of a leaf: each wave stages V (its own rows, 64 x 16 at a time) in LDS
-// and forms its part of W = V_s^T [V_prev, C] with 16 x 16 x 4 MFMAs, reading
-// 128 contiguous bytes per lane of the other columns; the parts are summed
-// over the waves (MULTI: and workgroups).  W2 = T_s^T (V_s^T C) comes out of
+// and forms its part of W = V_s^T [V_prev, C] with 16 x 16 x 4 MFMAs; the parts are
+// summed over the waves (MULTI: and workgroups).  W2 = T_s^T (V_s^T C) comes out of
 // the MFMA in the layout that the update C -= V_s W2 takes as its operand.
 // V_prev^T V_s goes to the packed V^T V from which the first workgroup merges
 // T once, after the last leaf.
+//
+// J = 1 keeps the other three blocks of 16 columns in registers too, as tiles that
+// are both the operand of W and the accumulator of the update: the panel is read
+// once, and a leaf's columns are written once.  After a leaf its V becomes a tile
+// and the next leaf's tile is turned to a row per lane through LDS.  T_s is
+// formed by one wave between its MFMAs.  For J > 1 the other columns are read and
+// written at every leaf end.
 //
 // The workgroups' exchange of a column (MULTI): wave 0 stores the workgroup's
 // 16 sums, the first workgroup also the pivot row, as 16-byte slots
@@ -595,18 +603,23 @@ __global__ __launch_bounds__(kPT) void panel_kernel(PanelArgs a) {
 // alternate between two parities: a workgroup rewrites a slot only after every
 // other one has published the exchange after the one that read it.  Tags grow
 // through a factorisation and start from zeroed slots.  Every wait is bounded.
+// With a matrix's workgroups on one XCD the slots stay in its L2; the accesses are
+// coherent over the whole GPU, so the placement matters for speed alone.
 //
-// Bound: latency of the 64 dependent columns, 0.75-0.9 us each in one workgroup of
-// 256 rows and 1.2 us more with the exchange, and of the four leaf ends.  64-column
-// panels, us, against the kernel before (the slab in LDS, a sweep of 16 columns
-// per column through LDS, two or more workgroups from 128 rows on, flag exchange):
-//   live rows      128   256   512  1024  2048  4160  8256  8 x 8256
-//   before         372   400   408   426   433   471   502       542
-//   this kernel    100   108   141   206   220   254   290       309
-// and one workgroup per matrix (many-matrix call) 2048 rows 420 against about 660.
+// Bound: latency of the 64 dependent columns, about 250 dependent instructions each:
+// in one workgroup 1500 cycles (256 rows) or 2170 (512 rows), 2600-3500 more with the
+// exchange; a leaf end takes 16-20k cycles.  64-column panels, us, against the slab
+// in LDS (a sweep of 16 columns per column, flag exchange) and against the leaf
+// alone in registers, with square root and divisions in the column's chain and the
+// exchange across the XCDs:
+//   live rows       128   256   512  1024  2048  4160  8256  8 x 8256
+//   slab in LDS     372   400   408   426   433   471   502       542
+//   leaf            100   108   141   206   220   254   290       309
+//   this kernel      73    77   106   166   179   214   246       249
 // ---------------------------------------------------------------------------
 typedef unsigned u4v __attribute__((ext_vector_type(4)));
 typedef double dpair_u __attribute__((ext_vector_type(2), aligned(8)));
+typedef double dpair __attribute__((ext_vector_type(2)));
 
 template <int CTRL>
 __device__ inline double dpp(double x) {
@@ -658,7 +671,7 @@ __device__ inline double row_bcast(double x) {
                                           0ll, __builtin_bit_cast(long long, x), kDppRowBcast + N, 0xf, 0xf, true));
 }
 template <int Q>
-__device__ inline void ring_turn(double (&xr)[kLW], double c, double v) {
+__device__ __forceinline__ void ring_turn(double (&xr)[kLW], double c, double v) {
     if constexpr (Q < kLW) {
         xr[Q - 1] = fma(-row_bcast<Q>(c), v, xr[Q]);
         ring_turn<Q + 1>(xr, c, v);
@@ -668,20 +681,106 @@ __device__ inline void ring_turn(double (&xr)[kLW], double c, double v) {
 // Packed strict upper triangle: (i, j), i < j.
 __device__ inline int upper_at(int i, int j) { return j * (j - 1) / 2 + i; }
 
+// T_s of a leaf from its taus and V^T V: T[i][c] = -tau_c sum_{i <= l < c} T[i][l]
+// (V^T V)[l][c], T[c][c] = tau_c.  Lane i of each row of 16 lanes holds row i of T,
+// row[c] the sum so far: once column C is final its terms go to all later columns,
+// which are independent of each other (a sum per column at a time is a chain of
+// 120 dependent operations, 7.4k cycles).  z: row C of V^T V, the same in all lanes.
+template <int C>
+__device__ __forceinline__ void leaf_z(double (&z)[kLW], const double* s_G, int c0) {
+#pragma unroll
+    for (int c = C + 1; c < kLW; ++c) z[c] = s_G[upper_at(c0 + C, c0 + c)];
+}
+template <int C>
+__device__ __forceinline__ void leaf_t_column(double (&row)[kLW], const double (&z)[kLW], double tau, int lw, int l16,
+                                     double (*s_Ts)[kLW + 1]) {
+    const double t = row_bcast<C>(tau);
+    const double x = l16 == C ? t : (C > 0 && l16 < C && C < lw ? -t * row[C] : 0.0);
+    s_Ts[l16][C] = x;                             // the four rows of lanes alike
+#pragma unroll
+    for (int c = C + 1; c < kLW; ++c) row[c] = C == 0 ? x * z[c] : fma(x, z[c], row[c]);
+}
+template <int C = 0>
+__device__ __forceinline__ void leaf_t_all(double (&row)[kLW], const double (&z)[kLW], const double* s_G, double tau, int c0,
+                                  int lw, int l16, double (*s_Ts)[kLW + 1]) {
+    if constexpr (C < kLW) {
+        double zn[kLW];
+        leaf_z<C + 1>(zn, s_G, c0);
+        leaf_t_column<C>(row, z, tau, lw, l16, s_Ts);
+        __builtin_amdgcn_sched_barrier(0);
+        leaf_t_all<C + 1>(row, zn, s_G, tau, c0, lw, l16, s_Ts);
+    }
+}
+__device__ __forceinline__ void leaf_t(const double* s_G, const double* s_tau, int c0, int lw, int l16,
+                              double (*s_Ts)[kLW + 1]) {
+    double row[kLW], z[kLW];
+    const double tau = l16 < lw ? s_tau[c0 + min(l16, lw - 1)] : 0.0;
+    leaf_z<0>(z, s_G, c0);
+    leaf_t_all(row, z, s_G, tau, c0, lw, l16, s_Ts);
+}
+// The 16 steps U of the products of a tile of V (column l % 16, at sv) with the
+// NQ tiles y.  TS: column U of T_s is formed between step U's MFMAs
+// (64 cycles each), which hide it.
+template <bool TS, int NQ, int VS, int U = 0>
+__device__ __forceinline__ void leaf_steps(const double* sv, const double (*y)[kLW], d4* w, dpair v,
+                                           double (&row)[kLW], const double* s_G, double tau, int c0, int lw,
+                                           int lane, double (*s_Ts)[kLW + 1]) {
+    if constexpr (U < kLW) {
+        const int l16 = lane & 15, lg = lane >> 4;
+        double z[kLW];
+        if constexpr (TS) leaf_z<U>(z, s_G, c0);
+        if constexpr (U % 2 == 0) v = *reinterpret_cast<const dpair*>(&sv[l16 * VS + 4 * U + 2 * lg]);
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) w[q] = mfma_f64_16x16x4(v[U % 2], y[q][U], w[q]);
+        if constexpr (TS) {
+            leaf_t_column<U>(row, z, tau, lw, l16, s_Ts);
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);               // an MFMA,
+                __builtin_amdgcn_sched_group_barrier(0x2, (kLW - U + 12) / NQ, 0);   // vector instructions of T_s
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);        // one step's loads at a time (registers)
+        leaf_steps<TS, NQ, VS, U + 1>(sv, y, w, v, row, s_G, tau, c0, lw, lane, s_Ts);
+    }
+}
+
 template <int NT, int J, bool MULTI>
 __global__ __launch_bounds__(NT) void panel_leaf_kernel(PanelArgs a) {
     constexpr int NW = NT / 64;
-    constexpr int VS = 65;                        // row stride of a staged V column
+    constexpr int VS = 66;                        // row stride of a staged V column (16-byte loads)
+    constexpr int NO = kOther / kLW;              // other blocks of 16 columns
+    constexpr bool RES = J == 1;                  // the whole panel in registers
+    constexpr int TW = NW - 1;                    // the wave that forms T_s
     constexpr int TS = kNB + 1;
-    __shared__ double s_v[NW][kLW * VS];          // staged V, then the waves' parts of W, at the end T
-    __shared__ double s_W[kLW * kOther];          // W[i][q] at i * kOther + q
-    __shared__ double s_G[kNB * (kNB - 1) / 2];   // V^T V, strict upper
-    __shared__ double s_Ts[kNL][kLW][kLW + 1];    // T_s of each leaf
-    __shared__ double s_part[2][NW][kLW], s_prow[2][kLW], s_tot[2][2 * kLW];
-    __shared__ double s_tau[kNB];
-    static_assert(4 * kLW * VS >= kNB * TS && kLW * kOther <= kLW * VS, "s_v holds T and a part of W");
-    static_assert(NW >= 4, "T in s_v");
-    const int g = MULTI ? blockIdx.x % a.G : 0, b = MULTI ? blockIdx.x / a.G : blockIdx.x;
+    // The words that every column takes come first: within 64 KiB an address is
+    // an instruction's offset.
+    __shared__ struct __attribute__((aligned(16))) {
+        double part[2][NW][kLW], prow[2][kLW], tot[2][2 * kLW];
+        double tau[kNB], unused[kLW];
+        double Ts[kNL][kLW][kLW + 1];             // T_s of each leaf
+        double G[kNB * (kNB - 1) / 2];            // V^T V, strict upper
+        double W[kLW * kOther];                   // W[i][q] at i * kOther + q
+        double v[NW][kLW * VS];                   // staged V, at the end T
+        double p[RES ? NW : 1][RES ? kLW * kOther : 1];   // the waves' parts of W
+    } sm;
+    auto &s_part = sm.part;
+    auto &s_v = sm.v;
+    auto &s_prow = sm.prow;
+    auto &s_tot = sm.tot;
+    auto &s_tau = sm.tau;
+    auto &s_Ts = sm.Ts;
+    auto &s_G = sm.G;
+    auto &s_W = sm.W;
+    auto &s_p = sm.p;
+    static_assert(4 * kLW * VS >= kNB * TS, "s_v holds T");
+    static_assert(NW == 4 || NW == 8, "T in s_v; sum_waves");
+    // Workgroups are dealt to the XCDs round-robin: with `local` matrix b's lie on
+    // XCD b % kNumXcd (and the others of the grid leave).
+    const int chunk = MULTI && a.local ? kNumXcd : 1;
+    const int idx = blockIdx.x / chunk;
+    const int g = MULTI ? idx % a.G : 0, b = MULTI ? blockIdx.x % chunk + chunk * (idx / a.G) : blockIdx.x;
+    if (MULTI && b >= a.batch) return;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, lg = lane >> 4;
@@ -782,11 +881,28 @@ __global__ __launch_bounds__(NT) void panel_leaf_kernel(PanelArgs a) {
         return sum;
     };
 
-    for (int c0 = 0; c0 < nb; c0 += kLW) {
-        const int lw = min(kLW, nb - c0), leaf = c0 / kLW;
-        double xr[J][kLW];
-        // Loads from valid addresses, then zeros for rows past the slab and
-        // columns past a short leaf.
+    // A tile: 16 columns of 64 rows, element u of lane l is row 8 (u / 2) + 2 (l / 16) +
+    // u % 2 of column cb + l % 16, so that a load of 16 bytes a lane takes 64
+    // contiguous bytes of each column.
+    auto load_tile = [&](int cb, int base, double (&y)[kLW]) __attribute__((always_inline)) {
+        const int row = base + 2 * lg;
+        const double* p = X + (long long)min(cb + l16, nb - 1) * ld;
+        if (base + 64 <= nr) {
+#pragma unroll
+            for (int u = 0; u < kLW; u += 2) {
+                const dpair_u t = *reinterpret_cast<const dpair_u*>(p + row + 4 * u);
+                y[u] = t[0];
+                y[u + 1] = t[1];
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < kLW; ++u) y[u] = p[min(row + 4 * (u & ~1) + (u & 1), nr - 1)];
+        }
+    };
+    // The leaf's columns, a row per lane: loads from valid addresses, then zeros
+    // for rows past the slab and columns past a short leaf.
+    double xr[J][kLW];
+    auto load_leaf = [&](int c0, int lw) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < J; ++j) {
             const unsigned at = min(tid + NT * j, nr - 1);
@@ -799,6 +915,23 @@ __global__ __launch_bounds__(NT) void panel_leaf_kernel(PanelArgs a) {
 #pragma unroll
             for (int q = 0; q < kLW; ++q) xr[j][q] = keep_if(xr[j][q], q < lw ? in : 0);
         }
+    };
+    // The other blocks in the order later ones, finished ones (V).
+    double y[RES ? NO : 1][kLW];
+    if constexpr (RES) {
+        load_leaf(0, min(kLW, nb));
+#pragma unroll
+        for (int q = 0; q < NO; ++q) load_tile(kLW + kLW * q, min(64 * wv, (nr - 1) & ~63), y[q]);
+#pragma unroll
+        for (int q = 0; q < NO; ++q)
+#pragma unroll
+            for (int u = 0; u < kLW; ++u)
+                y[q][u] = keep_if(y[q][u], opaque(64 * wv + 2 * lg + 4 * (u & ~1) + (u & 1) < nr &&
+                                                          kLW + kLW * q + l16 < nb ? -1 : 0));
+    }
+    for (int c0 = 0; c0 < nb; c0 += kLW) {
+        const int lw = min(kLW, nb - c0), leaf = c0 / kLW;
+        if constexpr (!RES) load_leaf(c0, lw);
         for (int kk = 0; kk < lw; ++kk) {
             const int k = c0 + kk, kr = k - r0;   // kr: pivot row within the slab
             const int buf = kk & 1;
@@ -822,6 +955,11 @@ __global__ __launch_bounds__(NT) void panel_leaf_kernel(PanelArgs a) {
                 double h[NW];
 #pragma unroll
                 for (int w = 0; w < NW; ++w) h[w] = s_part[buf][w][l16];
+                prow = s_prow[buf][l16];
+                // One wait for all of the words (the compiler would take them two by two).
+                if constexpr (NW == 4) asm volatile("" : "+v"(h[0]), "+v"(h[1]), "+v"(h[2]), "+v"(h[3]), "+v"(prow));
+                else asm volatile("" : "+v"(h[0]), "+v"(h[1]), "+v"(h[2]), "+v"(h[3]), "+v"(h[4]), "+v"(h[5]),
+                                       "+v"(h[6]), "+v"(h[7]), "+v"(prow));
 #pragma unroll
                 for (int s = 1; s < NW; s *= 2)
 #pragma unroll
@@ -830,8 +968,8 @@ __global__ __launch_bounds__(NT) void panel_leaf_kernel(PanelArgs a) {
             };
             if constexpr (MULTI) {
                 if (wv == 0) {
-                    prow = s_prow[buf][l16];
-                    sum = column_exchange(k, sum_waves(), prow);
+                    sum = sum_waves();
+                    sum = column_exchange(k, sum, prow);
                     if (lane < 2 * kLW) s_tot[buf][lane] = lane < kLW ? sum : prow;
                 }
                 __syncthreads();
@@ -839,23 +977,44 @@ __global__ __launch_bounds__(NT) void panel_leaf_kernel(PanelArgs a) {
                 prow = s_tot[buf][kLW + l16];
             } else {
                 sum = sum_waves();
-                prow = s_prow[buf][l16];
             }
             // Reflector k on x = [alpha; below], beta = -sign(alpha) |x|,
             // v = [1; below / (alpha - beta)]  (no cancellation in alpha - beta).
+            // |x| and 1 / |x| from one reciprocal square root and a second reciprocal,
+            // Newton steps to the last bits: half the dependent operations of a square
+            // root and two divisions.
             const double s2 = uniform(sum), alpha = uniform(prow);
             double beta = alpha, tau = 0.0, scale = 0.0;
             if (s2 != 0.0) {
-                const double nrm = sqrt(alpha * alpha + s2);
+                const double t = fma(alpha, alpha, s2);
+                double h = __builtin_amdgcn_rsq(t);
+                double nrm = t * h;
+                h *= 0.5;
+                double e = fma(-h, nrm, 0.5);
+                nrm = fma(nrm, e, nrm);
+                h = fma(h, e, h);
+                const double d = fma(-nrm, nrm, t);
+                e = fma(-h, nrm, 0.5);
+                nrm = fma(d, h, nrm);
+                h = fma(h, e, h);                 // 1 / (2 |x|)
+                const double den = fabs(alpha) + nrm;
+                double x = __builtin_amdgcn_rcp(den);
+                e = fma(-den, x, 1.0);
+                x = fma(x, e, x);
+                e = fma(-den, x, 1.0);
+                x = fma(x, e, x);
                 beta = alpha >= 0.0 ? -nrm : nrm;
-                tau = (beta - alpha) / beta;
-                scale = 1.0 / (alpha - beta);
+                tau = den * (h + h);              // (beta - alpha) / beta
+                scale = alpha >= 0.0 ? x : -x;    // 1 / (alpha - beta)
             }
-            const double w = prow + scale * sum;  // v_k^T column (later) or v_l^T v_k (finished)
+            const double w = fma(scale, sum, prow);   // v_k^T column (later) or v_l^T v_k (finished)
             const double c = l16 < kLW - kk ? tau * w : 0.0;
-            if (wv == 0 && lane < kLW) {
-                if (lane >= kLW - kk) s_G[upper_at(c0 + lane - (kLW - kk), k)] = w;
-                if (lane == 0) s_tau[k] = tau;
+            // tau from lane 0, V^T V from the finished columns' lanes, in one store
+            // by the wave that has the fewest rows.
+            if (wv == TW && lane < kLW) {
+                double* to = lane >= kLW - kk ? &s_G[upper_at(c0 + lane - (kLW - kk), k)] : &sm.unused[lane];
+                to = lane == 0 ? &s_tau[k] : to;
+                *to = lane == 0 ? tau : w;
             }
 #pragma unroll
             for (int j = 0; j < J; ++j) {
@@ -889,19 +1048,64 @@ __global__ __launch_bounds__(NT) void panel_leaf_kernel(PanelArgs a) {
                     if (q < lw) (X + (long long)(c0 + q) * ld)[(unsigned)row] = xr[j][q];
             }
         }
-        // V of the wave's rows 64 wv + NT j ... + 63, staged in LDS by the wave
-        // for itself: from the registers for one row per thread, else read
-        // back (so that the leaf's registers are free from here on).
+        // Tile q of 16 other columns is later, q < nlater, or finished, q >= fin, of a
+        // resident panel; else they are in the order of the columns.
+        const int nother = nb - lw, nblk = (nother + kLW - 1) / kLW, nc = nb - c0 - lw;
+        const int nlater = (nc + kLW - 1) / kLW, fin = NO - leaf;
+        const int later0 = RES ? 0 : c0, prev0 = RES ? kLW * fin : 0;
+        auto tile_col = [&](int q) __attribute__((always_inline)) { return kLW * q < c0 ? kLW * q : kLW * q + lw; };
         double* const sv = s_v[wv];
-        auto load_v = [&](int j, double (&v)[kLW]) __attribute__((always_inline)) {
-            if constexpr (J == 1) {
+        if constexpr (RES) {
+            // V staged in LDS by each wave for its own 64 rows: 1 on the pivot,
+            // zeros above it.
+            d4 w4[NO];
 #pragma unroll
-                for (int q = 0; q < kLW; ++q) v[q] = xr[0][q];
-            } else {
-                const unsigned at = min(tid + NT * j, nr - 1);
+            for (int q = 0; q < NO; ++q) w4[q] = d4{0, 0, 0, 0};
+            if (64 * wv < nr) {
+                __builtin_amdgcn_wave_barrier();
+                if (wv > 0 || r0 > 0) {           // no pivots here
 #pragma unroll
-                for (int q = 0; q < kLW; ++q) v[q] = (X + (long long)(c0 + min(q, lw - 1)) * ld)[at];
+                    for (int q = 0; q < kLW; ++q) sv[q * VS + lane] = xr[0][q];
+                } else {
+#pragma unroll
+                    for (int q = 0; q < kLW; ++q) {
+                        const int k = c0 + q;
+                        sv[q * VS + lane] = lane > k ? xr[0][q] : (lane == k && q < lw ? 1.0 : 0.0);
+                    }
+                }
+                __builtin_amdgcn_wave_barrier();
+                double row[kLW];
+                const double tau = l16 < lw ? s_tau[c0 + min(l16, lw - 1)] : 0.0;
+                if (nlater + leaf == NO) {
+                    if (wv == TW) {
+                        leaf_steps<true, NO, VS>(sv, y, w4, dpair{}, row, s_G, tau, c0, lw, lane, s_Ts[leaf]);
+                    } else {
+                        leaf_steps<false, NO, VS>(sv, y, w4, dpair{}, row, s_G, tau, c0, lw, lane, s_Ts[leaf]);
+                    }
+                } else {
+                    if (wv == TW) leaf_t(s_G, s_tau, c0, lw, l16, s_Ts[leaf]);
+#pragma unroll
+                    for (int q = 0; q < NO; ++q)
+                        if (q < nlater || q >= fin)
+                            leaf_steps<false, 1, VS>(sv, &y[q], &w4[q], dpair{}, row, s_G, tau, c0, lw, lane, s_Ts[leaf]);
+                }
+            } else if (wv == TW) {
+                leaf_t(s_G, s_tau, c0, lw, l16, s_Ts[leaf]);
             }
+            if (nother > 0) {
+#pragma unroll
+                for (int q = 0; q < NO; ++q)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        s_p[RES ? wv : 0][Mfma<double>::row(lane, e) * kOther + kLW * q + l16] = w4[q][e];
+            }
+        }
+        // V of the wave's rows 64 wv + NT j ... + 63, staged in LDS by the wave for
+        // itself, read back so that the leaf's registers are free from here on.
+        auto load_v = [&](int j, double (&v)[kLW]) __attribute__((always_inline)) {
+            const unsigned at = min(tid + NT * j, nr - 1);
+#pragma unroll
+            for (int q = 0; q < kLW; ++q) v[q] = (X + (long long)(c0 + min(q, lw - 1)) * ld)[at];
         };
         auto stage = [&](int j, const double (&v)[kLW]) __attribute__((always_inline)) {
             const int row = tid + NT * j;
@@ -920,82 +1124,50 @@ __global__ __launch_bounds__(NT) void panel_leaf_kernel(PanelArgs a) {
             }
             __builtin_amdgcn_wave_barrier();
         };
-        const int nother = nb - lw, nblk = (nother + 15) / 16;
-        const int nc = nb - c0 - lw;              // later columns of the panel
-        d4 w4[kOther / 16];
+        if constexpr (!RES) {
+            d4 w4[kOther / 16];
 #pragma unroll
-        for (int q = 0; q < kOther / 16; ++q) w4[q] = d4{0, 0, 0, 0};
-        if (nother > 0) {
-            // This lane's 16 rows of column cb + l % 16 in the wave's j-th 64 rows.
-            auto load_y = [&](int q, int j, double (&yv)[16]) __attribute__((always_inline)) {
-                const int cb = 16 * q < c0 ? 16 * q : 16 * q + lw;
-                const int base = 64 * wv + NT * j, row = base + 16 * lg;
-                const double* y = X + (long long)min(cb + l16, nb - 1) * ld;
-                if (base + 64 <= nr) {
+            for (int q = 0; q < kOther / 16; ++q) w4[q] = d4{0, 0, 0, 0};
+            if (nother > 0) {
+                auto product = [&](const double (&yv)[16], d4 w) __attribute__((always_inline)) {
 #pragma unroll
                     for (int u = 0; u < 16; u += 2) {
-                        const dpair_u t = *reinterpret_cast<const dpair_u*>(y + row + u);
-                        yv[u] = t[0];
-                        yv[u + 1] = t[1];
+                        const dpair t = *reinterpret_cast<const dpair*>(&sv[l16 * VS + 4 * u + 2 * lg]);
+                        w = mfma_f64_16x16x4(t[0], yv[u], w);
+                        w = mfma_f64_16x16x4(t[1], yv[u + 1], w);
                     }
-                } else {
-#pragma unroll
-                    for (int u = 0; u < 16; ++u) yv[u] = y[min(row + u, nr - 1)];
-                }
-            };
-            auto product = [&](const double (&yv)[16], d4 w) __attribute__((always_inline)) {
-#pragma unroll
-                for (int u = 0; u < 16; ++u) w = mfma_f64_16x16x4(sv[l16 * VS + 16 * lg + u], yv[u], w);
-                return w;
-            };
+                    return w;
+                };
 #pragma unroll 1
-            for (int j = 0; j < J; ++j) {
-                if (64 * wv + NT * j >= nr) break;
-                double v[kLW], yv[kOther / 16][16];
-                load_v(j, v);
+                for (int j = 0; j < J; ++j) {
+                    if (64 * wv + NT * j >= nr) break;
+                    double v[kLW], yv[kOther / 16][16];
+                    load_v(j, v);
+#pragma unroll
+                    for (int q = 0; q < kOther / 16; ++q)
+                        if (q < nblk) load_tile(tile_col(q), 64 * wv + NT * j, yv[q]);
+                    stage(j, v);
+#pragma unroll
+                    for (int q = 0; q < kOther / 16; ++q)
+                        if (q < nblk) w4[q] = product(yv[q], w4[q]);
+                }
+                __builtin_amdgcn_wave_barrier();
 #pragma unroll
                 for (int q = 0; q < kOther / 16; ++q)
-                    if (q < nblk) load_y(q, j, yv[q]);
-                stage(j, v);
 #pragma unroll
-                for (int q = 0; q < kOther / 16; ++q)
-                    if (q < nblk) w4[q] = product(yv[q], w4[q]);
+                    for (int e = 0; e < 4; ++e) sv[Mfma<double>::row(lane, e) * kOther + 16 * q + l16] = w4[q][e];
             }
-            __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int q = 0; q < kOther / 16; ++q)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) sv[Mfma<double>::row(lane, e) * kOther + 16 * q + l16] = w4[q][e];
         }
         __syncthreads();
-        // T_s: T[i][c] = -tau_c sum_{i <= l < c} T[i][l] (V^T V)[l][c], T[c][c] = tau_c (lane i: row i).
-        if (wv == NW - 1) {
-            double row[kLW];
-#pragma unroll
-            for (int c = 0; c < kLW; ++c) {
-                const double t = c < lw ? s_tau[c0 + c] : 0.0;
-                double s0 = 0.0, s1 = 0.0;
-                if (c < lw) {
-#pragma unroll
-                    for (int l = 0; l < c; ++l) {
-                        const double z = s_G[upper_at(c0 + l, c0 + c)];
-                        if (l & 1) s1 += row[l] * z;
-                        else s0 += row[l] * z;
-                    }
-                }
-                row[c] = l16 == c ? t : (l16 < c ? -t * (s0 + s1) : 0.0);
-            }
-            if (lane < kLW) {
-#pragma unroll
-                for (int c = 0; c < kLW; ++c) s_Ts[leaf][lane][c] = row[c];
-            }
+        if constexpr (!RES) {
+            if (wv == TW) leaf_t(s_G, s_tau, c0, lw, l16, s_Ts[leaf]);
         }
         if (nother > 0) {
             for (int t = tid; t < kLW * kOther; t += NT) {
-                double s = s_v[0][t];
+                double h = RES ? s_p[0][t] : s_v[0][t];
 #pragma unroll
-                for (int w = 1; w < NW; ++w) s += s_v[w][t];
-                s_W[t] = s;
+                for (int w = 1; w < NW; ++w) h += RES ? s_p[RES ? w : 0][t] : s_v[w][t];
+                s_W[t] = h;
             }
         }
         __syncthreads();
@@ -1004,117 +1176,175 @@ __global__ __launch_bounds__(NT) void panel_leaf_kernel(PanelArgs a) {
         if (g == 0) {                             // V_prev^T V_s
             for (int t = tid; t < c0 * lw; t += NT) {
                 const int q = t / lw, i = t % lw;
-                s_G[upper_at(q, c0 + i)] = s_W[i * kOther + q];
+                s_G[upper_at(q, c0 + i)] = s_W[i * kOther + prev0 + q];
             }
         }
-        if (nc > 0) {
+        if (nc > 0) {                             // a full leaf
             // -W2 = -T_s^T (V_s^T C): the MFMA leaves W2[l / 16 + 4 e][l % 16]
             // in element e of lane l, the operand of step e below.
-            d4 w2[kOther / 16];
+            d4 w2[NO];
 #pragma unroll
-            for (int q = 0; q < kOther / 16; ++q) {
+            for (int q = 0; q < NO; ++q) {
                 w2[q] = d4{0, 0, 0, 0};
-                if (16 * q < nc) {
+                if (q < nlater) {
 #pragma unroll
-                    for (int s = 0; s < 4; ++s)
-                        w2[q] = mfma_f64_16x16x4(-s_Ts[leaf][4 * s + lg][l16],
-                                                 s_W[(4 * s + lg) * kOther + min(c0 + 16 * q + l16, kOther - 1)], w2[q]);
+                    for (int e = 0; e < 4; ++e)
+                        w2[q] = mfma_f64_16x16x4(-s_Ts[leaf][4 * e + lg][l16],
+                                                 s_W[(4 * e + lg) * kOther + min(later0 + kLW * q + l16, kOther - 1)],
+                                                 w2[q]);
                 }
             }
-            // C goes through the MFMA 16 columns x 16 rows at a time, the next
-            // tile's loads issued before this tile's stores.  Rows past the slab
-            // and columns past the panel load valid addresses and are not stored.
-            unsigned long long off[kOther / 4];   // column offsets of this lane
+            if constexpr (RES) {
+                // C -= V_s W2 on the tiles as they are: their elements 4 t .. 4 t + 3 are
+                // the MFMA's rows l / 16 + 4 e, so its row i is row 16 t + pr of the 64.
+                if (64 * wv < nr) {
+                    const int pr = 8 * (l16 >> 3) + 2 * (l16 & 3) + ((l16 >> 2) & 1);
 #pragma unroll
-            for (int q = 0; q < kOther / 4; ++q)
-                off[q] = (unsigned long long)(unsigned)min(4 * q + lg, nc - 1) * (unsigned)ld;
-            double* const Cl = X + (long long)(c0 + lw) * ld;
-            auto load_c = [&](int row, d4 (&cv)[kOther / 16]) __attribute__((always_inline)) {
-                const double* p = Cl + min(row, nr - 1);
+                    for (int t = 0; t < 4; ++t) {
+                        double av[4];
 #pragma unroll
-                for (int q = 0; q < kOther / 16; ++q)
-                    if (16 * q < nc) {
+                        for (int e = 0; e < 4; ++e) av[e] = sv[(4 * e + lg) * VS + 16 * t + pr];
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) cv[q][e] = p[off[4 * q + e]];
+                        for (int q = 0; q < NO; ++q)
+                            if (q < nlater) {
+                                d4 x = d4{y[q][4 * t], y[q][4 * t + 1], y[q][4 * t + 2], y[q][4 * t + 3]};
+#pragma unroll
+                                for (int e = 0; e < 4; ++e) x = mfma_f64_16x16x4(av[e], w2[q][e], x);
+#pragma unroll
+                                for (int e = 0; e < 4; ++e) y[q][4 * t + e] = x[e];
+                            }
                     }
-            };
-#pragma unroll 1
-            for (int j = 0; j < J; ++j) {
-                const int base = 64 * wv + NT * j;
-                if (base >= nr) break;
-                double v[kLW];
-                d4 cv[2][kOther / 16];
-                load_v(j, v);
-                load_c(base + l16, cv[0]);
-                stage(j, v);
+                }
+                // The next leaf, a row per lane; the other tiles move up, V_s last
+                // (a wave without rows keeps zeros).
+                __builtin_amdgcn_wave_barrier();
 #pragma unroll
-                for (int rt = 0; rt < 4; ++rt) {
-                    const int row = base + 16 * rt + l16;
-                    if (rt < 3) load_c(row + 16, cv[(rt + 1) & 1]);
-                    double bv[4];
+                for (int u = 0; u < kLW; u += 2) {
+                    dpair* const at = reinterpret_cast<dpair*>(&sv[l16 * VS + 4 * u + 2 * lg]);
+                    const dpair v = *at;
+                    *at = dpair{y[0][u], y[0][u + 1]};
 #pragma unroll
-                    for (int s = 0; s < 4; ++s) bv[s] = sv[(4 * s + lg) * VS + 16 * rt + l16];
-                    double* p = Cl + row;
+                    for (int q = 0; q + 1 < NO; ++q) {
+                        y[q][u] = y[q + 1][u];
+                        y[q][u + 1] = y[q + 1][u + 1];
+                    }
+                    y[NO - 1][u] = 64 * wv < nr ? v[0] : 0.0;
+                    y[NO - 1][u + 1] = 64 * wv < nr ? v[1] : 0.0;
+                }
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int q = 0; q < kLW; ++q) xr[0][q] = sv[q * VS + lane];
+            } else {
+                // C goes through the MFMA 16 columns x 16 rows at a time, the next
+                // tile's loads issued before this tile's stores.  Rows past the slab
+                // and columns past the panel load valid addresses and are not stored.
+                unsigned long long off[kOther / 4];   // column offsets of this lane
+#pragma unroll
+                for (int q = 0; q < kOther / 4; ++q)
+                    off[q] = (unsigned long long)(unsigned)min(4 * q + lg, nc - 1) * (unsigned)ld;
+                double* const Cl = X + (long long)(c0 + lw) * ld;
+                auto load_c = [&](int row, d4 (&cv)[kOther / 16]) __attribute__((always_inline)) {
+                    const double* p = Cl + min(row, nr - 1);
 #pragma unroll
                     for (int q = 0; q < kOther / 16; ++q)
                         if (16 * q < nc) {
-                            d4& c = cv[rt & 1][q];
 #pragma unroll
-                            for (int s = 0; s < 4; ++s) c = mfma_f64_16x16x4(w2[q][s], bv[s], c);
-                            if (row < nr) {
-                                if (16 * q + 16 <= nc) {
+                            for (int e = 0; e < 4; ++e) cv[q][e] = p[off[4 * q + e]];
+                        }
+                };
+#pragma unroll 1
+                for (int j = 0; j < J; ++j) {
+                    const int base = 64 * wv + NT * j;
+                    if (base >= nr) break;
+                    double v[kLW];
+                    d4 cv[2][kOther / 16];
+                    load_v(j, v);
+                    load_c(base + l16, cv[0]);
+                    stage(j, v);
 #pragma unroll
-                                    for (int e = 0; e < 4; ++e) p[off[4 * q + e]] = c[e];
-                                } else {
+                    for (int rt = 0; rt < 4; ++rt) {
+                        const int row = base + 16 * rt + l16;
+                        if (rt < 3) load_c(row + 16, cv[(rt + 1) & 1]);
+                        double bv[4];
 #pragma unroll
-                                    for (int e = 0; e < 4; ++e)
-                                        if (16 * q + 4 * e + lg < nc) p[off[4 * q + e]] = c[e];
+                        for (int s = 0; s < 4; ++s) bv[s] = sv[(4 * s + lg) * VS + 16 * rt + l16];
+                        double* p = Cl + row;
+#pragma unroll
+                        for (int q = 0; q < kOther / 16; ++q)
+                            if (16 * q < nc) {
+                                d4& c = cv[rt & 1][q];
+#pragma unroll
+                                for (int s = 0; s < 4; ++s) c = mfma_f64_16x16x4(w2[q][s], bv[s], c);
+                                if (row < nr) {
+                                    if (16 * q + 16 <= nc) {
+#pragma unroll
+                                        for (int e = 0; e < 4; ++e) p[off[4 * q + e]] = c[e];
+                                    } else {
+#pragma unroll
+                                        for (int e = 0; e < 4; ++e)
+                                            if (16 * q + 4 * e + lg < nc) p[off[4 * q + e]] = c[e];
+                                    }
                                 }
                             }
-                        }
+                    }
                 }
             }
         }
-        __syncthreads();
+        if constexpr (!RES) __syncthreads();
     }
+    __syncthreads();                              // the columns are in memory
     if (g != 0) return;
     // The first workgroup holds the top block: R's diagonal block saved, V
     // made explicit (1 on the diagonal, 0 above), so that the GEMMs can use
     // the stored panel as V.
     double* Rd = a.Rd + b * a.srd;
-    for (int e = tid; e < kNB * kNB; e += NT) {
-        const int i = e % kNB, j = e / kNB;
-        const bool in = i < nb && j < nb && i < a.L;
-        const double v = in ? X[i + j * ld] : 0.0;
-        Rd[e] = (in && i <= j) ? v : 0.0;
-        if (in && i <= j) X[i + j * ld] = (i == j) ? 1.0 : 0.0;
+    {
+        double v[kNB * kNB / NT];                 // all loads in flight, from valid addresses
+#pragma unroll
+        for (int u = 0; u < kNB * kNB / NT; ++u) {
+            const int e = tid + u * NT, i = e % kNB, j = e / kNB;
+            v[u] = X[min(i, min(nb, a.L) - 1) + (long long)min(j, nb - 1) * ld];
+        }
+#pragma unroll
+        for (int u = 0; u < kNB * kNB / NT; ++u) {
+            const int e = tid + u * NT, i = e % kNB, j = e / kNB;
+            const bool upper = i < nb && j < nb && i < a.L && i <= j;
+            Rd[e] = upper ? v[u] : 0.0;
+            if (upper) X[i + j * ld] = (i == j) ? 1.0 : 0.0;
+        }
     }
     // T from the leaves' T_s and V^T V: T12 = -T1 (V1^T V2) T2 for 16 and 32
     // columns a side, on the matrix cores.
     double* const T = s_v[0];                     // T[i][j] at i + j TS
-    for (int e = tid; e < kNB * TS; e += NT) {
-        const int i = e % TS, j = e / TS;
-        T[e] = (i < kNB && i / kLW == j / kLW && j / kLW * kLW < nb) ? s_Ts[j / kLW][i % kLW][j % kLW] : 0.0;
+#pragma unroll
+    for (int u = 0; u < kNB * kNB / NT; ++u) {
+        const int e = tid + u * NT, i = e % kNB, j = e / kNB;
+        const double x = s_Ts[j / kLW][i % kLW][j % kLW];
+        T[i + j * TS] = keep_if(x, opaque(i / kLW == j / kLW && j / kLW * kLW < nb ? -1 : 0));
     }
     __syncthreads();
-    for (int s = kLW; s < kNB; s *= 2) {
+    auto merge = [&](auto width) __attribute__((always_inline)) {
+        constexpr int s = decltype(width)::value;
         const int ts = s / 16, per = ts * ts, total = kNB / (2 * s) * per;   // 2, 4 tiles
         const int o = wv / per * 2 * s, ti = wv % per % ts * 16, tj = wv % per / ts * 16;
+#pragma unroll
         for (int phase = 0; phase < 2; ++phase) {
             d4 acc = d4{0, 0, 0, 0};
             if (wv < total) {
+                double x[kNB / 8], yv[kNB / 8];   // all operands in flight
+#pragma unroll
                 for (int k = 0; k < s; k += 4) {
-                    double x, y;
                     if (phase == 0) {             // Y = (V1^T V2) T2 into the place of T12
                         const int i = o + ti + l16, l = o + s + k + lg;
-                        x = l < nb ? s_G[upper_at(i, l)] : 0.0;
-                        y = T[o + s + k + lg + (o + s + tj + l16) * TS];
+                        x[k / 4] = keep_if(s_G[upper_at(i, l)], opaque(l < nb ? -1 : 0));
+                        yv[k / 4] = T[o + s + k + lg + (o + s + tj + l16) * TS];
                     } else {
-                        x = -T[o + ti + l16 + (o + k + lg) * TS];
-                        y = T[o + k + lg + (o + s + tj + l16) * TS];
+                        x[k / 4] = -T[o + ti + l16 + (o + k + lg) * TS];
+                        yv[k / 4] = T[o + k + lg + (o + s + tj + l16) * TS];
                     }
-                    acc = mfma_f64_16x16x4(x, y, acc);
                 }
+#pragma unroll
+                for (int k = 0; k < s; k += 4) acc = mfma_f64_16x16x4(x[k / 4], yv[k / 4], acc);
             }
             __syncthreads();
             if (wv < total) {
@@ -1124,7 +1354,10 @@ __global__ __launch_bounds__(NT) void panel_leaf_kernel(PanelArgs a) {
             }
             __syncthreads();
         }
-    }
+    };
+    merge(std::integral_constant<int, kLW>{});
+    merge(std::integral_constant<int, 2 * kLW>{});
+    static_assert(4 * kLW == kNB, "two levels of merges");
     double* Tb = a.T + b * a.st;
     for (int e = tid; e < kNB * kNB; e += NT) {
         const int i = e % kNB, j = e / kNB;
@@ -1236,9 +1469,9 @@ constexpr int kNumLeafVariants = sizeof(kLeafVariants) / sizeof(kLeafVariants[0]
 
 // One workgroup per matrix up to this many live rows.  Measured on gfx950, one
 // 64-column panel, one workgroup against 256-row workgroups with their column
-// exchange: 512 rows 141 against 213 us, 1024 rows 206 against 222 us (one
-// matrix or eight alike), 2048 rows 420 against 220 us.
-constexpr int kSoloRows = 1024;
+// exchange: 513 rows 155 against 166 us, 764 rows 170 against 172, 1024 rows 194
+// against 166-176 (one matrix or eight alike).
+constexpr int kSoloRows = 768;
 
 // Rows each workgroup owns when the slab stays in global memory.
 constexpr int kPanelRowsTarget = 256;
@@ -1246,8 +1479,8 @@ constexpr int kPanelRowsTarget = 256;
 // Panels of the solves of zolo_pd_batched with at most this many live rows
 // take one workgroup per matrix: an ordinary launch on the solve's own
 // stream, instead of a cooperative launch on the panel stream that all
-// concurrent solves share: 420 us at 2048 rows where a cooperative panel takes
-// 220, but the panels of sixteen solves overlap.
+// concurrent solves share: about 410 us at 2048 rows where a cooperative panel takes
+// 180, but the panels of sixteen solves overlap.
 constexpr int kSinglePanelRows = 2048;
 
 // At most this many workgroups share a matrix's panel: every column polls
@@ -1290,24 +1523,35 @@ int global_coresident() {
     return v;
 }
 
-// One workgroup per matrix where that is enough (above), else the smallest
-// workgroups that all fit on the GPU at once, at most kPanelMaxG a matrix: 256
-// rows each measured fastest wherever they fit (one matrix of 4160 rows: 254 us
-// against 269 with 512 rows and 323 with 1024; 8256 rows: 290, 298, 325), and
-// eight matrices of 8256 rows, 264 such workgroups for 256 CUs, take 512 rows
-// each.  Matrices too tall for the last shape go to panel_kernel.
+// Shapes that keep the whole panel in registers: one row per thread.
+inline bool resident(int v) { return kLeafVariants[v].rows == kLeafVariants[v].nt; }
+// The grid that puts each matrix's G workgroups on one XCD (workgroups are dealt
+// to the XCDs round-robin; those without a matrix leave at once).
+inline long long panel_spread(int G, int batch) { return (long long)kNumXcd * ((batch + kNumXcd - 1) / kNumXcd) * G; }
+
+// One workgroup per matrix where that is enough (above), else a resident shape
+// whose grid can put each matrix on one XCD, 256 rows a workgroup before 512, else
+// the smallest workgroups that all fit on the GPU at once, at most kPanelMaxG a
+// matrix.  The exchange within one XCD's L2 against across them, 64-column panel:
+// 2048 rows 179 against 195 us, 4160 rows 214 against 232, eight of 8256 rows (512
+// a workgroup) 249 against 266; one of 8256 rows with 512-row workgroups on one XCD
+// 246 against 270 with 256 rows across all.  Matrices too tall for the last shape go to
+// panel_kernel.
 Geometry panel_geometry(int L, int batch, bool single) {
     if (L <= (single ? kSinglePanelRows : kSoloRows)) {
         int v = 0;
         while (L > kLeafVariants[v].rows) ++v;
         return {1, L, v};
     }
-    for (int v = 0; v < kNumLeafVariants; ++v) {
-        int G = (L + kLeafVariants[v].rows - 1) / kLeafVariants[v].rows;
-        if (G > kPanelMaxG || G * (long long)batch > leaf_coresident(v)) continue;
-        const int rows = ((L + G - 1) / G + 15) / 16 * 16;
-        G = (L + rows - 1) / rows;
-        return {G, rows, v};
+    for (int pass = 0; pass < 2; ++pass) {
+        for (int v = 0; v < kNumLeafVariants; ++v) {
+            int G = (L + kLeafVariants[v].rows - 1) / kLeafVariants[v].rows;
+            if (pass == 0 && (!resident(v) || panel_spread(G, batch) > leaf_coresident(v))) continue;
+            if (G > kPanelMaxG || G * (long long)batch > leaf_coresident(v)) continue;
+            const int rows = ((L + G - 1) / G + 15) / 16 * 16;
+            G = (L + rows - 1) / rows;
+            return {G, rows, v};
+        }
     }
     const int target = kPanelRowsTarget;
     int G = (L + target - 1) / target;
@@ -1391,7 +1635,9 @@ hipError_t run_panel(int m, int e, int p, int nb, double* M, long long ld, long 
     // The partial-sum and flag buffers hold max_coresident workgroups.
     if ((long long)geo.G * batch > w.max_coresident && geo.G > 1) return hipErrorInvalidValue;
     PanelArgs pa;
-    pa.L = L; pa.nb = nb; pa.G = geo.G; pa.rows_per_wg = geo.rows;
+    pa.L = L; pa.nb = nb; pa.G = geo.G; pa.rows_per_wg = geo.rows; pa.batch = batch;
+    const long long spread = panel_spread(geo.G, batch);
+    pa.local = geo.variant >= 0 && geo.G > 1 && spread <= leaf_coresident(geo.variant);
     pa.P = M + p0 + (long long)p0 * ld; pa.ld = ld; pa.sp = sm;
     pa.T = w.T + (long long)p * kNB * kNB; pa.st = stT;
     pa.Rd = w.Rd + (long long)p * kNB * kNB; pa.srd = stT;
@@ -1425,7 +1671,7 @@ hipError_t run_panel(int m, int e, int p, int nb, double* M, long long ld, long 
     StatScope sc(geo.variant >= 0 ? "panel_leaf<workgroups>" : "panel_kernel<global>", ps, flops, bytes);
     if (geo.variant >= 0) {
         const LeafVariant& v = kLeafVariants[geo.variant];
-        err = hipLaunchCooperativeKernel(v.multi, dim3(pa.G * batch), dim3(v.nt), args, 0, ps);
+        err = hipLaunchCooperativeKernel(v.multi, dim3(pa.local ? (int)spread : pa.G * batch), dim3(v.nt), args, 0, ps);
     } else {
         err = hipLaunchCooperativeKernel((const void*)panel_kernel, dim3(pa.G * batch), dim3(kPT), args, 0, ps);
     }

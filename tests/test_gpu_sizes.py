@@ -67,6 +67,16 @@ def test_panel_shapes(z, m, n, batch, stacked):
     check_qr(z, m, n, pivots, batch, 31 * m + n)
 
 
+@pytest.mark.parametrize("m,n,batch,stacked", [
+    (70, 18, 1, False), (64, 33, 2, True), (250, 47, 1, False), (255, 49, 1, True), (400, 63, 2, False),
+    (512, 31, 1, False), (704, 65, 2, True), (769, 40, 9, False), (769, 64, 1, False), (900, 100, 1, True)])
+def test_panel_widths_and_placement(z, m, n, batch, stacked):
+    # One to four leaves, whole and cut short, in one workgroup and in several;
+    # more matrices than XCDs.
+    pivots = [0.7 / (b + 1) for b in range(batch)] if stacked else None
+    check_qr(z, m, n, pivots, batch, 17 * m + n)
+
+
 def test_panel_beyond_the_tallest_shape(z):
     # 16 matrices of 33 000 rows: more 2048-row slabs than the GPU holds at once.
     check_qr(z, 33000, 66, None, 16, 5)
