@@ -19,6 +19,8 @@
 #include "misc.hpp"
 #include "stats.hpp"
 
+#include <limits>
+
 namespace zolo {
 namespace {
 
@@ -56,84 +58,123 @@ __device__ void load_upper(const T* Z, long long ld, int kb, T (*S)[kB + 1]) {
     }
 }
 
+// Inverse of the 16 x 16 diagonal block at o of the upper triangular S into Si (LDS),
+// by one wave: lane j of each row of 16 lanes back-substitutes column j.  rcp
+// holds 1 / S[i][i].  Each entry found goes to all the sums above it, which are
+// independent of each other (a sum per entry at a time is one chain of 120
+// operations: 11.4k cycles for the four blocks at once, now 2.5k).
+template <class T, int K>
+__device__ __forceinline__ void inverse16_steps(const T (*S)[kB + 1], const T* rcp, T (*Si)[kB + 1], T (&x)[kDB],
+                                                const T (&z)[kDB], T r, int o, int l16) {
+    if constexpr (K >= 0) {
+        T zn[kDB], rn = 0;
+        if constexpr (K > 0) {
+            rn = rcp[o + K - 1];
+#pragma unroll
+            for (int i = 0; i < K - 1; ++i) zn[i] = S[o + i][o + K - 1];
+        }
+        const T xk = K <= l16 ? x[K] * r : (T)0;
+        Si[o + K][o + l16] = xk;                  // the four rows of lanes alike
+#pragma unroll
+        for (int i = 0; i < K; ++i) x[i] -= z[i] * xk;
+        __builtin_amdgcn_sched_barrier(0);        // one column's loads ahead (registers)
+        inverse16_steps<T, K - 1>(S, rcp, Si, x, zn, rn, o, l16);
+    }
+}
+template <class T>
+__device__ __forceinline__ void inverse16(const T (*S)[kB + 1], const T* rcp, T (*Si)[kB + 1], int o, int l16) {
+    T x[kDB], z[kDB];
+#pragma unroll
+    for (int i = 0; i < kDB; ++i) x[i] = i == l16 ? (T)1 : (T)0;
+#pragma unroll
+    for (int i = 0; i < kDB - 1; ++i) z[i] = S[o + i][o + kDB - 1];
+    inverse16_steps<T, kDB - 1>(S, rcp, Si, x, z, rcp[o + kDB - 1], o, l16);
+}
+// A 16 x 16 tile of S12 Si22 (phase 0) or -Si11 times it (phase 1) for blocks of
+// W at o and o + W, the tile's rows and columns at ti and tj, on the matrix cores.
+template <class T, int W>
+__device__ __forceinline__ typename Mfma<T>::acc merge_tile(const T (*S)[kB + 1], const T (*Si)[kB + 1], int phase, int o,
+                                                            int ti, int tj, int l16, int lg) {
+    T x[W / 4], y[W / 4];                         // all operands in flight
+#pragma unroll
+    for (int k = 0; k < W; k += 4) {
+        x[k / 4] = phase == 0 ? S[o + ti + l16][o + W + k + lg] : -Si[o + ti + l16][o + k + lg];
+        y[k / 4] = phase == 0 ? Si[o + W + k + lg][o + W + tj + l16] : Si[o + k + lg][o + W + tj + l16];
+    }
+    typename Mfma<T>::acc acc = {0, 0, 0, 0};
+#pragma unroll
+    for (int k = 0; k < W; k += 4) acc = Mfma<T>::run(x[k / 4], y[k / 4], acc);
+    return acc;
+}
+template <class T, int W>
+__device__ __forceinline__ void merge_store(T (*Si)[kB + 1], const typename Mfma<T>::acc& acc, int o, int ti, int tj,
+                                            int lane) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) Si[o + ti + Mfma<T>::row(lane, e)][o + W + tj + (lane & 15)] = acc[e];
+}
+// Si12 = -Si11 (S12 Si22): blocks of 16 by one wave, of 32 by the workgroup.
+template <class T>
+__device__ __forceinline__ void merge16(const T (*S)[kB + 1], T (*Si)[kB + 1], int o, int lane) {
+    for (int phase = 0; phase < 2; ++phase) {
+        const typename Mfma<T>::acc acc = merge_tile<T, kDB>(S, Si, phase, o, 0, 0, lane & 15, lane >> 4);
+        __builtin_amdgcn_wave_barrier();
+        merge_store<T, kDB>(Si, acc, o, 0, 0, lane);
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+template <class T>
+__device__ __forceinline__ void merge32(const T (*S)[kB + 1], T (*Si)[kB + 1], int wave, int lane) {
+    const int ti = wave % 2 * kDB, tj = wave / 2 * kDB;
+    for (int phase = 0; phase < 2; ++phase) {
+        const typename Mfma<T>::acc acc = merge_tile<T, 2 * kDB>(S, Si, phase, 0, ti, tj, lane & 15, lane >> 4);
+        __syncthreads();
+        merge_store<T, 2 * kDB>(Si, acc, 0, ti, tj, lane);
+        __syncthreads();
+    }
+}
+
 // Inverse of the upper-triangular 64 x 64 matrix S (LDS; identity beyond the
-// matrix) into Si (LDS), by the workgroup's 256 threads; rcp holds 1 / S[i][i].
-// The four 16 x 16 diagonal blocks are inverted at once (wave w inverts block
-// w: lane j back-substitutes column j in registers); then neighbouring blocks
-// of 16 and of 32 are merged on the matrix cores,
-//     Si12 = -Si11 (S12 Si22).
+// matrix) into Si (LDS), by the workgroup's 256 threads: the four 16 x 16
+// diagonal blocks at once, then neighbouring blocks of 16 and of 32 merged.
 template <class T>
 __device__ void lds_upper_inverse(const T (*S)[kB + 1], const T* rcp, T (*Si)[kB + 1]) {
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, l16 = lane & 15, lg = lane >> 4;
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     for (int e = tid; e < kB * kB; e += 256) {
         const int i = e / kB, j = e % kB;
         if (i / kDB != j / kDB) Si[i][j] = 0;
     }
-    {
-        const int o = w * kDB;
-        T x[kDB];
-#pragma unroll
-        for (int i = kDB - 1; i >= 0; --i) {
-            T s0 = (i == l16) ? (T)1 : (T)0, s1 = 0;
-#pragma unroll
-            for (int k = i + 1; k < kDB; ++k) {
-                if (k & 1) s1 -= S[o + i][o + k] * x[k];
-                else s0 -= S[o + i][o + k] * x[k];
-            }
-            x[i] = i <= l16 ? (s0 + s1) * rcp[o + i] : (T)0;
-        }
-        if (lane < kDB) {
-#pragma unroll
-            for (int i = 0; i < kDB; ++i) Si[o + i][o + lane] = x[i];
-        }
-    }
+    inverse16<T>(S, rcp, Si, w * kDB, lane & 15);
     __syncthreads();
-    for (int s = kDB; s < kB; s *= 2) {
-        const int ts = s / kDB, per = ts * ts, total = kB / (2 * s) * per;   // 2, 4 tiles
-        const int o = w / per * 2 * s, ti = w % per % ts * kDB, tj = w % per / ts * kDB;
-        for (int phase = 0; phase < 2; ++phase) {   // S12 Si22 into the place of Si12, then -Si11 times it
-            typename Mfma<T>::acc acc = {0, 0, 0, 0};
-            if (w < total) {
-                for (int k = 0; k < s; k += 4) {
-                    const T x = phase == 0 ? S[o + ti + l16][o + s + k + lg] : -Si[o + ti + l16][o + k + lg];
-                    const T y = phase == 0 ? Si[o + s + k + lg][o + s + tj + l16] : Si[o + k + lg][o + s + tj + l16];
-                    acc = Mfma<T>::run(x, y, acc);
-                }
-            }
-            __syncthreads();
-            if (w < total) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) Si[o + ti + Mfma<T>::row(lane, e)][o + s + tj + l16] = acc[e];
-            }
-            __syncthreads();
-        }
-    }
+    if (w < 2) merge16<T>(S, Si, 2 * w * kDB, lane);
+    __syncthreads();
+    merge32<T>(S, Si, w, lane);
 }
 
 // sqrt(d) and 1 / sqrt(d) of a positive, finite d: the hardware estimate
-// refined to the last bit or so (the library's square root and divide, one
-// after the other, are most of a pivot's latency).
-__device__ inline void sqrt_rcp(double d, double& r, double& ri) {
-    if (d < 1e-280) {   // the residuals below would underflow
-        r = sqrt(d);
-        ri = 1.0 / r;
-        return;
-    }
+// refined to the last bit or so, without a branch, 1 / sqrt(d) first, which the
+// next pivot waits for.  Small d is scaled by an even power of two, so that no
+// residual underflows.
+__device__ __forceinline__ void sqrt_rcp(double d, double& r, double& ri) {
+    const bool small = d < 0x1p-900;
+    d *= small ? 0x1p512 : 1.0;
     const double y = __builtin_amdgcn_rsq(d);
     double g = d * y, h = 0.5 * y;
-    double t = fma(-h, g, 0.5);
-    g = fma(g, t, g);
+    const double t = fma(-h, g, 0.5);
     h = fma(h, t, h);
-    t = fma(-g, g, d);
-    g = fma(t, h, g);
-    t = fma(-g, g, d);
-    r = fma(t, h, g);
     const double z = h + h;
-    ri = fma(fma(-r, z, 1.0), z, z);
+    const double x = fma(fma(-(d * z), z, 1.0), h, z);
+    g = d * x;
+    r = fma(fma(-g, g, d), h, g) * (small ? 0x1p-256 : 1.0);
+    ri = x * (small ? 0x1p256 : 1.0);
 }
-__device__ inline void sqrt_rcp(float d, float& r, float& ri) {
-    r = sqrtf(d);
-    ri = 1.0f / r;
+__device__ __forceinline__ void sqrt_rcp(float d, float& r, float& ri) {
+    const bool small = d < 0x1p-96f;
+    d *= small ? 0x1p64f : 1.0f;
+    const float y = __builtin_amdgcn_rsqf(d), h = 0.5f * y;
+    const float x = fmaf(fmaf(-(d * y), y, 1.0f), h, y);
+    const float g = d * x;
+    r = fmaf(fmaf(-g, g, d), h, g) * (small ? 0x1p-32f : 1.0f);
+    ri = x * (small ? 0x1p32f : 1.0f);
 }
 
 // Upper Cholesky of the kb x kb diagonal block at (k0, k0) of each matrix
@@ -142,24 +183,35 @@ __device__ inline void sqrt_rcp(float d, float& r, float& ri) {
 // in registers, the diagonal block and the row panel to its right in the same
 // instructions (the multipliers of a row reach all lanes by readlane); then the
 // rows below take their rank-16 update on the matrix cores, a 16 x 16 tile per
-// wave.  Rows and columns past kb are those of the identity.  A non-positive
-// pivot is reported (1-based global column) and replaced by 1 so that every
-// wave finishes; the caller discards the result.  Bound: latency of the 64
-// dependent pivots.  One launch in a solve takes 28 us (FP32: 23); with a block at
-// a time factored, its panel solved one thread per column and the trailing and
-// inverse blocks summed element by element it took 58 (51): 2.8 of the 10.9 ms of a
-// 3001 x 1501 solve by Cholesky-type steps, 1.6 of 4.1 ms of four FP32 factors at
-// n = 2000.
+// wave.  While wave 0 factors, the others invert and store the blocks before and
+// merge the first two inverses.  Rows and columns past kb are those of the
+// identity.  A non-positive pivot is reported (1-based global column) and
+// replaced by 1 so that every wave finishes; the caller discards the result.
+// The pivots run without a branch, so that one's reciprocal square root overlaps
+// the updates of the one before.  Bound: latency of the 64 dependent pivots.  One
+// launch in a solve takes 19 us (FP32: 15); with inverse, merges and stores after the
+// factor and two branches per pivot it took 28 (23), with the panel of a block
+// solved one thread per column and sums element by element 58 (51): 3001 x 1501 by
+// Cholesky-type steps 10.9, 6.8 and 6.3 ms, four FP32 factors at n = 2000 4.1, 3.2
+// and 2.9 ms.
 template <class T>
 __global__ __launch_bounds__(256) void potrf_diag_kernel(int k0, int kb, T* Z, long long ldz, long long sz,
                                                          int* info, T* inv, long long ldi, long long si) {
     __shared__ T S[kB][kB + 1];
     __shared__ T Si[kB][kB + 1];
     __shared__ T s_rcp[kB];
-    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, lg = lane >> 4;
+    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     T* Zb = Z + b * sz + k0 + (long long)k0 * ldz;
     load_upper<T>(Zb, ldz, kb, S);
     __syncthreads();
+    // Rows [o, o + 16) of R to memory by `nw` waves, this one the w-th: 16 rows of 4
+    // columns at a time.
+    auto store_rows = [&](int o, int w, int nw) __attribute__((always_inline)) {
+        const int i = o + l16;
+        for (int j = 4 * w + lg; j < kb; j += 4 * nw)
+            if (i < kb) Zb[i + (long long)j * ldz] = i <= j ? S[i][j] : (T)0;
+    };
     int bad = 0;
 #pragma unroll 1
     for (int jb = 0; jb < kB; jb += kDB) {
@@ -170,19 +222,29 @@ __global__ __launch_bounds__(256) void potrf_diag_kernel(int k0, int kb, T* Z, l
 #pragma unroll
             for (int i = 0; i < kDB; ++i) {
                 T d = lane_bcast(c[i], jb + i);
-                if (!(d > (T)0) || !isfinite(d)) {
-                    if (bad == 0) bad = k0 + jb + i + 1;
-                    d = 1;
-                }
+                asm("" : "+v"(d));                // tested in vector registers: no turns to the scalar unit
+                const bool ok = d > (T)0 && d <= std::numeric_limits<T>::max();
+                bad = ok || bad != 0 ? bad : k0 + jb + i + 1;
+                d = ok ? d : (T)1;
                 T r, ri;
                 sqrt_rcp(d, r, ri);
                 c[i] = lane == jb + i ? r : c[i] * ri;
-                if (lane == 0) s_rcp[jb + i] = ri;
+                s_rcp[jb + i] = ri;               // all lanes alike
 #pragma unroll
                 for (int l = i + 1; l < kDB; ++l) c[l] -= lane_bcast(c[i], jb + l) * c[i];   // R[i][jb + l]
             }
 #pragma unroll
             for (int i = 0; i < kDB; ++i) S[jb + i][lane] = lane >= jb + i ? c[i] : (T)0;
+        } else if (jb == 0) {
+            for (int e = tid - 64; e < kB * kB; e += 192) {
+                const int i = e / kB, j = e % kB;
+                if (i / kDB != j / kDB) Si[i][j] = 0;
+            }
+        } else if (wave == 1) {
+            inverse16<T>(S, s_rcp, Si, jb - kDB, l16);
+        } else {
+            store_rows(jb - kDB, wave - 2, 2);
+            if (jb == kB - kDB && wave == 2) merge16<T>(S, Si, 0, lane);
         }
         __syncthreads();
         // Rows below (upper tiles): S[i][j] -= sum_k R[jb+k][i] R[jb+k][j].
@@ -203,16 +265,18 @@ __global__ __launch_bounds__(256) void potrf_diag_kernel(int k0, int kb, T* Z, l
         }
         __syncthreads();
     }
-    for (int e = tid; e < kb * kb; e += 256) {
-        const int i = e % kb, j = e / kb;
-        Zb[i + (long long)j * ldz] = (i <= j) ? S[i][j] : (T)0;
+    if (wave == 0) {
+        inverse16<T>(S, s_rcp, Si, kB - kDB, l16);
+        __builtin_amdgcn_wave_barrier();
+        merge16<T>(S, Si, 2 * kDB, lane);
+    } else {
+        store_rows(kB - kDB, wave - 1, 3);
     }
-    lds_upper_inverse<T>(S, s_rcp, Si);
-    T* wb = inv + b * si;
-    for (int e = tid; e < kB * kB; e += 256) {
-        const int i = e % kB, j = e / kB;
-        if (i < kb && j < kb) wb[i + j * ldi] = Si[i][j];
-    }
+    __syncthreads();
+    merge32<T>(S, Si, wave, lane);
+    T* wb = inv + b * si + lane;
+    if (lane < kb)
+        for (int j = wave; j < kb; j += 4) wb[(long long)j * ldi] = Si[lane][j];
     if (tid == 0 && bad != 0 && info[b] == 0) info[b] = bad;
 }
 
