@@ -77,6 +77,8 @@ hipError_t gemm(const SGemmDesc& d, hipStream_t stream);
 // With `pieces`, the pieces are left unsummed in `work` and *pieces says how
 // many there are (1: the product is in C as usual).
 hipError_t gemm_split(GemmDesc d, double* work, size_t work_elems, hipStream_t stream, int* pieces = nullptr);
+hipError_t gemm_few(const GemmDesc& d, double* work, size_t work_elems, hipStream_t stream);
+inline hipError_t gemm_few(const SGemmDesc& d, float*, size_t, hipStream_t stream) { return gemm(d, stream); }
 
 // Nonzeros of a trapezoidal operand with `r` rows (the side that is not k)
 // and depth k: "from diagonal" = zero where k < r-index (upper op(A), lower

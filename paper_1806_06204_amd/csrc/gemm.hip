@@ -1023,16 +1023,18 @@ hipError_t gemm(const SGemmDesc& d, hipStream_t s) { return gemm_dispatch(d, s);
 hipError_t gemm_split(GemmDesc d, double* work, size_t work_elems, hipStream_t s, int* pieces) {
     d.splitk = 1;
     d.keep_pieces = pieces != nullptr;
-    if (work != nullptr && d.batch2 == 1 && d.k >= 512 && d.m > 0 && d.n > 0 && d.batch > 0 &&
-        !(d.flags & kCUpperTiles)) {
+    // The sum over a reduced batch is part of the k-range.
+    const long long k = (long long)d.k * (d.reduce ? d.batch : 1);
+    if (work != nullptr && d.batch2 == 1 && k >= 384 && d.m > 0 && d.n > 0 && d.batch > 0 &&
+        (!(d.flags & kCUpperTiles) || (d.flags & kCStoreUpper))) {   // the sum reads what tiles were formed
         int bm, bn;
         tile_dims(pick_tile(d), bm, bn);
         const long long tiles = (long long)((d.m + bm - 1) / bm) * ((d.n + bn - 1) / bn) * (d.reduce ? 1 : d.batch);
         if (tiles < 1024) {
             long long sk = std::max(4LL, (1024 + tiles - 1) / tiles);
-            sk = std::min(sk, (long long)d.k / 512);             // at least 512 of k per piece
+            sk = std::min(sk, k / 512);                          // at least 512 of k per piece
             sk = std::min(sk, 32LL);
-            if (tiles * sk < 256) sk = std::max(sk, std::min({32LL, (long long)d.k / 128, (512 + tiles - 1) / tiles}));
+            if (tiles * sk < 256) sk = std::max(sk, std::min({32LL, k / 128, (512 + tiles - 1) / tiles}));
             const long long per = (long long)d.m * d.n * (d.reduce ? 1 : d.batch);
             if (sk * per > (long long)work_elems) sk = (long long)work_elems / per;
             if (sk > 1) {
@@ -1043,6 +1045,18 @@ hipError_t gemm_split(GemmDesc d, double* work, size_t work_elems, hipStream_t s
     }
     if (pieces) *pieces = d.splitk;
     return gemm_dispatch(d, s);
+}
+
+// The products of a solve's steps (Gram matrix, sum over the r factors, update of
+// X, H) with fewer tiles than CUs; those that fill the chip stay whole.  A k-range
+// of 384 in all is the shortest that gains: three factors of 256 x 128 25 us whole,
+// 11 + 5 in three pieces, and 256 (18 us whole) would not.  256 x 128 754 -> 712 us,
+// 1000 x 777 10.19 -> 9.70 ms, 32 small problems 23.1 -> 21.3 ms.
+hipError_t gemm_few(const GemmDesc& d, double* work, size_t work_elems, hipStream_t s) {
+    int bm, bn;
+    tile_dims(pick_tile(d), bm, bn);
+    if ((long long)((d.m + bm - 1) / bm) * ((d.n + bn - 1) / bn) * (d.reduce ? 1 : d.batch) >= 256) return gemm(d, s);
+    return gemm_split(d, work, work_elems, s);
 }
 
 }  // namespace zolo

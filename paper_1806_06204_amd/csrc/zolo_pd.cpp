@@ -209,15 +209,16 @@ void scalars_to_host(zolo_handle h, Work& w) {
     std::memset(w.iflags, 0, 64 * sizeof(int));
 }
 
-// G = X^T X (upper tiles; symmetric result in the upper triangle).
+// G = X^T X (upper tiles; symmetric result in the upper triangle); work: room for
+// pieces of it.
 template <class T>
-hipError_t gram(int m, int n, const T* X, long long ldx, T* G, hipStream_t st) {
+hipError_t gram(int m, int n, const T* X, long long ldx, T* G, T* work, size_t work_elems, hipStream_t st) {
     GemmDescT<T> g;
     g.m = n; g.n = n; g.k = m; g.transa = 1;
     g.A = X; g.lda = ldx; g.B = X; g.ldb = ldx;
     g.C = G; g.ldc = n;
     g.flags = kCUpperTiles | kCStoreUpper;
-    return gemm(g, st);
+    return gemm_few(g, work, work_elems, st);
 }
 
 struct StepCtx {
@@ -237,7 +238,7 @@ int chol_core(StepCtx& cx, const Coeffs& co, const CholBufs<T>& b, bool g_valid)
     hipStream_t st = cx.h->stream;
     const long long nn = (long long)n * n;
     if (!g_valid) {
-        HIPCHECK(gram<T>(m, n, b.X, m, b.G, st));
+        HIPCHECK(gram<T>(m, n, b.X, m, b.G, b.Z, (size_t)nn * r, st));
         cx.flops_exec += (double)m * n * n;
     }
     ShiftArgs sh;
@@ -259,13 +260,13 @@ int chol_core(StepCtx& cx, const Coeffs& co, const CholBufs<T>& b, bool g_valid)
     f.batch = r; f.reduce = 1; f.nalpha = r;
     for (int j = 0; j < r; ++j) f.alphas[j] = co.a[j];
     f.flags = kAUpper | kBLower | kCUpperTiles | kCStoreUpper;
-    HIPCHECK(gemm(f, st));
+    HIPCHECK(gemm_few(f, b.Z, (size_t)nn * r, st));   // Z (R_j) is not needed any more
     HIPCHECK(symmetrize<T>(n, b.G, n, b.F, n, 1, 1.0, st));
     GemmDescT<T> x;
     x.m = m; x.n = n; x.k = n;
     x.A = b.X; x.lda = m; x.B = b.F; x.ldb = n;
     x.C = b.Xn; x.ldc = m; x.alpha = co.mhat;
-    HIPCHECK(gemm(x, st));
+    HIPCHECK(gemm_few(x, b.Z, (size_t)nn * r, st));
     // One wait per step, with the whole step queued: after a breakdown Xn holds
     // garbage that the QR-type step replaces (X is as it was).
     if (int rc = wait(cx.h)) return rc;
@@ -345,7 +346,7 @@ int qr_step(StepCtx& cx, const Coeffs& co) {
     g.alpha = co.mhat; g.batch = r; g.reduce = 1; g.nalpha = r;
     for (int j = 0; j < r; ++j) g.alphas[j] = co.a[j] / piv[j];
     g.flags = cx.dense_qr ? 0u : kBLower;
-    HIPCHECK(gemm(g, st));
+    HIPCHECK(gemm_few(g, w.qr.splitk, w.qr.splitk_elems, st));
     if (cx.dense_qr) {
         const double M = (double)m + n, N = n;
         cx.flops_exec += r * (2.0 * (2.0 * M * N * N - 2.0 * N * N * N / 3.0) + 2.0 * m * N * N);
@@ -481,6 +482,7 @@ int pd_core(zolo_handle h, char* base, int m, int n, const double* A, int lda, d
     const bool mixed = opts.precision == 1;
     const bool dense_qr = opts.qr_variant == 1;
     Work w = layout(base, dense_qr ? m + n : m, n, rmax, h->panel_coresident, mixed);
+    const size_t stack = ((size_t)m + n) * n;      // doubles of Y that a step's products may use
     scalars_to_host(h, w);
     w.qr.panel_stream = h->panel_stream;
     w.qr.single_panels = h->single_panels;
@@ -633,7 +635,7 @@ int pd_core(zolo_handle h, char* base, int m, int n, const double* A, int lda, d
         } else {
             std::swap(w.X, w.Xn);
             if (l_pred >= kConverged) {
-                HIPFIN(gram(m, n, w.X, m, w.G, st));
+                HIPFIN(gram(m, n, w.X, m, w.G, w.Y, stack, st));
                 HIPFIN(orth2(n, w.G, n, w.part, w.scal, st));
                 if ((rc = wait(h))) return finish(rc);
                 cx.flops_exec += (double)m * n * n;
@@ -675,7 +677,7 @@ int pd_core(zolo_handle h, char* base, int m, int n, const double* A, int lda, d
     hg.m = n; hg.n = n; hg.k = m; hg.transa = 1;
     hg.A = w.X; hg.lda = m; hg.B = A; hg.ldb = lda;
     hg.C = w.F; hg.ldc = n;
-    HIPFIN(gemm(hg, st));
+    HIPFIN(gemm_few(hg, w.Y, stack, st));
     HIPFIN(symmetrize(n, w.F, n, H, ldh, 0, 0.0, st));
     cx.flops_exec += 2.0 * m * (double)n * n;
     inf.flops_paper += 2.0 * m * (double)n * n;
@@ -689,7 +691,7 @@ int pd_core(zolo_handle h, char* base, int m, int n, const double* A, int lda, d
         pg.C = w.Xn; pg.ldc = m;
         HIPFIN(gemm(pg, st));
         HIPFIN(frob2(m, n, A, lda, w.Xn, m, w.part, w.scal, st));
-        HIPFIN(gram(m, n, Qp, ldq, w.G, st));
+        HIPFIN(gram(m, n, Qp, ldq, w.G, w.Y, stack, st));
         HIPFIN(orth2(n, w.G, n, w.part, w.scal + 2, st));
         if ((rc = wait(h))) return finish(rc);
         inf.bwd_err = std::sqrt(w.scal[0]) / std::sqrt(w.scal[1]);

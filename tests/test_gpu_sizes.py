@@ -203,3 +203,17 @@ def test_products_at_odd_offsets(z, off, lda, ldb, ldc):
         c = buf["C"][off + b * (ldc * 97 + 2):][:ldc * n].reshape(n, ldc)[:, :m].T
         got = dv["C"].cpu().numpy()[off + b * (ldc * 97 + 2):][:ldc * n].reshape(n, ldc)[:, :m].T
         assert np.array_equal(got, a @ x + c)
+
+
+@pytest.mark.parametrize("m,n", [(128, 128), (384, 64), (500, 130), (383, 191), (700, 257), (1100, 321)])
+@pytest.mark.parametrize("cond", [3.0, 1e6])
+def test_steps_of_few_tiles(z, m, n, cond):
+    # The products of Cholesky-type (low condition) and QR-type steps in pieces.
+    # Stopping bound of the solver 5e-14 for the orthogonality, n eps for H.
+    A, U, s, V = W.svd_matrix(m, n, cond, 80 + m, 90 + n)
+    Q, H, info = z.pd(dev(A), alpha=1.0, l=0.9 / cond)
+    assert info["status"] == 0
+    Q, H = Q.cpu().numpy(), H.cpu().numpy()
+    assert np.linalg.norm(Q.T @ Q - np.eye(n)) / np.sqrt(n) <= 1e-13
+    assert np.linalg.norm(Q @ H - A) / np.linalg.norm(A) <= 1e-13
+    assert np.array_equal(H, H.T)
