@@ -37,7 +37,7 @@ constexpr double kEps = 1.1102230246251565e-16;   // unit roundoff 2^-53
 struct DeflateScan {
     double rho, tol;
     int k, K, ndef, nrot, prev;
-    double dprev, zprev;
+    double dprev, zprev, plast;   // plast: the last kept pole
     double *pole, *zp, *dval, *rc, *rs;
     int *src, *ri, *rj;
 
@@ -47,14 +47,14 @@ struct DeflateScan {
         tol = tol_;
         K = ndef = nrot = 0;
         prev = -1;
-        dprev = zprev = 0.0;
+        dprev = zprev = plast = 0.0;
     }
     // A rotation moves a pole by at most tol, so a kept pole can land on or
     // below its predecessor; it is then moved just above it (an eigenvalue
     // change below tol), which keeps the poles strictly ascending.
     ZOLO_HD void keep(int t, double d, double z) {
-        if (K > 0 && !(d > pole[K - 1])) d = nextafter(pole[K - 1], INFINITY);
-        pole[K] = d;
+        if (K > 0 && !(d > plast)) d = nextafter(plast, INFINITY);
+        pole[K] = plast = d;
         zp[K] = z;
         src[K] = t;
         ++K;
@@ -69,7 +69,11 @@ struct DeflateScan {
             drop(t, dc);
             return;
         }
-        if (prev >= 0) {
+        // Far from the test below, |cs sn| = |z z_prev| / h^2, decided without the
+        // root and the divisions (the scan is one thread's chain).
+        if (prev >= 0 && fabs((dc - dprev) * zprev * zc) > 1.0000001 * tol * (zprev * zprev + zc * zc)) {
+            keep(prev, dprev, zprev);
+        } else if (prev >= 0) {
             // Two close poles: a rotation of their columns zeroes z_prev.
             const double h = hypot(zprev, zc);
             const double cs = zc / h, sn = -zprev / h;
