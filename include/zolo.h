@@ -112,7 +112,7 @@ typedef struct {
     int batch_streams;   /* zolo_pd_batched only: number of solves run at once,
                             each on its own stream and host thread (0: 16; 1:
                             one after another on the handle's stream).  Their
-                            panels of up to 2304 live rows run one workgroup
+                            panels of up to 2048 live rows run one workgroup
                             per matrix on the solve's stream; larger panels
                             are cooperative launches that share one stream,
                             so at most one of those is in flight at any time.
