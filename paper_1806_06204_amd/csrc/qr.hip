@@ -621,34 +621,6 @@ typedef unsigned u4v __attribute__((ext_vector_type(4)));
 typedef double dpair_u __attribute__((ext_vector_type(2), aligned(8)));
 typedef double dpair __attribute__((ext_vector_type(2)));
 
-template <int CTRL>
-__device__ inline double dpp(double x) {
-    const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
-    const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)u, CTRL, 0xf, 0xf, true);
-    const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), CTRL, 0xf, 0xf, true);
-    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
-}
-constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E;             // quad_perm [1,0,3,2], [2,3,0,1]
-constexpr int kDppRor8 = 0x128, kDppHalfMirror = 0x141;     // lane ^ 8; lane ^ 7
-constexpr int kDppRowBcast = 0x150;                         // row_newbcast:0 (+ n: lane n of each row of 16)
-
-// a' = [a.low half, b.low half] and b' = [a.high half, b.high half] over the
-// 32-lane halves; the sum adds each value's two halves, a in lanes 0-31, b above.
-__device__ inline double swap32_add(double a, double b) {
-    const unsigned long long x = __builtin_bit_cast(unsigned long long, a), y = __builtin_bit_cast(unsigned long long, b);
-    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)y, false, false);
-    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
-    return __builtin_bit_cast(double, ((unsigned long long)hi[0] << 32) | lo[0]) +
-           __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
-}
-// The same over neighbouring rows of 16 lanes: a in rows 0 and 2, b in rows 1 and 3.
-__device__ inline double swap16_add(double a, double b) {
-    const unsigned long long x = __builtin_bit_cast(unsigned long long, a), y = __builtin_bit_cast(unsigned long long, b);
-    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)y, false, false);
-    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
-    return __builtin_bit_cast(double, ((unsigned long long)hi[0] << 32) | lo[0]) +
-           __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
-}
 // Sums of 16 values over the wave: lane l returns the sum of value (l >> 2) & 15.
 __device__ inline double wave_sums16(double (&h)[16], int lane) {
 #pragma unroll
@@ -980,33 +952,9 @@ __global__ __launch_bounds__(NT) void panel_leaf_kernel(PanelArgs a) {
             }
             // Reflector k on x = [alpha; below], beta = -sign(alpha) |x|,
             // v = [1; below / (alpha - beta)]  (no cancellation in alpha - beta).
-            // |x| and 1 / |x| from one reciprocal square root and a second reciprocal,
-            // Newton steps to the last bits: half the dependent operations of a square
-            // root and two divisions.
             const double s2 = uniform(sum), alpha = uniform(prow);
             double beta = alpha, tau = 0.0, scale = 0.0;
-            if (s2 != 0.0) {
-                const double t = fma(alpha, alpha, s2);
-                double h = __builtin_amdgcn_rsq(t);
-                double nrm = t * h;
-                h *= 0.5;
-                double e = fma(-h, nrm, 0.5);
-                nrm = fma(nrm, e, nrm);
-                h = fma(h, e, h);
-                const double d = fma(-nrm, nrm, t);
-                e = fma(-h, nrm, 0.5);
-                nrm = fma(d, h, nrm);
-                h = fma(h, e, h);                 // 1 / (2 |x|)
-                const double den = fabs(alpha) + nrm;
-                double x = __builtin_amdgcn_rcp(den);
-                e = fma(-den, x, 1.0);
-                x = fma(x, e, x);
-                e = fma(-den, x, 1.0);
-                x = fma(x, e, x);
-                beta = alpha >= 0.0 ? -nrm : nrm;
-                tau = den * (h + h);              // (beta - alpha) / beta
-                scale = alpha >= 0.0 ? x : -x;    // 1 / (alpha - beta)
-            }
+            if (s2 != 0.0) householder(alpha, s2, beta, tau, scale);
             const double w = fma(scale, sum, prow);   // v_k^T column (later) or v_l^T v_k (finished)
             const double c = l16 < kLW - kk ? tau * w : 0.0;
             // tau from lane 0, V^T V from the finished columns' lanes, in one store
