@@ -65,9 +65,10 @@ struct TrdArgs {
     double* xa;                    // n: first subdiagonal entry of each column before its reflector
     double* yr; double* a1;        // n: (A x)_i over rows >= j + 2, and A[j + 1][i]
     double* pq;                    // 2 kTB: V^T x, W'^T x over the same rows
-    double* partA;                 // kMaxG: sums of squares of x
+    const double* sq;              // sums of squares of x of column j - 1, gA of them
+    double* sq_next;               // row groups: those of column j
     double* partY;                 // 2 kMaxG: sums of a1_i x_i and yr_i x_i, i >= j + 2
-    int gA, gY;                    // partial counts written by the producers
+    int gA, gY;                    // partial counts written by the producers (sq, partY)
     double* P; double* Q;          // n x 2 kTB: [V W] and [W V] of the panel's trailing rows
 };
 
@@ -82,7 +83,12 @@ constexpr int kTrdRows = 64;       // rows per workgroup of trd_column
 // a[j+2:n, j]^2; `finish` (end of a panel) writes the operands [V W], [W V] of
 // the trailing update instead.  One row per lane, the earlier columns of V
 // and W spread over the four waves; what every row needs of row j is formed
-// by each workgroup for itself from values this launch does not change.
+// by each workgroup for itself.  Nothing orders the workgroups of a launch: a
+// word that one of them writes is read by no other.  The sums of squares of
+// column j - 1 and of column j therefore lie in two arrays that change places
+// from launch to launch, and the columns of V and W and the words of column
+// j - 1 that this launch forms (A[j:n, j - 1], W[:, c - 1], alpha[c - 1], xa[j])
+// are not among those read for all rows (columns up to c - 2, xa[j - 1]).
 __global__ __launch_bounds__(kET) void trd_column(TrdArgs a, int finish) {
     __shared__ double sh[3][4];
     __shared__ double s_p[kTB], s_q[kTB], s_al[kTB], s_wj[kTB], s_vj[kTB], s_sc[4];
@@ -93,22 +99,26 @@ __global__ __launch_bounds__(kET) void trd_column(TrdArgs a, int finish) {
     // needs of row j and of the row itself.
     const int row = j + blockIdx.x * kTrdRows + lane, rc = min(row, n - 1);
     constexpr int S = kTB / 4;
+    // With fewer than two earlier columns none of these words is used: they then
+    // come from a column that this launch leaves alone (a branch around the
+    // loads cost 1 % of the eigensolver).
+    const int last = c > 1 ? c - 2 : min(c + 1, n - 1 - j0), w0 = c > 1 ? wave : last;
     double vr[S], wr[S];
 #pragma unroll
     for (int u = 0; u < S; ++u) {
-        const int k = min(wave + 4 * u, max(c - 2, 0));
+        const int k = min(w0 + 4 * u, last);
         vr[u] = a.A[rc + (long long)(j0 + k) * a.lda];
         wr[u] = a.W[rc + (long long)k * a.ldw];
     }
-    const int kl = min(lane, max(c - 2, 0));
+    const int kl = min(c > 1 ? lane : last, last);
     const double rv = a.A[j + (long long)(j0 + kl) * a.lda], rw = a.W[j + (long long)kl * a.ldw];
     const double ral = a.alpha[kl], rpv = a.pq[kl], rpw = a.pq[kTB + kl];
-    const double x1 = a.xa[max(j - 1, 0)], y1 = a.a1[j], y2 = a.yr[j];
+    const double x1 = a.xa[j > 0 ? j - 1 : 1], y1 = a.a1[j], y2 = a.yr[j];
     const double ca1 = a.a1[rc], cyr = a.yr[rc], cp = a.A[rc + (long long)max(j - 1, 0) * a.lda];
     const double cj = a.A[rc + (long long)j * a.lda];
     if (c > 0) {
         double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-        for (int i = tid; i < a.gA; i += kET) s0 += a.partA[i];
+        for (int i = tid; i < a.gA; i += kET) s0 += a.sq[i];
         for (int i = tid; i < a.gY; i += kET) {
             s1 += a.partY[2 * i];
             s2 += a.partY[2 * i + 1];
@@ -215,7 +225,7 @@ __global__ __launch_bounds__(kET) void trd_column(TrdArgs a, int finish) {
     }
     if (finish) return;
     part = wave_sum(part);
-    if (lane == 0) a.partA[blockIdx.x] = part;
+    if (lane == 0) a.sq_next[blockIdx.x] = part;
 }
 
 // x = A[j+2:n, j]: yr_i = A[j+2:n, i]^T x and a1_i = A[j+1][i] for the trailing
@@ -701,7 +711,7 @@ size_t syevd_work_bytes(int n) {
     const size_t nblk = ((size_t)n + kBT - 1) / kBT;
     return 3 * (nn * 8 + 256) + (size_t)n * kTB * 8 + 256 + nblk * (2 * kBT * kBT + kFT * kFT) * 8 + 768 +
            2 * ((size_t)n * 2 * kTB * 8 + 256) + 22 * (N * 8 + 256) + 10 * (N * 4 + 256) +
-           (row_groups_max(n) + 2 * kMaxG) * 8 + 4096;
+           2 * (row_groups_max(n) * 8 + 256) + 2 * kMaxG * 8 + 4096;
 }
 
 // Eigen-decomposition of the symmetric n x n matrix A (lower triangle used;
@@ -732,14 +742,14 @@ hipError_t syevd(int n, double* A, long long lda, double* w_host, double* Z, lon
     int *colsrc = carve<int>(p, N), *src = carve<int>(p, N), *ri = carve<int>(p, N), *rj = carve<int>(p, N);
     int *org = carve<int>(p, N), *inv = carve<int>(p, N), *Kc = carve<int>(p, N), *nrot = carve<int>(p, N);
     int* perm = carve<int>(p, N);
-    double* partA = carve<double>(p, row_groups_max(n));
+    double *sq = carve<double>(p, row_groups_max(n)), *sq_next = carve<double>(p, row_groups_max(n));
     double* partY = carve<double>(p, 2 * kMaxG);
     hipError_t err;
 
     // --- Stage 1: tridiagonalisation ----------------------------------------
     TrdArgs ta;
     ta.n = n; ta.A = A; ta.lda = lda; ta.W = W; ta.ldw = n; ta.alpha = alpha; ta.tau = tau;
-    ta.d = d; ta.e = e; ta.xa = xa; ta.yr = yr; ta.a1 = a1; ta.pq = pq; ta.partA = partA; ta.partY = partY;
+    ta.d = d; ta.e = e; ta.xa = xa; ta.yr = yr; ta.a1 = a1; ta.pq = pq; ta.partY = partY;
     ta.P = P; ta.Q = Q;
     auto row_groups = [](int rows) { return (rows + kTrdRows - 1) / kTrdRows; };
     for (int j0 = 0; j0 < n - 1; j0 += kTB) {
@@ -748,7 +758,9 @@ hipError_t syevd(int n, double* A, long long lda, double* w_host, double* Z, lon
         for (int c = 0; c < jb; ++c) {
             const int j = j0 + c;
             ta.j = j; ta.c = c;
+            ta.sq = sq; ta.sq_next = sq_next;
             trd_column<<<row_groups(n - j), kET, 0, st>>>(ta, 0);
+            std::swap(sq, sq_next);
             ta.gA = row_groups(n - j);
             // Columns per wave: enough waves to fill the chip first (256 CUs,
             // four waves a workgroup), then fewer reads of x.
@@ -761,6 +773,7 @@ hipError_t syevd(int n, double* A, long long lda, double* w_host, double* Z, lon
         const int r0 = j0 + jb;
         const int nt = n - r0;
         ta.j = r0; ta.c = jb;
+        ta.sq = sq;
         trd_column<<<row_groups(nt), kET, 0, st>>>(ta, 1);
         GemmDesc g;  // A22 -= [V W] [W V]^T
         g.m = nt; g.n = nt; g.k = 2 * jb; g.transb = 1;

@@ -1,0 +1,242 @@
+"""CPU replay of the tridiagonalisation (stage 1 of the eigensolver, eig.hip).
+
+The kernels and their launch loop are taken from the source file as they are
+and compiled for the host: the threads of a workgroup run as fibers that meet
+at the barriers and at the wave reductions, the workgroups of a launch one
+after another, in ascending or in descending order.  Nothing orders the
+workgroups of a launch on the GPU, so that both orders have to give the same
+bits: a word that one workgroup writes and another reads in the same launch is
+seen old in one order and new in the other."""
+
+import ctypes
+import os
+import re
+import subprocess
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1806_06204_amd", "csrc")
+CLANG = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", "clang++")
+
+SHIM = r"""
+#include <algorithm>
+#include <cfloat>
+#include <cmath>
+#include <cstdint>
+#include <cstdio>
+#include <cstdlib>
+#include <functional>
+#include <ucontext.h>
+#include <vector>
+#define __global__
+#define __device__
+#define __forceinline__ inline
+#define __launch_bounds__(...)
+#define __shared__ static
+#define __restrict__
+typedef int hipError_t;
+typedef int hipStream_t;
+enum { hipSuccess = 0 };
+static int hipGetLastError() { return hipSuccess; }
+using std::isfinite;
+using std::max;
+using std::min;
+struct dim3 { unsigned x, y, z; dim3(unsigned a = 1, unsigned b = 1, unsigned c = 1) : x(a), y(b), z(c) {} };
+static dim3 blockIdx, blockDim, gridDim, threadIdx;
+
+// Fibers: RUN, at a barrier of the wave, at one of the workgroup, DONE.
+enum { RUN, WAVE, GROUP, DONE };
+static const int kMaxThreads = 1024;
+static ucontext_t g_main, g_ctx[kMaxThreads];
+static std::vector<char> g_stack[kMaxThreads];
+static int g_state[kMaxThreads], g_tid, g_descending;
+static unsigned g_ops[kMaxThreads];
+static double g_slot[2][kMaxThreads];
+static std::function<void()> g_body;
+static void block_on(int s) { g_state[g_tid] = s; swapcontext(&g_ctx[g_tid], &g_main); }
+static void fiber() { g_body(); g_state[g_tid] = DONE; }
+static void __syncthreads() { block_on(GROUP); }
+static double* meet(double v) {
+    double* slots = g_slot[g_ops[g_tid]++ & 1];
+    slots[g_tid] = v;
+    block_on(WAVE);
+    return slots + (g_tid & ~63);
+}
+static double wave_sum(double v) {
+    const double* s = meet(v);
+    double t = 0.0;
+    for (int l = 0; l < 64; ++l) t += s[l];
+    return t;
+}
+static double __shfl_xor(double v, int off, int) { const int l = g_tid & 63; return meet(v)[l ^ off]; }
+static double keep_if(double x, int mask) { return mask ? x : 0.0; }
+static int opaque(int x) { return x; }
+static double __builtin_amdgcn_rsq(double x) { return 1.0 / std::sqrt(x); }
+static double __builtin_amdgcn_rcp(double x) { return 1.0 / x; }
+
+static void run_group(int threads) {
+    for (int t = 0; t < threads; ++t) {
+        if (g_stack[t].empty()) g_stack[t].resize(32768);
+        getcontext(&g_ctx[t]);
+        g_ctx[t].uc_stack.ss_sp = g_stack[t].data();
+        g_ctx[t].uc_stack.ss_size = g_stack[t].size();
+        g_ctx[t].uc_link = &g_main;
+        makecontext(&g_ctx[t], fiber, 0);
+        g_state[t] = RUN;
+        g_ops[t] = 0;
+    }
+    for (;;) {
+        int live = 0;
+        for (int w = 0; w < threads; w += 64) {
+            for (bool again = true; again;) {
+                int at_wave = 0, at_group = 0;
+                for (int t = w; t < w + 64; ++t) {
+                    if (g_state[t] == RUN) {
+                        g_tid = t;
+                        threadIdx.x = t;
+                        swapcontext(&g_main, &g_ctx[t]);
+                    }
+                    at_wave += g_state[t] == WAVE;
+                    at_group += g_state[t] == GROUP;
+                }
+                if (at_wave && at_wave != 64) { std::fprintf(stderr, "a wave reduction that not all lanes reach\n"); std::abort(); }
+                again = at_wave == 64;
+                if (again) for (int t = w; t < w + 64; ++t) g_state[t] = RUN;
+                live += again ? 0 : at_group;
+            }
+        }
+        if (live == 0) return;
+        for (int t = 0; t < threads; ++t) if (g_state[t] == GROUP) g_state[t] = RUN;
+    }
+}
+template <class F>
+static void launch(dim3 grid, int threads, F body) {
+    g_body = body;
+    gridDim = grid;
+    blockDim = dim3(threads);
+    const unsigned total = grid.x * grid.y;
+    for (unsigned i = 0; i < total; ++i) {
+        const unsigned b = g_descending ? total - 1 - i : i;
+        blockIdx = dim3(b % grid.x, b / grid.x);
+        run_group(threads);
+    }
+}
+struct GemmDesc {
+    int m, n, k, transa = 0, transb = 0;
+    const double *A, *B, *Cin = nullptr;
+    double* C;
+    long long lda, ldb, ldc, ldcin = 0;
+    double alpha = 1.0, beta = 0.0;
+};
+static hipError_t gemm(const GemmDesc& g, hipStream_t) {   // as the loop below uses it: C = Cin - A B^T
+    if (g.transa || !g.transb || g.alpha != -1.0 || g.beta != 1.0 || g.Cin != g.C || g.ldcin != g.ldc) std::abort();
+    for (int j = 0; j < g.n; ++j)
+        for (int i = 0; i < g.m; ++i) {
+            double s = 0.0;
+            for (int k = 0; k < g.k; ++k) s += g.A[i + k * g.lda] * g.B[j + k * g.ldb];
+            g.C[i + j * g.ldc] -= s;
+        }
+    return hipSuccess;
+}
+template <class T>
+static hipError_t fill_matrix(int m, int n, T* Z, long long ld, long long, int, double diag, double off, hipStream_t) {
+    for (int j = 0; j < n; ++j)
+        for (int i = 0; i < m; ++i) Z[i + j * ld] = i == j ? diag : off;
+    return hipSuccess;
+}
+template <class T>
+T* carve(char*& p, size_t count) {
+    T* r = reinterpret_cast<T*>(p);
+    p += ((count * sizeof(T) + 255) / 256) * 256;
+    return r;
+}
+"""
+
+TAIL = r"""
+extern "C" int trd(int n, double* A, double* d_out, double* e_out, double* tau_out, long work_bytes, char* work,
+                   int descending) {
+    g_descending = descending;
+    if ((long)syevd_work_bytes(n) > work_bytes) return -1;
+    std::vector<double> zbuf((size_t)n * n);
+    double* Z = zbuf.data();
+    const long long lda = n, ldz = n;
+    hipStream_t st = 0;
+    // as in syevd
+    %(setup)s
+    %(loop)s
+    (void)Z; (void)ldz; (void)err;
+    std::copy(d, d + n, d_out);
+    std::copy(e, e + n - 1, e_out);
+    std::copy(tau, tau + n - 1, tau_out);
+    %(unscale)s
+    return p - work > (long)syevd_work_bytes(n) ? -2 : 0;
+}
+"""
+
+
+def between(text, first, last):
+    i = text.index(first)
+    return text[i:text.index(last, i)]
+
+
+def source():
+    src = open(os.path.join(CSRC, "eig.hip")).read()
+    common = open(os.path.join(CSRC, "common.hpp")).read()
+    consts = "".join(re.findall(r"^constexpr int k(?:TB|BT|FT|ET|MaxG)\b.*\n", src, flags=re.M))
+    hh = between(common, "__device__ __forceinline__ void householder", "// Number of XCDs")
+    kernels = between(src, "struct TrdArgs {", "// T factors (compact WY)")
+    sizes = between(src, "static size_t row_groups_max", "// Eigen-decomposition of the symmetric")
+    setup = between(src, "    char* p = work;", "    // --- Stage 1")
+    loop = between(src, "    // --- Stage 1", "    // --- Stage 2")
+    loop = re.sub(r"\b(\w+(?:<\d+>)?)<<<(.*?), (\w+), 0, st>>>\((.*?)\);",
+                  r"launch(\2, \3, [=] { \1(\4); });", loop)
+    assert "<<<" not in loop
+    unscale = "for (int i = 0; i < n; ++i) { d_out[i] /= *scale; if (i + 1 < n) e_out[i] /= *scale; }" \
+        if "scale" in setup else ""
+    return "\n".join([SHIM, "namespace {", consts, hh, kernels, "}", sizes,
+                      TAIL % {"setup": setup, "loop": loop, "unscale": unscale}])
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    if not os.path.exists(CLANG):
+        pytest.skip("no clang++")
+    d = tmp_path_factory.mktemp("trd")
+    (d / "trd.cpp").write_text(source())
+    r = subprocess.run([CLANG, "-O1", "-std=c++17", "-w", "-shared", "-fPIC", "-o", str(d / "trd.so"), str(d / "trd.cpp")],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    return ctypes.CDLL(str(d / "trd.so"))
+
+
+def tridiagonalise(lib, A, descending):
+    n = A.shape[0]
+    F = np.array(A, order="F")
+    d, e, tau = np.zeros(n), np.zeros(max(n - 1, 1)), np.zeros(max(n - 1, 1))
+    work = np.full((32 << 20) // 8, np.nan)
+    ptr = lambda x: x.ctypes.data_as(ctypes.c_void_p)
+    rc = lib.trd(n, ptr(F), ptr(d), ptr(e), ptr(tau), ctypes.c_long(work.nbytes), ptr(work), descending)
+    assert rc == 0
+    return d, e[:n - 1], tau[:n - 1], F
+
+
+def symmetric(n, seed):
+    B = np.random.default_rng(seed).standard_normal((n, n))
+    return (B + B.T) / 2
+
+
+# One row group, two, and several with a ragged last one; one panel and several.
+@pytest.mark.parametrize("n", [2, 33, 65, 129, 200])
+def test_any_order_of_workgroups_gives_the_same_bits(lib, n):
+    A = symmetric(n, n)
+    up = tridiagonalise(lib, A, 0)
+    down = tridiagonalise(lib, A, 1)
+    for x, y in zip(up, down):
+        assert np.array_equal(x, y)
+    d, e = up[:2]
+    T = np.diag(d) + np.diag(e, 1) + np.diag(e, -1)
+    # Backward error of a Householder reduction, a modest multiple of n eps ||A||.
+    w, ref = np.linalg.eigvalsh(T), np.linalg.eigvalsh(A)
+    assert np.abs(w - ref).max() <= 4 * n * np.finfo(float).eps * np.abs(ref).max()
