@@ -21,6 +21,7 @@
 #include "misc.hpp"
 
 #include <algorithm>
+#include <cfloat>
 #include <cmath>
 #include <numeric>
 #include <vector>
@@ -322,6 +323,50 @@ __global__ __launch_bounds__(kET) void trd_product(TrdArgs a) {
         const double* p = sh[threadIdx.x];
         a.partY[2 * blockIdx.x + threadIdx.x] = (p[0] + p[1]) + (p[2] + p[3]);
     }
+}
+
+// The reduction forms x^T A x of raw columns x, of the order of ||A||^3: right
+// for norms from about 1e-100 to 1e100 alone (with entries of 1e-106 the
+// eigenvalues were off by 1e-2 ||A||, with 1e104 NaN).  A matrix whose largest
+// entry lies outside 2^+-32 is therefore scaled into [1, 2) by a power of two, and
+// its eigenvalues are scaled back on the host: every operation of the solver
+// commutes with that, so the eigenvectors keep their bits.  One pass over the
+// lower triangle for the largest entry (partial maxima, one per workgroup), and
+// the launch that makes the identity of the merges applies the scale.  From
+// subnormal entries up the scale stays a normal number.
+constexpr int kMaxParts = 256;     // workgroups of trd_max
+constexpr int kScaleFree = 32, kScaleMost = 1000;
+
+__device__ inline double block_max256(double v, double* sh) {
+    for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+    __syncthreads();
+    return fmax(fmax(sh[0], sh[1]), fmax(sh[2], sh[3]));
+}
+
+__global__ __launch_bounds__(kET) void trd_max(int n, const double* A, long long lda, double* part) {
+    __shared__ double sh[4];
+    double m = 0.0;
+    for (int j = blockIdx.x; j < n; j += gridDim.x)
+        for (int i = j + threadIdx.x; i < n; i += kET) m = fmax(m, fabs(A[i + j * lda]));
+    m = block_max256(m, sh);
+    if (threadIdx.x == 0) part[blockIdx.x] = m;
+}
+
+// A <- scale A where that is needed, *scale, and Q = I.
+__global__ __launch_bounds__(kET) void trd_scale(int n, double* A, long long lda, const double* part, int nparts,
+                                                 double* scale, double* Q, long long ldq) {
+    __shared__ double sh[4];
+    const double m = block_max256((int)threadIdx.x < nparts ? part[threadIdx.x] : 0.0, sh);
+    const bool apply = m > 0.0 && m <= DBL_MAX && (m < ldexp(1.0, -kScaleFree) || m >= ldexp(1.0, kScaleFree));
+    const double s = apply ? ldexp(1.0, max(-kScaleMost, min(kScaleMost, -ilogb(m)))) : 1.0;
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *scale = s;
+    const int step = gridDim.x * kET;
+    for (int j = blockIdx.y; j < n; j += gridDim.y)
+        for (int i = blockIdx.x * kET + threadIdx.x; i < n; i += step) {
+            if (apply) A[i + j * lda] *= s;
+            Q[i + j * ldq] = i == j ? 1.0 : 0.0;
+        }
 }
 
 // After the reduction: d[n-1], and zeros on and above the diagonal of A so
@@ -711,13 +756,13 @@ size_t syevd_work_bytes(int n) {
     const size_t nblk = ((size_t)n + kBT - 1) / kBT;
     return 3 * (nn * 8 + 256) + (size_t)n * kTB * 8 + 256 + nblk * (2 * kBT * kBT + kFT * kFT) * 8 + 768 +
            2 * ((size_t)n * 2 * kTB * 8 + 256) + 22 * (N * 8 + 256) + 10 * (N * 4 + 256) +
-           2 * (row_groups_max(n) * 8 + 256) + 2 * kMaxG * 8 + 4096;
+           2 * (row_groups_max(n) * 8 + 256) + 2 * kMaxG * 8 + kMaxParts * 8 + 4096;
 }
 
 // Eigen-decomposition of the symmetric n x n matrix A (lower triangle used;
 // A is overwritten).  w_host: eigenvalues, descending; Z (ldz): the matching
 // orthonormal eigenvectors.  work: syevd_work_bytes(n) bytes of device memory.
-// host: pinned buffer of at least n doubles.  Synchronises the stream.
+// host: pinned buffer of at least n + 1 doubles.  Synchronises the stream.
 hipError_t syevd(int n, double* A, long long lda, double* w_host, double* Z, long long ldz, char* work,
                  double* host, hipStream_t st) {
     if (n < 1) return hipErrorInvalidValue;
@@ -744,9 +789,14 @@ hipError_t syevd(int n, double* A, long long lda, double* w_host, double* Z, lon
     int* perm = carve<int>(p, N);
     double *sq = carve<double>(p, row_groups_max(n)), *sq_next = carve<double>(p, row_groups_max(n));
     double* partY = carve<double>(p, 2 * kMaxG);
+    double* partM = carve<double>(p, kMaxParts);
+    double* const scale = D + n;     // read back behind the eigenvalues
     hipError_t err;
 
     // --- Stage 1: tridiagonalisation ----------------------------------------
+    const int gM = std::min(kMaxParts, n);
+    trd_max<<<gM, kET, 0, st>>>(n, A, lda, partM);
+    trd_scale<<<dim3(std::min(8, (n + kET - 1) / kET), std::min(n, 1024)), kET, 0, st>>>(n, A, lda, partM, gM, scale, Qa, ld);
     TrdArgs ta;
     ta.n = n; ta.A = A; ta.lda = lda; ta.W = W; ta.ldw = n; ta.alpha = alpha; ta.tau = tau;
     ta.d = d; ta.e = e; ta.xa = xa; ta.yr = yr; ta.a1 = a1; ta.pq = pq; ta.partY = partY;
@@ -788,7 +838,6 @@ hipError_t syevd(int n, double* A, long long lda, double* w_host, double* Z, lon
 
     // --- Stage 2: divide and conquer on T ------------------------------------
     dc_init<<<(n + kET - 1) / kET, kET, 0, st>>>(n, d, e, D);
-    if ((err = fill_matrix<double>(n, n, Qa, ld, 0, 1, 1.0, 0.0, st)) != hipSuccess) return err;
     DcArgs da;
     da.n = n; da.e = e; da.D = D; da.ld = ld; da.ds = ds; da.zs = zs; da.pole = pole; da.zp = zp;
     da.dval = dval; da.rc = rc; da.rs = rs; da.tau = dtau; da.zh = zh; da.vals = vals; da.rho = rho;
@@ -836,12 +885,13 @@ hipError_t syevd(int n, double* A, long long lda, double* w_host, double* Z, lon
     }
 
     // Eigenvalues to the host, descending order; matching columns.
-    if ((err = hipMemcpyAsync(host, D, sizeof(double) * n, hipMemcpyDeviceToHost, st)) != hipSuccess) return err;
+    if ((err = hipMemcpyAsync(host, D, sizeof(double) * (n + 1), hipMemcpyDeviceToHost, st)) != hipSuccess) return err;
     if ((err = hipStreamSynchronize(st)) != hipSuccess) return err;
+    const double unscale = host[n];
     std::vector<int> order(n);
     std::iota(order.begin(), order.end(), 0);
     std::stable_sort(order.begin(), order.end(), [&](int x, int y2) { return host[x] > host[y2]; });
-    for (int i = 0; i < n; ++i) w_host[i] = host[order[i]];
+    for (int i = 0; i < n; ++i) w_host[i] = host[order[i]] / unscale;
     int* hperm = reinterpret_cast<int*>(host);
     for (int i = 0; i < n; ++i) hperm[i] = order[i];
     if ((err = hipMemcpyAsync(perm, hperm, sizeof(int) * n, hipMemcpyHostToDevice, st)) != hipSuccess) return err;

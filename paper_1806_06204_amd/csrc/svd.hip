@@ -31,7 +31,7 @@ struct Scratch {
     }
 };
 
-// Pinned host buffer of n doubles (the handle's 4 KiB one when it suffices).
+// Pinned host buffer of n + 1 doubles (the handle's 4 KiB one when it suffices).
 struct HostBuf {
     double* p = nullptr;
     bool own = false;
@@ -57,10 +57,10 @@ extern "C" int zolo_dsyevd(zolo_handle h, int n, const double* A, int lda, doubl
     double* Ac = reinterpret_cast<double*>(buf.p);
     char* work = buf.p + ((sizeof(double) * nn + 255) / 256) * 256;
     HostBuf hb;
-    if ((size_t)n * sizeof(double) <= 4096) {
+    if (((size_t)n + 1) * sizeof(double) <= 4096) {
         hb.p = h->host;
     } else {
-        if (hipHostMalloc((void**)&hb.p, sizeof(double) * n) != hipSuccess) return ZOLO_ALLOC;
+        if (hipHostMalloc((void**)&hb.p, sizeof(double) * ((size_t)n + 1)) != hipSuccess) return ZOLO_ALLOC;
         hb.own = true;
     }
     if (hipMemcpy2DAsync(Ac, sizeof(double) * n, A, sizeof(double) * lda, sizeof(double) * n, n,
@@ -95,10 +95,10 @@ extern "C" int zolo_svd(zolo_handle h, int m, int n, const double* A, int lda, d
     double* Qtmp = reinterpret_cast<double*>(buf.p + round(sizeof(double) * nn));
     char* work = buf.p + round(sizeof(double) * nn) + round(sizeof(double) * mn);
     HostBuf hb;
-    if ((size_t)n * sizeof(double) <= 4096) {
+    if (((size_t)n + 1) * sizeof(double) <= 4096) {
         hb.p = h->host;
     } else {
-        if (hipHostMalloc((void**)&hb.p, sizeof(double) * n) != hipSuccess) return ZOLO_ALLOC;
+        if (hipHostMalloc((void**)&hb.p, sizeof(double) * ((size_t)n + 1)) != hipSuccess) return ZOLO_ALLOC;
         hb.own = true;
     }
     zolo_info inf;

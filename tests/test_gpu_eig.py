@@ -118,6 +118,32 @@ def test_tridiagonal_input_and_lower_triangle_only(z):
     assert np.max(np.abs(w - np.linalg.eigvalsh(T)[::-1])) <= 1e-14 * np.linalg.norm(T, 2)
 
 
+# A power of two on the matrix is the same power of two on its eigenvalues, bit
+# for bit, and leaves the eigenvectors alone; orders around the handle's 512
+# pinned words.
+@pytest.mark.parametrize("n,exponent", [(60, -1000), (60, -480), (60, -350), (60, 350), (60, 480), (60, 1000),
+                                        (511, -400), (512, 400), (513, -400)])
+def test_scaled_by_powers_of_two(z, n, exponent):
+    rng = np.random.default_rng(1200 + n)
+    B = rng.standard_normal((n, n))
+    A = (B + B.T) / 2
+    w0, Z0 = check(z, A)
+    w, Z = z.syevd(dev(np.ldexp(A, exponent)))
+    assert np.array_equal(w, np.ldexp(w0, exponent))
+    assert np.array_equal(Z.cpu().numpy(), Z0)
+
+
+@pytest.mark.parametrize("exponent", [-480, -350, 350, 480])
+def test_svd_scaled_by_powers_of_two(z, exponent):
+    m, n = 150, 70
+    A, _, s, _ = W.svd_matrix(m, n, 20.0, 61, 62)
+    U0, S0, V0, i0 = z.svd(dev(A), alpha=1.0, l=0.04)
+    U, S, V, info = z.svd(dev(np.ldexp(A, exponent)), alpha=float(np.ldexp(1.0, exponent)), l=0.04)
+    assert info["status"] == i0["status"] == 0
+    assert np.array_equal(S, np.ldexp(S0, exponent)) and np.abs(S0 - s).max() <= 1e-13
+    assert np.array_equal(U.cpu().numpy(), U0.cpu().numpy()) and np.array_equal(V.cpu().numpy(), V0.cpu().numpy())
+
+
 def test_exact_spectrum_n4096(z):
     # H = V diag(sigma) V^T with sigma log-spaced from 1 to 1e-16 (the H of
     # the kappa = 1e16 workload at n = 4096): eigenvalues against sigma.

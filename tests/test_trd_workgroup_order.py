@@ -240,3 +240,17 @@ def test_any_order_of_workgroups_gives_the_same_bits(lib, n):
     # Backward error of a Householder reduction, a modest multiple of n eps ||A||.
     w, ref = np.linalg.eigvalsh(T), np.linalg.eigvalsh(A)
     assert np.abs(w - ref).max() <= 4 * n * np.finfo(float).eps * np.abs(ref).max()
+
+
+# The product with the raw column makes x^T A x of the order of ||A||^3: whatever
+# the norm, the reduction is that of the matrix of norm about 1.  Scaling by a
+# power of two is exact (no entry here is subnormal), so T and the reflectors keep
+# their bits.
+@pytest.mark.parametrize("exponent", [-1000, -480, -350, -33, -32, -31, 0, 31, 32, 33, 350, 480, 1000])
+def test_scaled_matrices(lib, exponent):
+    n = 60
+    A = symmetric(n, 7)
+    d0, e0, tau0, _ = tridiagonalise(lib, A, 0)
+    d, e, tau, _ = tridiagonalise(lib, np.ldexp(A, exponent), 0)
+    assert np.array_equal(d, np.ldexp(d0, exponent)) and np.array_equal(e, np.ldexp(e0, exponent))
+    assert np.array_equal(tau, tau0)
