@@ -72,8 +72,9 @@ int zolo_structured_qr_batched(zolo_handle h, int m, int n, const double* pivots
  * and conquer on the tridiagonal matrix, back-transformation.  w (HOST, n
  * entries) receives the eigenvalues in descending order, Z (device, ldz >= n)
  * the matching orthonormal eigenvectors.  Allocates its workspace (about
- * 4 n^2 doubles) for the call.  Returns 0, a negative argument index, 3 if
- * the workspace cannot be allocated or 4 for a HIP error. */
+ * 4 n^2 doubles) for the call.  A of any norm.  Returns 0, a negative argument
+ * index, ZOLO_NONFINITE if A holds NaN or Inf (w and Z are then not written), 3
+ * if the workspace cannot be allocated or 4 for a HIP error. */
 int zolo_dsyevd(zolo_handle h, int n, const double* A, int lda, double* w, double* Z, int ldz);
 
 #ifdef __cplusplus

@@ -333,7 +333,9 @@ __global__ __launch_bounds__(kET) void trd_product(TrdArgs a) {
 // commutes with that, so the eigenvectors keep their bits.  One pass over the
 // lower triangle for the largest entry (partial maxima, one per workgroup), and
 // the launch that makes the identity of the merges applies the scale.  From
-// subnormal entries up the scale stays a normal number.
+// subnormal entries up the scale stays a normal number.  A matrix with a NaN or an
+// infinity is refused (scale 0) and solved as zero: NaN eigenvalues have no ranks,
+// and the merges index by rank.
 constexpr int kMaxParts = 256;     // workgroups of trd_max
 constexpr int kScaleFree = 32, kScaleMost = 1000;
 
@@ -348,23 +350,27 @@ __global__ __launch_bounds__(kET) void trd_max(int n, const double* A, long long
     __shared__ double sh[4];
     double m = 0.0;
     for (int j = blockIdx.x; j < n; j += gridDim.x)
-        for (int i = j + threadIdx.x; i < n; i += kET) m = fmax(m, fabs(A[i + j * lda]));
+        for (int i = j + threadIdx.x; i < n; i += kET) {
+            const double v = fabs(A[i + j * lda]);
+            m = fmax(m, v <= DBL_MAX ? v : INFINITY);
+        }
     m = block_max256(m, sh);
     if (threadIdx.x == 0) part[blockIdx.x] = m;
 }
 
-// A <- scale A where that is needed, *scale, and Q = I.
+// A <- scale A where that is needed (0 A = 0 for a refused one), *scale, and Q = I.
 __global__ __launch_bounds__(kET) void trd_scale(int n, double* A, long long lda, const double* part, int nparts,
                                                  double* scale, double* Q, long long ldq) {
     __shared__ double sh[4];
     const double m = block_max256((int)threadIdx.x < nparts ? part[threadIdx.x] : 0.0, sh);
-    const bool apply = m > 0.0 && m <= DBL_MAX && (m < ldexp(1.0, -kScaleFree) || m >= ldexp(1.0, kScaleFree));
-    const double s = apply ? ldexp(1.0, max(-kScaleMost, min(kScaleMost, -ilogb(m)))) : 1.0;
+    const bool apply = m > 0.0 && (m < ldexp(1.0, -kScaleFree) || m >= ldexp(1.0, kScaleFree));
+    double s = 1.0;
+    if (apply) s = m <= DBL_MAX ? ldexp(1.0, max(-kScaleMost, min(kScaleMost, -ilogb(m)))) : 0.0;
     if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *scale = s;
     const int step = gridDim.x * kET;
     for (int j = blockIdx.y; j < n; j += gridDim.y)
         for (int i = blockIdx.x * kET + threadIdx.x; i < n; i += step) {
-            if (apply) A[i + j * lda] *= s;
+            if (apply) A[i + j * lda] = s > 0.0 ? s * A[i + j * lda] : 0.0;
             Q[i + j * ldq] = i == j ? 1.0 : 0.0;
         }
 }
@@ -763,8 +769,9 @@ size_t syevd_work_bytes(int n) {
 // A is overwritten).  w_host: eigenvalues, descending; Z (ldz): the matching
 // orthonormal eigenvectors.  work: syevd_work_bytes(n) bytes of device memory.
 // host: pinned buffer of at least n + 1 doubles.  Synchronises the stream.
+// *finite: false when A holds a NaN or an infinity; w_host and Z are then not written.
 hipError_t syevd(int n, double* A, long long lda, double* w_host, double* Z, long long ldz, char* work,
-                 double* host, hipStream_t st) {
+                 double* host, hipStream_t st, bool* finite) {
     if (n < 1) return hipErrorInvalidValue;
     char* p = work;
     const long long ld = n;
@@ -888,6 +895,8 @@ hipError_t syevd(int n, double* A, long long lda, double* w_host, double* Z, lon
     if ((err = hipMemcpyAsync(host, D, sizeof(double) * (n + 1), hipMemcpyDeviceToHost, st)) != hipSuccess) return err;
     if ((err = hipStreamSynchronize(st)) != hipSuccess) return err;
     const double unscale = host[n];
+    *finite = unscale > 0.0;
+    if (!*finite) return hipSuccess;
     std::vector<int> order(n);
     std::iota(order.begin(), order.end(), 0);
     std::stable_sort(order.begin(), order.end(), [&](int x, int y2) { return host[x] > host[y2]; });

@@ -16,7 +16,7 @@
 namespace zolo {
 size_t syevd_work_bytes(int n);
 hipError_t syevd(int n, double* A, long long lda, double* w_host, double* Z, long long ldz, char* work,
-                 double* host, hipStream_t st);
+                 double* host, hipStream_t st, bool* finite);
 }  // namespace zolo
 
 using namespace zolo;
@@ -66,8 +66,9 @@ extern "C" int zolo_dsyevd(zolo_handle h, int n, const double* A, int lda, doubl
     if (hipMemcpy2DAsync(Ac, sizeof(double) * n, A, sizeof(double) * lda, sizeof(double) * n, n,
                          hipMemcpyDeviceToDevice, st) != hipSuccess)
         return ZOLO_HIP;
-    if (syevd(n, Ac, n, w, Z, ldz, work, hb.p, st) != hipSuccess) return ZOLO_HIP;
-    return 0;
+    bool finite = true;
+    if (syevd(n, Ac, n, w, Z, ldz, work, hb.p, st, &finite) != hipSuccess) return ZOLO_HIP;
+    return finite ? 0 : ZOLO_NONFINITE;
 }
 
 extern "C" int zolo_svd(zolo_handle h, int m, int n, const double* A, int lda, double alpha, double l, int r,
@@ -114,7 +115,9 @@ extern "C" int zolo_svd(zolo_handle h, int m, int n, const double* A, int lda, d
         return code;
     };
     auto t0 = std::chrono::steady_clock::now();
-    if (syevd(n, Hm, n, S, V, ldv, work, hb.p, st) != hipSuccess) return fail(ZOLO_HIP);
+    bool finite = true;                            // H = Qp^T A may overflow
+    if (syevd(n, Hm, n, S, V, ldv, work, hb.p, st, &finite) != hipSuccess) return fail(ZOLO_HIP);
+    if (!finite) return fail(ZOLO_NONFINITE);
     // Tridiagonalisation 4/3 n^3 (full-storage update: 2 n^3), divide and
     // conquer about 8/3 n^3 in its block products, back-transformation 2 n^3.
     inf.flops_exec += (2.0 + 8.0 / 3.0 + 2.0) * (double)n * n * n;

@@ -144,6 +144,16 @@ def test_svd_scaled_by_powers_of_two(z, exponent):
     assert np.array_equal(U.cpu().numpy(), U0.cpu().numpy()) and np.array_equal(V.cpu().numpy(), V0.cpu().numpy())
 
 
+@pytest.mark.parametrize("bad", [np.nan, np.inf])
+def test_non_finite_is_refused(z, bad):
+    A = np.eye(40)
+    A[7, 5] = A[5, 7] = bad
+    from paper_1806_06204_amd.zolo import ZoloError
+    with pytest.raises(ZoloError, match="code 2"):
+        z.syevd(dev(A))
+    check(z, np.eye(40))                         # the handle goes on working
+
+
 def test_exact_spectrum_n4096(z):
     # H = V diag(sigma) V^T with sigma log-spaced from 1 to 1e-16 (the H of
     # the kappa = 1e16 workload at n = 4096): eigenvalues against sigma.
