@@ -765,8 +765,8 @@ size_t syevd_work_bytes(int n) {
            2 * (row_groups_max(n) * 8 + 256) + 2 * kMaxG * 8 + kMaxParts * 8 + 4096;
 }
 
-// Eigen-decomposition of the symmetric n x n matrix A (lower triangle used;
-// A is overwritten).  w_host: eigenvalues, descending; Z (ldz): the matching
+// Eigen-decomposition of the symmetric n x n matrix A (both triangles stored
+// and used; A is overwritten).  w_host: eigenvalues, descending; Z (ldz): the matching
 // orthonormal eigenvectors.  work: syevd_work_bytes(n) bytes of device memory.
 // host: pinned buffer of at least n + 1 doubles.  Synchronises the stream.
 // *finite: false when A holds a NaN or an infinity; w_host and Z are then not written.

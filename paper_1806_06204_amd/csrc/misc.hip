@@ -95,8 +95,8 @@ __global__ void fill_kernel(int m, int n, T* __restrict__ Z, long long ldz, long
     }
 }
 
-// S = (U + U^T)/2 from the upper triangle? mode 0: S = (C + C^T)/2 (full C);
-// mode 1: S[i][j] = C[min][max] + add_diag * delta_ij (mirror the upper triangle).
+// Mode 0: S = (C + C^T)/2 (full C); mode 1: S[i][j] = C[min][max] + add_diag * delta_ij
+// (mirror the upper triangle); mode 2: the same from the lower triangle.
 template <class T>
 __global__ void symmetrize_kernel(int n, const T* __restrict__ C, long long ldc,
                                   T* __restrict__ S, long long lds, int mode, double add_diag) {
@@ -106,7 +106,7 @@ __global__ void symmetrize_kernel(int n, const T* __restrict__ C, long long ldc,
         const long long j = e / n, i = e - j * n;
         T v;
         if (mode == 0) v = (T)0.5 * (C[i + j * ldc] + C[j + i * ldc]);
-        else v = (i <= j ? C[i + j * ldc] : C[j + i * ldc]) + (i == j ? (T)add_diag : (T)0);
+        else v = ((i <= j) == (mode == 1) ? C[i + j * ldc] : C[j + i * ldc]) + (i == j ? (T)add_diag : (T)0);
         S[i + j * lds] = v;
     }
 }

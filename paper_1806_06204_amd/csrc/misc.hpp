@@ -25,7 +25,7 @@ hipError_t fill_matrix(int m, int n, T* Z, long long ldz, long long sz, int batc
                        hipStream_t st);
 template <class T>
 hipError_t zero_strict_lower(int n, T* Z, long long ldz, long long sz, int batch, hipStream_t st);
-// mode 0: S = (C + C^T)/2;  mode 1: S = mirror of the upper triangle of C, plus add_diag * I.
+// mode 0: S = (C + C^T)/2;  mode 1 (2): S = mirror of the upper (lower) triangle of C, plus add_diag * I.
 template <class T>
 hipError_t symmetrize(int n, const T* C, long long ldc, T* S, long long lds, int mode, double add_diag,
                       hipStream_t st);

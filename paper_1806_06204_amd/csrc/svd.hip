@@ -63,9 +63,8 @@ extern "C" int zolo_dsyevd(zolo_handle h, int n, const double* A, int lda, doubl
         if (hipHostMalloc((void**)&hb.p, sizeof(double) * ((size_t)n + 1)) != hipSuccess) return ZOLO_ALLOC;
         hb.own = true;
     }
-    if (hipMemcpy2DAsync(Ac, sizeof(double) * n, A, sizeof(double) * lda, sizeof(double) * n, n,
-                         hipMemcpyDeviceToDevice, st) != hipSuccess)
-        return ZOLO_HIP;
+    // The reduction works on both triangles: the upper one is made from the lower.
+    if (symmetrize(n, A, lda, Ac, n, 2, 0.0, st) != hipSuccess) return ZOLO_HIP;
     bool finite = true;
     if (syevd(n, Ac, n, w, Z, ldz, work, hb.p, st, &finite) != hipSuccess) return ZOLO_HIP;
     return finite ? 0 : ZOLO_NONFINITE;

@@ -118,6 +118,16 @@ def test_tridiagonal_input_and_lower_triangle_only(z):
     assert np.max(np.abs(w - np.linalg.eigvalsh(T)[::-1])) <= 1e-14 * np.linalg.norm(T, 2)
 
 
+@pytest.mark.parametrize("n", [2, 60, 257])
+def test_only_the_lower_triangle_is_read(z, n):
+    rng = np.random.default_rng(1100 + n)
+    B = rng.standard_normal((n, n))
+    A = (B + B.T) / 2
+    w0, Z0 = check(z, A)
+    w, Z = z.syevd(dev(np.tril(A) + np.triu(np.full((n, n), 7.0), 1)))
+    assert np.array_equal(w, w0) and np.array_equal(Z.cpu().numpy(), Z0)
+
+
 # A power of two on the matrix is the same power of two on its eigenvalues, bit
 # for bit, and leaves the eigenvectors alone; orders around the handle's 512
 # pinned words.
