@@ -199,7 +199,8 @@ int wait(zolo_handle h) {
 // them there and a wait is all the host needs, without a copy before each wait
 // (48 x 32: 303 -> 289 us; 256 x 128: 869 -> 860 us; 32 small problems: 24.7 ->
 // 24.2 ms).  The first 2 KiB of the buffer stay free for copies.  Every solve
-// ends with a wait, so nothing of an earlier one can still write here.
+// ends with a wait, an error return too (finish in pd_core), so nothing of an
+// earlier one can still write here.
 void scalars_to_host(zolo_handle h, Work& w) {
     char* p = reinterpret_cast<char*>(h->host);
     w.iflags = reinterpret_cast<int*>(p + 2048);      // 64 ints
@@ -500,6 +501,13 @@ int pd_core(zolo_handle h, char* base, int m, int n, const double* A, int lda, d
         return stage.lap();
     };
     auto finish = [&](int status) {
+        // After an error, launches before it may still be queued: they would
+        // write flags and scalars that the next call has cleared.
+        if (status != 0 && status != ZOLO_NOT_CONVERGED) {
+            (void)hipStreamSynchronize(st);
+            if (w.qr.side_stream) (void)hipStreamSynchronize(w.qr.side_stream);
+            if (w.qr.panel_stream) (void)hipStreamSynchronize(w.qr.panel_stream);
+        }
         inf.status = status;
         inf.t_stage[7] = whole.lap();
         if (info) *info = inf;
