@@ -828,6 +828,9 @@ __global__ __launch_bounds__(NT) void panel_leaf_kernel(PanelArgs a) {
             u4v v[U + 1];
             unsigned spins = 0;
             for (;;) {
+                // The addresses do not change: without this the loads, which the
+                // compiler takes for ordinary ones, might be kept from turn to turn.
+                asm volatile("" ::: "memory");
                 bool ok = true;
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
