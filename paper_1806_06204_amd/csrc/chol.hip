@@ -60,10 +60,10 @@ __device__ void load_upper(const T* Z, long long ld, int kb, T (*S)[kB + 1]) {
 
 // Inverse of the 16 x 16 diagonal block at o of the upper triangular S into Si (LDS),
 // by one wave: lane j of each row of 16 lanes back-substitutes column j.  rcp
-// holds 1 / S[i][i].  Each entry found goes to all the sums above it, which are
+// holds 1 / S[i][i], with DIV S[i][i] itself.  Each entry found goes to all the sums above it, which are
 // independent of each other (a sum per entry at a time is one chain of 120
 // operations: 11.4k cycles for the four blocks at once, now 2.5k).
-template <class T, int K>
+template <class T, int K, bool DIV>
 __device__ __forceinline__ void inverse16_steps(const T (*S)[kB + 1], const T* rcp, T (*Si)[kB + 1], T (&x)[kDB],
                                                 const T (&z)[kDB], T r, int o, int l16) {
     if constexpr (K >= 0) {
@@ -73,22 +73,22 @@ __device__ __forceinline__ void inverse16_steps(const T (*S)[kB + 1], const T* r
 #pragma unroll
             for (int i = 0; i < K - 1; ++i) zn[i] = S[o + i][o + K - 1];
         }
-        const T xk = K <= l16 ? x[K] * r : (T)0;
+        const T xk = K <= l16 ? (DIV ? x[K] / r : x[K] * r) : (T)0;
         Si[o + K][o + l16] = xk;                  // the four rows of lanes alike
 #pragma unroll
         for (int i = 0; i < K; ++i) x[i] -= z[i] * xk;
         __builtin_amdgcn_sched_barrier(0);        // one column's loads ahead (registers)
-        inverse16_steps<T, K - 1>(S, rcp, Si, x, zn, rn, o, l16);
+        inverse16_steps<T, K - 1, DIV>(S, rcp, Si, x, zn, rn, o, l16);
     }
 }
-template <class T>
+template <class T, bool DIV = false>
 __device__ __forceinline__ void inverse16(const T (*S)[kB + 1], const T* rcp, T (*Si)[kB + 1], int o, int l16) {
     T x[kDB], z[kDB];
 #pragma unroll
     for (int i = 0; i < kDB; ++i) x[i] = i == l16 ? (T)1 : (T)0;
 #pragma unroll
     for (int i = 0; i < kDB - 1; ++i) z[i] = S[o + i][o + kDB - 1];
-    inverse16_steps<T, kDB - 1>(S, rcp, Si, x, z, rcp[o + kDB - 1], o, l16);
+    inverse16_steps<T, kDB - 1, DIV>(S, rcp, Si, x, z, rcp[o + kDB - 1], o, l16);
 }
 // A 16 x 16 tile of S12 Si22 (phase 0) or -Si11 times it (phase 1) for blocks of
 // W at o and o + W, the tile's rows and columns at ti and tj, on the matrix cores.
@@ -135,15 +135,16 @@ __device__ __forceinline__ void merge32(const T (*S)[kB + 1], T (*Si)[kB + 1], i
 
 // Inverse of the upper-triangular 64 x 64 matrix S (LDS; identity beyond the
 // matrix) into Si (LDS), by the workgroup's 256 threads: the four 16 x 16
-// diagonal blocks at once, then neighbouring blocks of 16 and of 32 merged.
-template <class T>
+// diagonal blocks at once (rcp and DIV as above), then neighbouring blocks of 16
+// and of 32 merged.
+template <class T, bool DIV>
 __device__ void lds_upper_inverse(const T (*S)[kB + 1], const T* rcp, T (*Si)[kB + 1]) {
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     for (int e = tid; e < kB * kB; e += 256) {
         const int i = e / kB, j = e % kB;
         if (i / kDB != j / kDB) Si[i][j] = 0;
     }
-    inverse16<T>(S, rcp, Si, w * kDB, lane & 15);
+    inverse16<T, DIV>(S, rcp, Si, w * kDB, lane & 15);
     __syncthreads();
     if (w < 2) merge16<T>(S, Si, 2 * w * kDB, lane);
     __syncthreads();
@@ -293,9 +294,22 @@ __global__ __launch_bounds__(256) void trtri_diag_kernel(int n, const T* R, long
     load_upper<T>(Rb, ldr, kb, S);
     __syncthreads();
     __shared__ T s_rcp[kB];
-    if (tid < kB) s_rcp[tid] = (T)1 / S[tid][tid];
-    __syncthreads();
-    lds_upper_inverse<T>(S, s_rcp, Si);
+    // A diagonal entry so small or so large that its reciprocal is no normal number
+    // (zero and infinity among them) is divided by: 0 times a reciprocal that
+    // overflows would be NaN.
+    bool plain = true;
+    if (tid < kB) {
+        const T r = (T)1 / S[tid][tid];
+        plain = fabs(r) >= std::numeric_limits<T>::min() && fabs(r) <= std::numeric_limits<T>::max();
+        s_rcp[tid] = r;
+    }
+    if (__syncthreads_and(plain)) {
+        lds_upper_inverse<T, false>(S, s_rcp, Si);
+    } else {
+        if (tid < kB) s_rcp[tid] = S[tid][tid];
+        __syncthreads();
+        lds_upper_inverse<T, true>(S, s_rcp, Si);
+    }
     for (int e = tid; e < kb * kb; e += 256) {
         const int i = e % kb, j = e / kb;
         Ib[i + (long long)j * ldi] = Si[i][j];

@@ -137,6 +137,28 @@ def test_cholesky_and_inverse_edges(z, n, dtype):
         assert np.linalg.norm(R[b] @ Ri[b] - np.eye(n)) <= 4 * (n + 8) * u * np.linalg.norm(R[b]) * np.linalg.norm(Ri[b])
 
 
+# Diagonal entries whose reciprocal overflows (or is subnormal): an entry of the
+# inverse above them is its sum divided by them, 0 or an ordinary number.
+@pytest.mark.parametrize("dtype,tiny,small,huge", [("float64", 2.0 ** -1040, 2.0 ** -1050, 2.0 ** 1023),
+                                                   ("float32", 2.0 ** -135, 2.0 ** -142, 2.0 ** 127)])
+@pytest.mark.parametrize("n", [2, 9, 16])
+def test_triangular_inverse_of_extreme_diagonals(z, n, dtype, tiny, small, huge):
+    import torch
+    R = np.stack([np.eye(n), np.eye(n), np.eye(n)])
+    R[0, 0, 0] = tiny                             # nothing above the other columns' ones
+    R[1, 0, 0] = tiny
+    R[1, 0, 1:] = small
+    R[2, 0, 0] = huge
+    R[2, 0, 1:] = huge / 4
+    Ri = z.trtri(torch.from_numpy(R.astype(dtype)).to("cuda")).cpu().numpy().astype(np.float64)
+    top = [1.0 / np.asarray([tiny, tiny, huge], dtype=dtype), [0.0, -small / tiny, -0.25]]
+    for b in range(3):
+        E = np.eye(n)
+        E[0, 0] = top[0][b]
+        E[0, 1:] = top[1][b]
+        assert np.array_equal(Ri[b], E), b
+
+
 @pytest.mark.parametrize("at", [0, 15, 16, 40, 63, 64, 99])
 def test_cholesky_breakdown_column(z, at):
     import torch
