@@ -151,10 +151,13 @@ __device__ void lds_upper_inverse(const T (*S)[kB + 1], const T* rcp, T (*Si)[kB
     merge32<T>(S, Si, w, lane);
 }
 
-// sqrt(d) and 1 / sqrt(d) of a positive, finite d: the hardware estimate
-// refined to the last bit or so, without a branch, 1 / sqrt(d) first, which the
-// next pivot waits for.  Small d is scaled by an even power of two, so that no
-// residual underflows.
+// sqrt(d) and 1 / sqrt(d) of a positive, finite d: the hardware's estimate of the
+// reciprocal root refined by Goldschmidt's and Newton's iterations without a branch,
+// 1 / sqrt(d) first, which the next pivot waits for, then the root from it and
+// its residual.  Small d is scaled by an even power of two, so that no residual
+// underflows.  Largest errors over all exponents: root 1.11e-16, as correctly
+// rounded, and reciprocal 1.38e-16, where a division by it leaves 1.65e-16 (FP32:
+// 5.96e-8, and 7.4e-8 against 8.9e-8).
 __device__ __forceinline__ void sqrt_rcp(double d, double& r, double& ri) {
     const bool small = d < 0x1p-900;
     d *= small ? 0x1p512 : 1.0;

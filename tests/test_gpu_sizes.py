@@ -97,6 +97,26 @@ def test_panel_zero_and_graded_columns(z):
     assert np.all(d <= 1e-14 * 70 * np.linalg.norm(Y[0], axis=0))
 
 
+def test_reflector_of_one_column(z):
+    # Q[0] = 1 - tau = alpha / beta of a column [alpha; x], tau = (|alpha| + |col|) / |col|
+    # in [1, 2].  With x^2 exact the norm is off by 1.5 u (its argument and the root),
+    # which tau takes at most half of, and the sum and the quotient by u each.
+    import torch
+    rng = np.random.default_rng(77)
+    u = 2.0 ** -53
+    worst = 0.0
+    for _ in range(200):
+        Y = np.empty((16, 2, 1))
+        Y[:, 0, 0] = 2.0 ** rng.uniform(-30.0, 2.0, 16) * rng.choice([-1.0, 1.0], 16)
+        Y[:, 1, 0] = np.round(rng.uniform(0.5, 1.0, 16) * 2 ** 24) / 2 ** 24
+        Q, _ = z.structured_qr(torch.from_numpy(Y).to("cuda"), None, form_q=True)
+        al, x = Y[:, 0, 0].astype(np.longdouble), Y[:, 1, 0].astype(np.longdouble)
+        tau = 1 + np.abs(al) / np.sqrt(al * al + x * x)
+        worst = max(worst, float(np.max(np.abs((1 - Q.cpu().numpy()[:, 0, 0].astype(np.longdouble)) / tau - 1))))
+    print(f"  largest error of tau: {worst / u:.3f} u")
+    assert worst <= 2.75 * u * (1 + 1e-3)
+
+
 @pytest.mark.parametrize("m,n", [(1024 - 64, 130), (1985, 70), (2048 - 64, 200), (2100, 100)])
 def test_batched_panels_one_workgroup(z, m, n):
     # The many-matrix call's panels: one workgroup up to 2048 live rows, more
