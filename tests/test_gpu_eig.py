@@ -164,6 +164,23 @@ def test_non_finite_is_refused(z, bad):
     check(z, np.eye(40))                         # the handle goes on working
 
 
+# Orders just past the lines where a wave of the tridiagonalisation's product takes
+# two and four columns, odd: leading dimension, last group of columns and pair loads.
+@pytest.mark.parametrize("n", [2051, 4099])
+def test_columns_per_wave(z, n):
+    import torch
+    g = torch.Generator().manual_seed(n)
+    B = torch.randn((n, n), generator=g, dtype=torch.float64)
+    A = (B + B.T) / 2
+    print(f"  n={n}: solving", flush=True)
+    w, Z = z.syevd(A.cuda())
+    Z = Z.cpu()
+    nrm = max(abs(w[0]), abs(w[-1]))
+    assert np.all(np.diff(w) <= 0)
+    assert float(torch.linalg.norm(A @ Z - Z * torch.from_numpy(w))) <= 1e-14 * nrm * np.sqrt(n)
+    assert float(torch.linalg.norm(Z.T @ Z - torch.eye(n, dtype=torch.float64))) <= 1e-15 * n
+
+
 def test_exact_spectrum_n4096(z):
     # H = V diag(sigma) V^T with sigma log-spaced from 1 to 1e-16 (the H of
     # the kappa = 1e16 workload at n = 4096): eigenvalues against sigma.
