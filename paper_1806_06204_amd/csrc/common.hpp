@@ -20,8 +20,10 @@ constexpr int kWave = 64;
 // (or, with `reduce`, one D = beta * Cin + sum_b alpha*alpha_b op(A_b) op(B_b)).
 // Column-major, op(X) = X or X^T.  Structural flags let a tile skip k-blocks
 // that are known to be zero (triangular operands) and skip whole tiles of a
-// symmetric result.  Zero regions of triangular operands must hold zeros in
-// memory: only whole BK-blocks are skipped.
+// symmetric result.  The zero region of a triangular operand may hold anything,
+// NaN included: whole blocks of it are skipped, and its elements in the blocks
+// on the diagonal are replaced by zeros element by element.  The Cholesky-type
+// step, whose factors are undefined there, relies on it.
 // ---------------------------------------------------------------------------
 enum GemmFlags : unsigned {
     kAUpper = 1u,        // op(A)[i][k] == 0 for k < i   (k-range starts at tile row 0)

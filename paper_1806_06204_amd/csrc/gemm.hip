@@ -957,7 +957,7 @@ hipError_t dispatch_pipe_tuned(const GemmDescT<double>& d, int static_choice, hi
 }
 
 // Kernel and tile shape for a descriptor: 0/1 = gemm_kernel with 64 x 64 /
-// 64 x 128 tiles, 5/6 = dgemm_pipe_kernel with 64 x 128 / 64 x 64 tiles.
+// 64 x 128 tiles (1: FP32 only), 5/6 = dgemm_pipe_kernel with 64 x 128 / 64 x 64 tiles.
 // FP64 runs the pipelined kernel wherever it has one whole slice along k and one
 // pair along an operand's contiguous rows or columns.  Measured on gfx950
 // (TFLOP/s): 8192^3 N,N 68.3, T,N 68.5, N,T 63.5 (gemm_kernel 39.7); 256 x 8192 x
@@ -978,9 +978,7 @@ int pick_tile(const GemmDescT<T>& d) {
         if (d.k >= kBK && (d.transa || d.m >= 2) && (!d.transb || d.n >= 2))
             return (d.k > 256 && d.m >= 128 && d.n >= 128 && t1 >= 256) ? 5 : 6;
     }
-    if (d.k <= 128) return 0;
-    if (d.m >= 128 && d.n >= 128 && t1 >= 256) return 1;
-    return 0;
+    return sizeof(T) == 4 && d.k > 128 && d.m >= 128 && d.n >= 128 && t1 >= 256 ? 1 : 0;
 }
 
 inline void tile_dims(int t, int& bm, int& bn) {
@@ -998,8 +996,10 @@ hipError_t gemm_dispatch(const GemmDescT<T>& d, hipStream_t s) {
     if constexpr (sizeof(T) == 8) {
         if (t == 5) return dispatch_pipe_tuned(d, 0, s);
         if (t == 6) return dispatch_pipe_tuned(d, 1, s);
+    } else {
+        if (t == 1) return launch_bm_bn<T, 64, 128>(d, s);
     }
-    return t == 1 ? launch_bm_bn<T, 64, 128>(d, s) : launch_bm_bn<T, 64, 64>(d, s);
+    return launch_bm_bn<T, 64, 64>(d, s);
 }
 
 }  // namespace

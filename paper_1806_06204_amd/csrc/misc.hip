@@ -39,18 +39,6 @@ __global__ void scale_copy_kernel(int m, int n, const double* __restrict__ A, lo
     if (bad && flag) raise_flag(flag);
 }
 
-// Y_b = X for b < batch (X is m x n with ld ldx; Y_b has ld ldy, stride sy).
-__global__ void broadcast_copy_kernel(int m, int n, const double* __restrict__ X, long long ldx,
-                                      double* __restrict__ Y, long long ldy, long long sy, int batch) {
-    const long long total = (long long)m * n;
-    for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < total;
-         e += (long long)gridDim.x * blockDim.x) {
-        const long long j = e / m, i = e - j * m;
-        const double v = X[i + j * ldx];
-        for (int b = 0; b < batch; ++b) Y[b * sy + i + j * ldy] = v;
-    }
-}
-
 // Z_b = G (upper triangle and diagonal) + shift_b I, strict lower part zero.
 template <class T>
 __global__ void shift_copy_kernel(int n, const T* __restrict__ G, long long ldg,
@@ -296,12 +284,6 @@ inline int grid_for(long long total) {
 hipError_t scale_copy(int m, int n, const double* A, long long lda, double* X, long long ldx, double s,
                       int* flag, hipStream_t st) {
     scale_copy_kernel<<<grid_for((long long)m * n), kThreads, 0, st>>>(m, n, A, lda, X, ldx, s, flag);
-    return hipGetLastError();
-}
-
-hipError_t broadcast_copy(int m, int n, const double* X, long long ldx, double* Y, long long ldy, long long sy,
-                          int batch, hipStream_t st) {
-    broadcast_copy_kernel<<<grid_for((long long)m * n), kThreads, 0, st>>>(m, n, X, ldx, Y, ldy, sy, batch);
     return hipGetLastError();
 }
 

@@ -14,8 +14,6 @@ struct ShiftArgs {
 // --- misc.hip -------------------------------------------------------------
 hipError_t scale_copy(int m, int n, const double* A, long long lda, double* X, long long ldx, double s,
                       int* nonfinite_flag, hipStream_t st);
-hipError_t broadcast_copy(int m, int n, const double* X, long long ldx, double* Y, long long ldy, long long sy,
-                          int batch, hipStream_t st);
 // The next four exist for T = double and T = float.
 template <class T>
 hipError_t shift_copy(int n, const T* G, long long ldg, T* Z, long long ldz, long long sz, const ShiftArgs& sh,

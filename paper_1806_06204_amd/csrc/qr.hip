@@ -1523,9 +1523,8 @@ inline int live_rows(int m, int e, int p0, int nb) {
 
 }  // namespace
 
-// The most panel workgroups one launch of either variant can use (the LDS
-// variant with its smallest slab packs the most per CU); sizes the buffers
-// of per-workgroup partial sums and flags.
+// The most panel workgroups one launch of any shape can use; sizes the buffers of
+// per-workgroup partial sums, flags and column slots.
 int panel_max_coresident() {
     int v = global_coresident();
     for (int i = 0; i < kNumLeafVariants; ++i) v = std::max(v, leaf_coresident(i));

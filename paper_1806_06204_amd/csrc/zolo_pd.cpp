@@ -78,14 +78,16 @@ struct CholBufs {
 };
 
 struct Work {
-    double *X, *Xn, *Y, *D, *G, *F, *trtri, *part, *scal, *vec_v, *vec_u, *vec_w, *lam;
-    int* iflags;  // [0] nonfinite, [1] panel error, [2..] potrf info per j (with scal and lam in the pinned buffer)
+    double *X, *Xn, *Y, *D, *G, *F, *trtri, *part, *vec_v, *vec_u, *vec_w;
+    // In the handle's pinned buffer (scalars_to_host).
+    double *scal, *lam;
+    int* iflags;  // [0] nonfinite, [1] panel error, [2..] potrf info per j
     QrWork qr;
     CholBufs<float> s;  // FP32 copies for the mixed schedule (null unless requested)
     double *sk, *feat;  // sketch scratch and the 39 features (learned l)
     float* mlp;         // network activations for one feature vector
     size_t bytes;
-    size_t counted;     // bytes without the tail that zolo_pd_noalloc's scratch holds beside its 256 MiB
+    size_t counted;     // what zolo_pd_noalloc holds against its 256 MiB
 };
 
 // Lay out (or size, if base == nullptr) the workspace for m x n and degree
@@ -102,14 +104,10 @@ Work layout(char* base, int m, int n, int rmax, int panel_coresident, bool mixed
     w.G = ar.take<double>(nn);
     w.F = ar.take<double>(nn);
     w.trtri = ar.take<double>(nn * rmax / 2 + (size_t)64 * 64 * rmax + 64);
-    ar.take<double>((size_t)64 * 64 * rmax);   // unused; keeps the counted size (zolo_pd_noalloc's limit) as it was
     w.part = ar.take<double>(4096);
-    w.scal = ar.take<double>(64);
     w.vec_v = ar.take<double>(n);
     w.vec_u = ar.take<double>(m);
     w.vec_w = ar.take<double>(n);
-    w.lam = ar.take<double>(128);
-    w.iflags = ar.take<int>(64);
     w.qr.W = ar.take<double>(qr_w_elems(n, rmax));
     w.qr.W2 = ar.take<double>(qr_w_elems(n, rmax));
     w.qr.T = ar.take<double>((size_t)rmax * npanels * kPanelNB * kPanelNB);
@@ -128,7 +126,6 @@ Work layout(char* base, int m, int n, int rmax, int panel_coresident, bool mixed
                                              qr_partials_elems(m, 0, 1, panel_coresident)));
     w.qr.flag_elems = std::max(qr_flag_elems(m, n, rmax, panel_coresident), qr_flag_elems(m, 0, 1, panel_coresident));
     w.qr.flags = ar.take<unsigned>(w.qr.flag_elems);
-    w.qr.error_flag = w.iflags + 1;
     w.qr.max_coresident = panel_coresident;
     w.sk = ar.take<double>(sketch_scratch_elems(m, n));
     w.feat = ar.take<double>(64);
@@ -142,9 +139,12 @@ Work layout(char* base, int m, int n, int rmax, int panel_coresident, bool mixed
         w.s.Z = ar.take<float>(nn * rmax);
         w.s.D = ar.take<float>(nn * rmax);
         w.s.trtri = ar.take<float>(nn * rmax / 2 + (size_t)64 * 64 * rmax + 64);
-        ar.take<float>((size_t)64 * 64 * rmax);   // as above
     }
-    w.counted = ar.off + 256;
+    // zolo_pd_noalloc's limit is part of its interface and stays where it was: it
+    // counts no column slots (the scratch has room for them past its 256 MiB), but
+    // blocks of 64 x 64 per factor and scalars that are not kept here any more.
+    w.counted = ar.off + 256 + sizeof(double) * ((size_t)64 * 64 * rmax + 64 + 128) + 256;
+    if (mixed) w.counted += ((256 - ar.off % 256) % 256) + sizeof(float) * 64 * 64 * rmax;
     w.qr.colslot_elems = std::max(qr_colslot_elems(m, n, rmax, panel_coresident),
                                   qr_colslot_elems(m, 0, 1, panel_coresident));
     w.qr.colslots = ar.take<unsigned long long>(w.qr.colslot_elems);
