@@ -401,23 +401,27 @@ __global__ void trd_cleanup(int n, double* A, long long lda, double* d) {
 // reflectors (28 ms of Zolo-SVD at n = 4096; 900 x 600: 3.6 of 36 ms).  With
 // this kernel, one launch for all blocks, S and V aligned for the pipelined
 // GEMM and 256 reflectors a block, the two calls went from 288 to 248 and from
-// 36.0 to 32.1 ms.
+// 36.0 to 32.1 ms.  Up to kFT reflectors in all there is one factor, of leading
+// dimension ld = kFT: one workgroup clears, merges and stores the columns there are, and
+// S need not hold zeros past them (with the blocks' whole 256 columns, cleared and merged
+// by two more products, order 2 took 204 us instead of 150, order 24 506 instead of 469).
 constexpr int kFTld = kFT + 2;
 constexpr size_t kFormTLds = (size_t)kFTld * kFT * sizeof(double);
-__global__ __launch_bounds__(512) void form_t(int nref, const double* S, const double* tau, double* T) {
+__global__ __launch_bounds__(512) void form_t(int nref, const double* S, const double* tau, double* T, int ld) {
     extern __shared__ double Tl[];               // T[i][j] at i + j kFTld
     __shared__ double Sl[kFT / 16][16][17];      // S's 16 x 16 diagonal blocks
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int c0 = blockIdx.x * kFT, half = (blockIdx.x & 1) * kFT;
-    const long long blk = (long long)(blockIdx.x >> 1) * kBT * kBT;
-    const double* Sb = S + blk + half + (long long)half * kBT;
-    for (int e = tid; e < kFTld * kFT; e += 512) Tl[e] = 0.0;
-    for (int e = tid; e < kFT * 16; e += 512) {
+    const long long blk = (long long)(blockIdx.x >> 1) * ld * ld;
+    const double* Sb = S + blk + half + (long long)half * ld;
+    const int cols = ld == kFT ? (nref + 15) / 16 * 16 : kFT;
+    for (int e = tid; e < kFTld * cols; e += 512) Tl[e] = 0.0;
+    for (int e = tid; e < cols * 16; e += 512) {
         const int q = e / 256, r = e % 16, c = (e / 16) % 16;
-        Sl[q][r][c] = r < c ? Sb[16 * q + r + (long long)(16 * q + c) * kBT] : 0.0;
+        Sl[q][r][c] = r < c && c0 + 16 * q + c < nref ? Sb[16 * q + r + (long long)(16 * q + c) * ld] : 0.0;
     }
     __syncthreads();
-    {
+    if (16 * w < cols) {
         // T[i][c] = -tau_c sum_{i <= k < c} T[i][k] S[k][c], T[c][c] = tau_c.
         const int i = lane & 15;
         double row[16];
@@ -437,7 +441,7 @@ __global__ __launch_bounds__(512) void form_t(int nref, const double* S, const d
     }
     __syncthreads();
     const int li = lane & 15, lk = lane >> 4;
-    for (int s = 16; s < kFT; s *= 2) {
+    for (int s = 16; s < cols; s *= 2) {
         const int ts = s / 16, per = ts * ts;    // 16 x 16 tiles of one merge
         const int total = kFT / (2 * s) * per;   // 4, 8, 16
         d4 acc[2];
@@ -449,11 +453,14 @@ __global__ __launch_bounds__(512) void form_t(int nref, const double* S, const d
                 acc[u] = d4{0, 0, 0, 0};
                 if (tile >= total) continue;
                 const int o = tile / per * 2 * s, ti = tile % per % ts * 16, tj = tile % per / ts * 16;
-                for (int k = 0; k < s; k += 4) {
+                if (o + s + tj >= cols) continue;      // no columns there
+                const int kend = phase == 0 ? min(s, tj + 16) : s;   // T2 is zero below its diagonal
+                for (int k = 0; k < kend; k += 4) {
                     double x, y;
                     if (phase == 0) {
-                        x = Sb[o + ti + li + (long long)(o + s + k + lk) * kBT];
-                        y = Tl[o + s + k + lk + (o + s + tj + li) * kFTld];
+                        const int at = o + s + k + lk;
+                        x = c0 + at < nref ? Sb[o + ti + li + (long long)at * ld] : 0.0;
+                        y = Tl[at + (o + s + tj + li) * kFTld];
                     } else {
                         x = Tl[o + ti + li + (o + k + lk) * kFTld];
                         y = Tl[o + k + lk + (o + s + tj + li) * kFTld];
@@ -467,6 +474,7 @@ __global__ __launch_bounds__(512) void form_t(int nref, const double* S, const d
                 const int tile = w + 8 * u;
                 if (tile >= total) continue;
                 const int o = tile / per * 2 * s, ti = tile % per % ts * 16, tj = tile % per / ts * 16;
+                if (o + s + tj >= cols) continue;
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
                     Tl[o + ti + Mfma<double>::row(lane, e) + (o + s + tj + li) * kFTld] =
@@ -476,11 +484,11 @@ __global__ __launch_bounds__(512) void form_t(int nref, const double* S, const d
         }
     }
     // The diagonal block of T, and zeros below it.
-    double* Tb = T + blk + (long long)half * kBT;
-    for (int e = tid; e < kFT * kFT; e += 512) {
+    double* Tb = T + blk + (long long)half * ld;
+    for (int e = tid; e < kFT * cols; e += 512) {
         const int i = e % kFT, j = e / kFT;
-        Tb[half + i + (long long)j * kBT] = Tl[i + j * kFTld];
-        if (half == 0) Tb[kFT + i + (long long)j * kBT] = 0.0;
+        Tb[half + i + (long long)j * ld] = Tl[i + j * kFTld];
+        if (half == 0 && ld == kBT) Tb[kFT + i + (long long)j * ld] = 0.0;
     }
 }
 
@@ -755,12 +763,15 @@ T* carve(char*& p, size_t count) {
 
 }  // namespace
 
+// Leading dimension of the T factors (and of S): one of at most kFT reflectors, or
+// blocks of kBT.
+static int factor_ld(int nref) { return nref <= kFT ? kFT : kBT; }
 static size_t row_groups_max(int n) { return ((size_t)n + kTrdRows - 1) / kTrdRows; }
 
 size_t syevd_work_bytes(int n) {
     const size_t nn = (size_t)n * n, N = (size_t)n + 64;
-    const size_t nblk = ((size_t)n + kBT - 1) / kBT;
-    return 3 * (nn * 8 + 256) + (size_t)n * kTB * 8 + 256 + nblk * (2 * kBT * kBT + kFT * kFT) * 8 + 768 +
+    const size_t nblk = ((size_t)n - 1 + kBT - 1) / kBT, ldf = factor_ld(n - 1);
+    return 3 * (nn * 8 + 256) + (size_t)n * kTB * 8 + 256 + nblk * (2 * ldf * ldf + kFT * kFT) * 8 + 768 +
            2 * ((size_t)n * 2 * kTB * 8 + 256) + 22 * (N * 8 + 256) + 10 * (N * 4 + 256) +
            2 * (row_groups_max(n) * 8 + 256) + 2 * kMaxG * 8 + kMaxParts * 8 + 4096;
 }
@@ -780,8 +791,9 @@ hipError_t syevd(int n, double* A, long long lda, double* w_host, double* Z, lon
     double* U = carve<double>(p, (size_t)n * n);
     double* W = carve<double>(p, (size_t)n * kTB);
     const int nref = n - 1, nblk = (nref + kBT - 1) / kBT;
-    double* S = carve<double>(p, (size_t)nblk * kBT * kBT);
-    double* Tf = carve<double>(p, (size_t)nblk * kBT * kBT);
+    const int ldf = factor_ld(nref);
+    double* S = carve<double>(p, (size_t)nblk * ldf * ldf);
+    double* Tf = carve<double>(p, (size_t)nblk * ldf * ldf);
     double* Y = carve<double>(p, (size_t)nblk * kFT * kFT);
     const size_t N = (size_t)n + 64;
     double *d = carve<double>(p, N), *e = carve<double>(p, N), *tau = carve<double>(p, N), *xa = carve<double>(p, N);
@@ -913,7 +925,8 @@ hipError_t syevd(int n, double* A, long long lda, double* w_host, double* Z, lon
     if (nref > 0) {
         // S = V^T V of every block at once (upper tiles; the rows above a
         // block are zero), then the T factors.
-        if ((err = fill_matrix<double>(kBT, kBT * nblk, S, kBT, 0, 1, 0.0, 0.0, st)) != hipSuccess) return err;
+        const bool one = ldf == kFT;
+        if (!one && (err = fill_matrix<double>(kBT, kBT * nblk, S, kBT, 0, 1, 0.0, 0.0, st)) != hipSuccess) return err;
         const int fullb = nref / kBT;
         for (int part = 0; part < 2; ++part) {
             const long long b0 = part == 0 ? 0 : (long long)fullb * kBT;
@@ -924,14 +937,14 @@ hipError_t syevd(int n, double* A, long long lda, double* w_host, double* Z, lon
             if (g.m <= 0 || g.batch <= 0) continue;
             g.A = g.B = A + b0 + b0 * lda; g.lda = g.ldb = lda;
             g.strideA = g.strideB = (long long)kBT * lda;
-            g.C = S + (b0 / kBT) * kBT * kBT; g.ldc = kBT; g.strideC = (long long)kBT * kBT;
+            g.C = S + (b0 / kBT) * kBT * kBT; g.ldc = ldf; g.strideC = (long long)kBT * kBT;
             g.flags = kCUpperTiles | kCStoreUpper;
             if ((err = gemm(g, st)) != hipSuccess) return err;
         }
         if ((err = hipFuncSetAttribute((const void*)form_t, hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)kFormTLds)) != hipSuccess)
             return err;
-        form_t<<<2 * nblk, 512, kFormTLds, st>>>(nref, S, tau, Tf);
+        form_t<<<one ? 1 : 2 * nblk, 512, kFormTLds, st>>>(nref, S, tau, Tf, ldf);
         if ((err = hipGetLastError()) != hipSuccess) return err;
         GemmDesc y;  // Y = S12 T2
         y.m = y.n = y.k = kFT; y.batch = nblk;
@@ -939,14 +952,14 @@ hipError_t syevd(int n, double* A, long long lda, double* w_host, double* Z, lon
         y.B = Tf + kFT + (long long)kFT * kBT; y.ldb = kBT; y.strideB = (long long)kBT * kBT;
         y.C = Y; y.ldc = kFT; y.strideC = (long long)kFT * kFT;
         y.flags = kBUpper;
-        if ((err = gemm(y, st)) != hipSuccess) return err;
+        if (!one && (err = gemm(y, st)) != hipSuccess) return err;
         GemmDesc t;  // T12 = -T1 Y
         t.m = t.n = t.k = kFT; t.batch = nblk;
         t.A = Tf; t.lda = kBT; t.strideA = (long long)kBT * kBT;
         t.B = Y; t.ldb = kFT; t.strideB = (long long)kFT * kFT;
         t.C = Tf + (long long)kFT * kBT; t.ldc = kBT; t.strideC = (long long)kBT * kBT;
         t.alpha = -1.0; t.flags = kAUpper;
-        if ((err = gemm(t, st)) != hipSuccess) return err;
+        if (!one && (err = gemm(t, st)) != hipSuccess) return err;
     }
     const long long ldt = std::min(kBT, n);   // scratch U, Qb hold nb x n with nb <= ldt
     for (int q = nblk - 1; q >= 0; --q) {
@@ -960,7 +973,7 @@ hipError_t syevd(int n, double* A, long long lda, double* w_host, double* Z, lon
         if ((err = gemm(w1, st)) != hipSuccess) return err;
         GemmDesc w2;  // Qb = T U
         w2.m = nb; w2.n = n; w2.k = nb;
-        w2.A = Tf + (long long)q * kBT * kBT; w2.lda = kBT; w2.B = U; w2.ldb = ldt; w2.C = Qb; w2.ldc = ldt;
+        w2.A = Tf + (long long)q * kBT * kBT; w2.lda = ldf; w2.B = U; w2.ldb = ldt; w2.C = Qb; w2.ldc = ldt;
         w2.flags = kAUpper;
         if ((err = gemm(w2, st)) != hipSuccess) return err;
         GemmDesc w3;  // Z[b0:, :] -= V Qb
