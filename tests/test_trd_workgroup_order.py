@@ -79,7 +79,7 @@ def source():
     consts = "".join(re.findall(r"^constexpr int k(?:TB|BT|FT|ET|MaxG)\b.*\n", src, flags=re.M))
     hh = between(common, "__device__ __forceinline__ void householder", "// Number of XCDs")
     kernels = between(src, "struct TrdArgs {", "// T factors (compact WY)")
-    sizes = between(src, "static size_t row_groups_max", "// Eigen-decomposition of the symmetric")
+    sizes = between(src, "static int factor_ld", "// Eigen-decomposition of the symmetric")
     setup = between(src, "    char* p = work;", "    // --- Stage 1")
     loop = between(src, "    // --- Stage 1", "    // --- Stage 2")
     loop = host_lanes.launches(loop)
