@@ -152,10 +152,14 @@ int predict_kinds(double l, int r, double chol_switch, char* kinds, int max_step
     return k;
 }
 
-// Cost model of one solve on one MI355X, fitted to solves of this library
-// (n = 8192: the QR-type step of degree 8 takes 596 ms of which the
-// 64-column panels take 75 ms, a Cholesky-type step 144 ms; the sweep over
-// r of the same matrix sets the panel and small-r terms).  The matrix-core
+// Cost model of one solve on one MI355X, fitted to solves with earlier kernels
+// (n = 8192: the QR-type step of degree 8 took 596 ms of which the 64-column
+// panels took 75 ms, a Cholesky-type step 144 ms; the sweep over r of the same
+// matrix set the panel and small-r terms).  With the present kernels these take
+// 489, 32 and 120 ms: over r = 1..8 at l = 1e-16 the model is between 4 % below and
+// 29 % above the measured time, and the degree of least predicted time is the
+// fastest at n = 2048 and 8192, but r = 8 at 1024 (9.2 ms; r = 5 takes 8.2) and r = 5 at
+// 4096 (107 ms; r = 1 takes 93).  The matrix-core
 // products run at kRate once they fill the chip; below kFill flops per
 // launch the rate falls in proportion (launch latency and too few tiles).
 namespace {
