@@ -7,6 +7,10 @@
 #include <cstddef>
 #include <vector>
 
+// Pinned bytes of a handle: 512 words for copies and scalars, and one more for
+// the scale that the eigensolver reads back behind its eigenvalues.
+constexpr size_t kPinnedBytes = 4096 + 64;
+
 struct zolo_handle_s {
     hipStream_t stream = nullptr;
     int device = 0;

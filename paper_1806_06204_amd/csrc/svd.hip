@@ -31,7 +31,7 @@ struct Scratch {
     }
 };
 
-// Pinned host buffer of n + 1 doubles (the handle's 4 KiB one when it suffices).
+// Pinned host buffer of n + 1 doubles (the handle's when it suffices, n <= 519).
 struct HostBuf {
     double* p = nullptr;
     bool own = false;
@@ -57,7 +57,7 @@ extern "C" int zolo_dsyevd(zolo_handle h, int n, const double* A, int lda, doubl
     double* Ac = reinterpret_cast<double*>(buf.p);
     char* work = buf.p + ((sizeof(double) * nn + 255) / 256) * 256;
     HostBuf hb;
-    if (((size_t)n + 1) * sizeof(double) <= 4096) {
+    if (((size_t)n + 1) * sizeof(double) <= kPinnedBytes) {
         hb.p = h->host;
     } else {
         if (hipHostMalloc((void**)&hb.p, sizeof(double) * ((size_t)n + 1)) != hipSuccess) return ZOLO_ALLOC;
@@ -95,7 +95,7 @@ extern "C" int zolo_svd(zolo_handle h, int m, int n, const double* A, int lda, d
     double* Qtmp = reinterpret_cast<double*>(buf.p + round(sizeof(double) * nn));
     char* work = buf.p + round(sizeof(double) * nn) + round(sizeof(double) * mn);
     HostBuf hb;
-    if (((size_t)n + 1) * sizeof(double) <= 4096) {
+    if (((size_t)n + 1) * sizeof(double) <= kPinnedBytes) {
         hb.p = h->host;
     } else {
         if (hipHostMalloc((void**)&hb.p, sizeof(double) * ((size_t)n + 1)) != hipSuccess) return ZOLO_ALLOC;

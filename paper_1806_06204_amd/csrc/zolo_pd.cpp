@@ -391,7 +391,7 @@ int ensure_workers(zolo_handle h, int want, size_t need) {
         x->panel_stream = h->worker_panel_stream;
         x->single_panels = true;
         bool ok = hipStreamCreate(&x->stream) == hipSuccess;
-        ok = ok && hipHostMalloc((void**)&x->host, 4096, hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess;
+        ok = ok && hipHostMalloc((void**)&x->host, kPinnedBytes, hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess;
         ok = ok && hipEventCreateWithFlags(&x->ev_ready, hipEventDisableTiming) == hipSuccess;
         ok = ok && hipEventCreateWithFlags(&x->ev_done, hipEventDisableTiming) == hipSuccess;
         h->workers.push_back(x);
@@ -737,7 +737,7 @@ int zolo_create(zolo_handle* out, void* stream) {
         delete h;
         return ZOLO_HIP;
     }
-    if (hipHostMalloc((void**)&h->host, 4096, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
+    if (hipHostMalloc((void**)&h->host, kPinnedBytes, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
         delete h;
         return ZOLO_HIP;
     }
